@@ -79,8 +79,9 @@ __device__ __forceinline__ d4v mfma4d(double a, double b, d4v c) {
 }
 
 // Eight consecutive elements of A = M + err_prev (columns c..c+7 of one row),
-// kept as raw loads until used.  Out-of-range or unaligned chunks hold the
-// exact element-wise A in e0/e1 and -0 in m (x + -0 == x for every x).
+// kept as raw loads until used.  Chunks across the end of a row (or past the
+// rows) hold the exact element-wise A in e0/e1 and -0 in m (x + -0 == x for
+// every x).
 template <int DT> struct Ch8;
 template <> struct Ch8<DT_BF16> { uint4 m; float4 e0, e1; };
 template <> struct Ch8<DT_F32> { float4 m0, m1; float4 e0, e1; };
@@ -98,27 +99,27 @@ __device__ __forceinline__ void ch8_neg_zero(Ch8<DT>& x) {
 template <int DT, bool VEC, bool RM = false>
 __device__ __forceinline__ Ch8<DT> ch8_load(const Desc& d, int row, int c, int c_hi) {
   Ch8<DT> x;
-  if (VEC && row < d.m && c + 8 <= c_hi) {
+  if (row < d.m && c + 8 <= c_hi) {
     const int64_t pr = prow<RM>(d, row);
     const int64_t mo = pr * d.ldm + c;
     if constexpr (DT == DT_BF16) {
-      x.m = *(const uint4*)((const uint16_t*)d.M + mo);
+      x.m = ld_h8<VEC>((const uint16_t*)d.M + mo);
     } else {
-      x.m0 = *(const float4*)((const float*)d.M + mo);
-      x.m1 = *(const float4*)((const float*)d.M + mo + 4);
+      x.m0 = ld_f4<VEC>((const float*)d.M + mo);
+      x.m1 = ld_f4<VEC>((const float*)d.M + mo + 4);
     }
     if (d.err_in) {
       const float* e = d.err_in + pr * d.lde_in + c;
-      x.e0 = *(const float4*)e;
-      x.e1 = *(const float4*)(e + 4);
+      x.e0 = ld_f4<VEC>(e);
+      x.e1 = ld_f4<VEC>(e + 4);
     } else {
       x.e0 = make_float4(-0.f, -0.f, -0.f, -0.f);
       x.e1 = x.e0;
     }
   } else {
     float lo[4], hi[4];
-    load_a4<DT, false, RM>(d, row, c, c_hi, lo);
-    load_a4<DT, false, RM>(d, row, c + 4, c_hi, hi);
+    load_a4<DT, RM>(d, row, c, c_hi, lo);
+    load_a4<DT, RM>(d, row, c + 4, c_hi, hi);
     ch8_neg_zero<DT>(x);
     x.e0 = make_float4(lo[0], lo[1], lo[2], lo[3]);
     x.e1 = make_float4(hi[0], hi[1], hi[2], hi[3]);
@@ -670,7 +671,7 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
   }
   const int cl = 4 * (lane % MX_LPR), rl = lane / MX_LPR;
   const int col = c0 + cl;
-  const bool vec_col = VEC && col + 4 <= d.n;
+  const bool vec_col = col + 4 <= d.n;
   float* tile = sm.t[wave];
   for (int r0 = r_lo + 16 * wave; r0 < r_hi; r0 += F_MHGROUP) {
     AChunk<DT> x[MX_NCH];
@@ -712,18 +713,29 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
       }
       if (vec_col) {
         // streaming outputs: nontemporal stores (the dirty lines would
-        // otherwise be written back during the next step's first pass)
+        // otherwise be written back during the next step's first pass).
+        // Rows at element alignment: plain stores, whose partly written
+        // lines meet in the L2 (nontemporal ones go out line by line,
+        // 3.0 against 6.0 TB/s)
         typedef float nt4 __attribute__((ext_vector_type(4)));
         typedef uint32_t nu2 __attribute__((ext_vector_type(2)));
-        if (WRITE_MHAT && OUTBF)
-          __builtin_nontemporal_store(nu2{bf16_pack2(mh[0], mh[1]), bf16_pack2(mh[2], mh[3])},
-                                      (nu2*)((uint16_t*)d.Mhat + pr * d.ldh + col));
-        else if (WRITE_MHAT)
-          __builtin_nontemporal_store(nt4{mh[0], mh[1], mh[2], mh[3]},
-                                      (nt4*)(d.Mhat + pr * d.ldh + col));
-        if (WRITE_ERR)
-          __builtin_nontemporal_store(nt4{e[0], e[1], e[2], e[3]},
-                                      (nt4*)(d.err_out + pr * d.lde_out + col));
+        if (WRITE_MHAT && OUTBF) {
+          const nu2 v = {bf16_pack2(mh[0], mh[1]), bf16_pack2(mh[2], mh[3])};
+          uint16_t* o = (uint16_t*)d.Mhat + pr * d.ldh + col;
+          if (VEC) __builtin_nontemporal_store(v, (nu2*)o);
+          else *(u2h_t*)o = v;
+        } else if (WRITE_MHAT) {
+          const nt4 v = {mh[0], mh[1], mh[2], mh[3]};
+          float* o = d.Mhat + pr * d.ldh + col;
+          if (VEC) __builtin_nontemporal_store(v, (nt4*)o);
+          else *(f4u_t*)o = v;
+        }
+        if (WRITE_ERR) {
+          const nt4 v = {e[0], e[1], e[2], e[3]};
+          float* o = d.err_out + pr * d.lde_out + col;
+          if (VEC) __builtin_nontemporal_store(v, (nt4*)o);
+          else *(f4u_t*)o = v;
+        }
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {

@@ -97,6 +97,12 @@ void with_rp(int rp, F&& f) {
 }
 
 template <typename F>
+void with_bool(bool x, F&& f) {
+  if (x) f(std::true_type{});
+  else f(std::false_type{});
+}
+
+template <typename F>
 void with_dt_vec(int dt, bool vec, F&& f) {
   if (dt == DT_F32) {
     if (vec) f(std::integral_constant<int, DT_F32>{}, std::true_type{});
@@ -116,6 +122,13 @@ struct Span {
 };
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
+
+// Rows of the outputs (fp32 M_hat and err) on 64-byte boundaries.
+bool rows_nt(const Desc& d, bool mhat) {
+  const float* err = d.err_fin ? d.err_fin : d.err_out;
+  const int64_t lde = d.err_fin ? d.lde_fin : d.lde_out;
+  return aligned(err, 64) && lde % 16 == 0 && (!mhat || (aligned(d.Mhat, 64) && d.ldh % 16 == 0));
+}
 
 size_t elem_size(int dt) { return dt == OCC_BF16 ? 2 : 4; }
 
@@ -156,7 +169,8 @@ occ_status_t check_shape(int64_t m, int64_t n, int64_t ld) {
 struct Batch {
   std::vector<Desc> descs;
   int rp = 4, dt = 0, iters = 1;
-  bool vec = false;
+  bool vec = false;   // rows of M, err and M_hat 16-byte aligned
+  bool nt = false;    // ... and those of err and M_hat on 64-byte boundaries
   bool fused = false;
   int64_t blocks[K_NUM] = {};
   size_t ws_needed = 0;
@@ -184,17 +198,17 @@ Slots device_slots_for(int dev) {
                  &bp, k_lp<DT, RP, SA_MERR_SAVE, X3, true>, lp_block_rows(RP, X3) / 32 * kWave,
                  0) == hipSuccess;
   if constexpr (X3)
-    ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_lqx<DT_F32, RP, SA_SAVED, true>,
+    ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_lqx<DT_F32, RP, SA_SAVED, TILES_16>,
                                                             lqx_waves(RP) * kWave, 0) == hipSuccess;
   else
-    ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_lq<DT_F32, RP, SA_SAVED, true>,
+    ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_lq<DT_F32, RP, SA_SAVED, TILES_16>,
                                                             kBlock, 0) == hipSuccess;
   if constexpr (X3)
-    ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bm, k_mlx<RP, 0, true, true>, kBlock,
+    ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bm, k_mlx<RP, 0, true, true, true>, kBlock,
                                                             0) == hipSuccess;
   else
     ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                   &bm, k_ml<DT_F32, RP, SA_SAVED, 0, true, true>, kBlock, 0) == hipSuccess;
+                   &bm, k_ml<DT_F32, RP, SA_SAVED, 0, true, true, true>, kBlock, 0) == hipSuccess;
   if (!ok || bp < 1 || bq < 1 || bm < 1) {
     (void)hipGetLastError();
     return Slots{};
@@ -349,6 +363,7 @@ occ_status_t plan_batch(const occ_mat_t* mats, int count, int rank, int iters, u
   spans.push_back({(uintptr_t)ws, (uintptr_t)ws + b.ws_needed, true});
   if (overlaps(spans)) return OCC_E_ALIAS;
   b.vec = vec;
+  b.nt = vec;
 
   finalize_regions(b, ws);
   for (int j = 0; j < count; ++j) {
@@ -365,7 +380,7 @@ occ_status_t plan_batch(const occ_mat_t* mats, int count, int rank, int iters, u
     d.lde_in = (int32_t)a.lde;
     d.lde_out = (int32_t)a.lde;
     d.ldh = write_mhat ? (int32_t)a.ldh : 0;
-    d.vec = vec ? 1 : 0;
+    b.nt = b.nt && rows_nt(d, write_mhat);
   }
   return OCC_OK;
 }
@@ -426,10 +441,13 @@ occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish,
               (int)b.blocks[K_QRED]);
           }
           if (finish) {
-            if (write_mhat)
-              L("mhat_err", k_mh16<DT, VEC, RP, 0, true, true, false, RM>, b.blocks[K_MHAT]);
-            else
-              L("err_only", k_mh16<DT, VEC, RP, 0, false, true, false, RM>, b.blocks[K_MHAT]);
+            with_bool(b.nt, [&](auto NTc) {
+              constexpr bool NT = decltype(NTc)::value;
+              if (write_mhat)
+                L("mhat_err", k_mh16<DT, NT, RP, 0, true, true, false, RM>, b.blocks[K_MHAT]);
+              else
+                L("err_only", k_mh16<DT, NT, RP, 0, false, true, false, RM>, b.blocks[K_MHAT]);
+            });
           }
           return;
         }
@@ -481,34 +499,37 @@ occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish,
             // the stored A through LDS tiles under the same conditions
             constexpr int QXT = lqx_waves(RP) * kWave;
             if (saved && whole)
-              LB("pass_q_a", k_lqx<DT_F32, RP, SA_SAVED, TL>, b.blocks[K_PASS_Q], QXT);
+              LB("pass_q_a", k_lqx<DT_F32, RP, SA_SAVED, TILES_16>, b.blocks[K_PASS_Q], QXT);
             else if (saved)
-              LB("pass_q_a", k_lqx<DT_F32, RP, SA_SAVED, false>, b.blocks[K_PASS_Q], QXT);
+              LB("pass_q_a", k_lqx<DT_F32, RP, SA_SAVED, TILES_4>, b.blocks[K_PASS_Q], QXT);
             else
-              LB("pass_q", k_lqx<DT, RP, SA_MERR, false, RM>, b.blocks[K_PASS_Q], QXT);
+              LB("pass_q", k_lqx<DT, RP, SA_MERR, TILES_NONE>, b.blocks[K_PASS_Q], QXT);
           } else {
             if (saved && whole)
-              L("pass_q_a", k_lq<DT_F32, RP, SA_SAVED, TL>, b.blocks[K_PASS_Q]);
+              L("pass_q_a", k_lq<DT_F32, RP, SA_SAVED, TILES_16>, b.blocks[K_PASS_Q]);
             else if (saved)
-              L("pass_q_a", k_lq<DT_F32, RP, SA_SAVED, false>, b.blocks[K_PASS_Q]);
+              L("pass_q_a", k_lq<DT_F32, RP, SA_SAVED, TILES_4>, b.blocks[K_PASS_Q]);
             else
-              L("pass_q", k_lq<DT, RP, SA_MERR, false, RM>, b.blocks[K_PASS_Q]);
+              L("pass_q", k_lq<DT, RP, SA_MERR, TILES_NONE>, b.blocks[K_PASS_Q]);
           }
           L("q_reduce", k_qredl<RP>, b.blocks[K_QRED]);
         }
         if (finish) {
           // bf16 M: the reconstruction on bf16 matrix cores with split operands
-          if constexpr (X3) {
-            if (write_mhat)
-              L("mhat_err_a", k_mlx<RP, 0, true, true, false, RM>, b.blocks[K_MHAT]);
-            else
-              L("err_only_a", k_mlx<RP, 0, false, true, false, RM>, b.blocks[K_MHAT]);
-          } else {
-            if (write_mhat)
-              L("mhat_err_a", k_ml<DT_F32, RP, SA_SAVED, 0, true, true, false, RM>, b.blocks[K_MHAT]);
-            else
-              L("err_only_a", k_ml<DT_F32, RP, SA_SAVED, 0, false, true, false, RM>, b.blocks[K_MHAT]);
-          }
+          with_bool(b.nt, [&](auto NTc) {
+            constexpr bool NT = decltype(NTc)::value;
+            if constexpr (X3) {
+              if (write_mhat)
+                L("mhat_err_a", k_mlx<RP, 0, true, true, NT, false, RM>, b.blocks[K_MHAT]);
+              else
+                L("err_only_a", k_mlx<RP, 0, false, true, NT, false, RM>, b.blocks[K_MHAT]);
+            } else {
+              if (write_mhat)
+                L("mhat_err_a", k_ml<DT_F32, RP, SA_SAVED, 0, true, true, NT, false, RM>, b.blocks[K_MHAT]);
+              else
+                L("err_only_a", k_ml<DT_F32, RP, SA_SAVED, 0, false, true, NT, false, RM>, b.blocks[K_MHAT]);
+            }
+          });
         }
       }
     });
@@ -550,29 +571,27 @@ occ_status_t decompress_impl(const float* P, const float* Q, int64_t m, int64_t 
   d.Mhat = (float*)M_hat;
   d.ldh = (int32_t)ldh;
   d.mr = t.mr;
-  // 4 consecutive elements per vector store: 16 bytes (fp32) or 8 (bf16)
-  const bool vec = aligned(M_hat, 4 * es) && ldh % 4 == 0;
-  d.vec = vec ? 1 : 0;
+  const bool nt = aligned(M_hat, 64) && (size_t)ldh * es % 64 == 0;
   occ_status_t st = OCC_OK;
   with_rp(rp, [&](auto RPc) {
     constexpr int RP = decltype(RPc)::value;
     st = launch(OUTBF ? "decompress_bf16" : "decompress", s, [&] {
       const dim3 grid(grid_of(t.blocks[K_MHAT]));
-      if constexpr (RP > kFusedMaxRank) {
-        if (split)
-          hipLaunchKernelGGL((k_mlx<RP, 1, true, false, OUTBF>), grid, dim3(kBlock), 0, s,
-                             (const Desc*)nullptr, 1, d);
-        else
-          hipLaunchKernelGGL((k_ml<DT_F32, RP, SA_SAVED, 1, true, false, OUTBF>), grid,
-                             dim3(kBlock), 0, s, (const Desc*)nullptr, 1, d);
-      } else if (vec) {
-        // same code as the fused step's reconstruction pass
-        hipLaunchKernelGGL((k_mh16<DT_F32, true, RP, 1, true, false, OUTBF>), grid, dim3(kBlock),
-                           0, s, (const Desc*)nullptr, 1, d);
-      } else {
-        hipLaunchKernelGGL((k_mh16<DT_F32, false, RP, 1, true, false, OUTBF>), grid,
-                           dim3(kBlock), 0, s, (const Desc*)nullptr, 1, d);
-      }
+      with_bool(nt, [&](auto NTc) {
+        constexpr bool NT = decltype(NTc)::value;
+        if constexpr (RP > kFusedMaxRank) {
+          if (split)
+            hipLaunchKernelGGL((k_mlx<RP, 1, true, false, NT, OUTBF>), grid, dim3(kBlock), 0, s,
+                               (const Desc*)nullptr, 1, d);
+          else
+            hipLaunchKernelGGL((k_ml<DT_F32, RP, SA_SAVED, 1, true, false, NT, OUTBF>), grid,
+                               dim3(kBlock), 0, s, (const Desc*)nullptr, 1, d);
+        } else {
+          // same code as the fused step's reconstruction pass
+          hipLaunchKernelGGL((k_mh16<DT_F32, NT, RP, 1, true, false, OUTBF>), grid, dim3(kBlock),
+                             0, s, (const Desc*)nullptr, 1, d);
+        }
+      });
     });
   });
   return st;
@@ -801,7 +820,7 @@ occ_status_t occ_step_rows(const occ_mat_t* mat, const int32_t* rows, int64_t n_
   }
   b.vec = aligned(a.M, 16) && a.ldm % (dt == OCC_BF16 ? 8 : 4) == 0 && aligned(a.err, 16) &&
           a.lde % 4 == 0 && (!write_mhat || (aligned(a.M_hat, 16) && a.ldh % 4 == 0));
-  d.vec = b.vec ? 1 : 0;
+  b.nt = b.vec && rows_nt(d, write_mhat);
   return run_batch(b, ws, fl, true, write_mhat, s);
 }
 
@@ -847,7 +866,6 @@ occ_status_t occ_compress(const void* M, int m_dtype, int64_t m, int64_t n, int6
   d.Mhat = nullptr;
   b.vec = aligned(M, 16) && ldm % (m_dtype == OCC_BF16 ? 8 : 4) == 0 &&
           (!err_prev || (aligned(err_prev, 16) && lde % 4 == 0));
-  d.vec = b.vec ? 1 : 0;
   return run_batch(b, ws, (uint32_t*)ws, false, false, (hipStream_t)stream);
 }
 

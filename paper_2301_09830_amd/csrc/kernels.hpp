@@ -70,13 +70,13 @@ __device__ __forceinline__ int64_t prow(const Desc& d, int row) {
 // loads and stores at any address that is a multiple of the element size, so
 // rows that start at any element use the same instructions as aligned ones
 // (measured on a 1 GiB stream: loads at 4-byte alignment 5.1 TB/s, as aligned;
-// at 2-byte alignment 4.9 TB/s; stores at 4-byte alignment 3.4-6.0 TB/s plain
-// but 3.0 TB/s nontemporal, so misaligned rows are stored plainly).  `AL`
-// only states that the address is known to be naturally aligned.
+// at 2-byte alignment 4.9 TB/s).  `AL` only states that the address is known
+// to be naturally aligned.
 typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f2u_t __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u4h_t __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u2h_t __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u1h_t __attribute__((aligned(2)));
 
 template <bool AL>
 __device__ __forceinline__ float4 ld_f4(const float* p) {
@@ -106,6 +106,39 @@ __device__ __forceinline__ uint2 ld_h4(const uint16_t* p) {
   } else {
     const u2h_t v = *(const u2h_t*)p;
     return make_uint2(v[0], v[1]);
+  }
+}
+
+// One value, stored nontemporally or plainly.
+template <bool NT, class T>
+__device__ __forceinline__ void st_as(T v, T* p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+// Four consecutive elements of an output row.  NT (every output row on
+// 64-byte boundaries): nontemporal, since the dirty lines of these streaming
+// outputs would otherwise be written back during the next pass.  Other rows:
+// plain stores at element alignment, whose partly written lines meet in the
+// L2 (16-byte stores along rows 16 bytes off the 64-byte grid: 6.3 TB/s
+// plain, 3.1 TB/s nontemporal; on the grid 6.9 and 5.6-5.8).
+template <bool NT>
+__device__ __forceinline__ void store_f4(float* o, float a, float b, float c, float e) {
+  typedef float nt4 __attribute__((ext_vector_type(4)));
+  if constexpr (NT) __builtin_nontemporal_store(nt4{a, b, c, e}, (nt4*)o);
+  else *(f4u_t*)o = f4u_t{a, b, c, e};
+}
+
+template <bool OUTBF, bool NT, class D>
+__device__ __forceinline__ void store_mhat4(const D& d, int64_t off, float a, float b, float c,
+                                            float e) {
+  if constexpr (OUTBF) {
+    typedef uint32_t nu2 __attribute__((ext_vector_type(2)));
+    uint16_t* o = (uint16_t*)d.Mhat + off;
+    if constexpr (NT) __builtin_nontemporal_store(nu2{bf16_pack2(a, b), bf16_pack2(c, e)}, (nu2*)o);
+    else *(u2h_t*)o = u2h_t{bf16_pack2(a, b), bf16_pack2(c, e)};
+  } else {
+    store_f4<NT>(d.Mhat + off, a, b, c, e);
   }
 }
 

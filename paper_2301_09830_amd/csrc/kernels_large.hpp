@@ -59,6 +59,11 @@ __device__ __forceinline__ constexpr int mf32_row(int v, int g) {
 
 enum { SA_MERR = 0, SA_MERR_SAVE = 1, SA_SAVED = 2 };
 
+// How a streaming kernel brings A in: straight into registers, or into LDS
+// tiles by DMA in 16-byte pieces (rows 16-byte aligned, whole 32-column
+// steps) or in 4-byte pieces (any row of fp32, any width).
+enum { TILES_NONE = 0, TILES_16 = 1, TILES_4 = 2 };
+
 // W consecutive floats / 32-bit words (W a power of two, naturally aligned).
 template <int W>
 __device__ __forceinline__ void ld_f(const float* p, float* o) {
@@ -76,18 +81,36 @@ __device__ __forceinline__ void ld_f(const float* p, float* o) {
   }
 }
 
+// The same at element alignment, for rows of M, err and A that start at any
+// element (ld_h: W bf16 elements, W even, as W / 2 words).
 template <int W>
-__device__ __forceinline__ void ld_u(const uint32_t* p, uint32_t* o) {
+__device__ __forceinline__ void ldu_f(const float* p, float* o) {
   if constexpr (W == 1) {
     o[0] = *p;
   } else if constexpr (W == 2) {
-    const uint2 v = *(const uint2*)p;
-    o[0] = v.x; o[1] = v.y;
+    const f2u_t v = *(const f2u_t*)p;
+    o[0] = v[0]; o[1] = v[1];
   } else {
 #pragma unroll
     for (int j = 0; j < W; j += 4) {
-      const uint4 v = *(const uint4*)(p + j);
-      o[j] = v.x; o[j + 1] = v.y; o[j + 2] = v.z; o[j + 3] = v.w;
+      const f4u_t v = *(const f4u_t*)(p + j);
+      o[j] = v[0]; o[j + 1] = v[1]; o[j + 2] = v[2]; o[j + 3] = v[3];
+    }
+  }
+}
+
+template <int W>
+__device__ __forceinline__ void ldu_h(const uint16_t* p, uint32_t* o) {
+  if constexpr (W == 2) {
+    o[0] = *(const u1h_t*)p;
+  } else if constexpr (W == 4) {
+    const u2h_t v = *(const u2h_t*)p;
+    o[0] = v[0]; o[1] = v[1];
+  } else {
+#pragma unroll
+    for (int j = 0; j < W; j += 8) {
+      const u4h_t v = *(const u4h_t*)(p + j);
+      o[j / 2] = v[0]; o[j / 2 + 1] = v[1]; o[j / 2 + 2] = v[2]; o[j / 2 + 3] = v[3];
     }
   }
 }
@@ -104,10 +127,22 @@ __device__ __forceinline__ void st_f(float* p, const float* v) {
   }
 }
 
+template <int W>
+__device__ __forceinline__ void stu_f(float* p, const float* v) {
+  if constexpr (W == 1) {
+    *p = v[0];
+  } else if constexpr (W == 2) {
+    *(f2u_t*)p = f2u_t{v[0], v[1]};
+  } else {
+#pragma unroll
+    for (int j = 0; j < W; j += 4) *(f4u_t*)(p + j) = f4u_t{v[j], v[j + 1], v[j + 2], v[j + 3]};
+  }
+}
+
 // W consecutive elements of A (columns c..c+W-1 of one row) as raw loads,
-// converted only when used so that the loads stay in flight.  Elements that
-// are out of range, or that the vector path cannot take, hold the exact A
-// value (0 out of range) in e and -0 in m (x + -0 == x for every x).
+// converted only when used so that the loads stay in flight.  A chunk across
+// the end of the columns (or past the rows) holds the exact A values (0 out
+// of range) in e and -0 in m (x + -0 == x for every x).
 template <int DT, int SA, int W>
 struct RawA {
   static constexpr int MW = SA == SA_SAVED ? 1 : (DT == DT_BF16 ? (W >= 2 ? W / 2 : 1) : W);
@@ -116,25 +151,27 @@ struct RawA {
 };
 
 template <int DT, int SA, int W, bool RM = false>
-__device__ __forceinline__ RawA<DT, SA, W> rawa_load(const Desc& d, bool vec, int row, int c,
-                                                    int c_hi) {
+__device__ __forceinline__ RawA<DT, SA, W> rawa_load(const Desc& d, int row, int c, int c_hi) {
   RawA<DT, SA, W> x;
-  if (vec && row < d.m && c + W <= c_hi) {
+  if (row < d.m && c + W <= c_hi) {
     // M and err_prev rows through the row map; the stored A is compact
     const int64_t pr = SA == SA_SAVED ? (int64_t)row : prow<RM>(d, row);
     if constexpr (SA == SA_SAVED) {
-      ld_f<W>(d.err_out + pr * d.lde_out + c, x.e);
+      ldu_f<W>(d.err_out + pr * d.lde_out + c, x.e);
       x.m[0] = 0u;
     } else {
       if constexpr (DT == DT_BF16) {
         const uint16_t* mp = (const uint16_t*)d.M + pr * d.ldm + c;
         if constexpr (W == 1) x.m[0] = (uint32_t)(*mp) << 16;
-        else ld_u<W / 2>((const uint32_t*)mp, x.m);
+        else ldu_h<W>(mp, x.m);
       } else {
-        ld_u<W>((const uint32_t*)((const float*)d.M + pr * d.ldm + c), x.m);
+        float mv[W];
+        ldu_f<W>((const float*)d.M + pr * d.ldm + c, mv);
+#pragma unroll
+        for (int j = 0; j < W; ++j) x.m[j] = __float_as_uint(mv[j]);
       }
       if (d.err_in) {
-        ld_f<W>(d.err_in + pr * d.lde_in + c, x.e);
+        ldu_f<W>(d.err_in + pr * d.lde_in + c, x.e);
       } else {
 #pragma unroll
         for (int j = 0; j < W; ++j) x.e[j] = -0.f;
@@ -178,12 +215,12 @@ __device__ __forceinline__ float rawa_val(const RawA<DT, SA, W>& x, int j) {
 // stored A is read back by the next pass, and nontemporal stores measured
 // slower for the whole step.
 template <int W>
-__device__ __forceinline__ void a_store(const Desc& d, bool vec, int row, int c, int c_hi,
+__device__ __forceinline__ void a_store(const Desc& d, int row, int c, int c_hi,
                                         const float* a) {
   if (row >= d.m) return;
   float* p = d.err_out + (int64_t)row * d.lde_out + c;
-  if (vec && c + W <= c_hi) {
-    st_f<W>(p, a);
+  if (c + W <= c_hi) {
+    stu_f<W>(p, a);
   } else {
 #pragma unroll
     for (int j = 0; j < W; ++j)
@@ -407,7 +444,6 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
   // bf16 form 2 x RP x 32 x 2 B (the same count)
   constexpr int QF4 = L_KC * RP / 4 / NT;
   static_assert(QF4 * 4 * NT == L_KC * RP, "Q tile must split evenly");
-  const bool vec = d.vec != 0;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 31, g = lane >> 5;
   const int row_tiles = (d.m + LR - 1) / LR;
@@ -540,7 +576,7 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
     RawA<DT, SA, 16> ring[LP_DEPTH + 1];
 #pragma unroll
     for (int x = 0; x <= LP_DEPTH; ++x)
-      if (x < nk) ring[x] = rawa_load<DT, SA, 16, RM>(d, vec, row, kcol_of(c_lo, ks0, x, nk) + 16 * g, c_hi);
+      if (x < nk) ring[x] = rawa_load<DT, SA, 16, RM>(d, row, kcol_of(c_lo, ks0, x, nk) + 16 * g, c_hi);
     __syncthreads();
 
     int kc = kcol_of(c_lo, ks0, 0, nk);
@@ -549,12 +585,12 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
       float a[16];
 #pragma unroll
       for (int j = 0; j < 16; ++j) a[j] = rawa_val<DT, SA, 16>(ring[0], j);
-      if constexpr (SA == SA_MERR_SAVE) a_store<16>(d, vec, row, kc + 16 * g, c_hi, a);
+      if constexpr (SA == SA_MERR_SAVE) a_store<16>(d, row, kc + 16 * g, c_hi, a);
       mfma_step(a, it & 1);
 #pragma unroll
       for (int x = 0; x < LP_DEPTH; ++x) ring[x] = ring[x + 1];
       if (it + LP_DEPTH + 1 < nk)
-        ring[LP_DEPTH] = rawa_load<DT, SA, 16, RM>(d, vec, row, kcol_of(c_lo, ks0, it + LP_DEPTH + 1, nk) + 16 * g, c_hi);
+        ring[LP_DEPTH] = rawa_load<DT, SA, 16, RM>(d, row, kcol_of(c_lo, ks0, it + LP_DEPTH + 1, nk) + 16 * g, c_hi);
       if (it + 1 < nk) {
         // slot 0 now holds K-step it + 1
 #pragma unroll
@@ -1171,7 +1207,6 @@ __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
   constexpr int NU = RP / 32, CPL = lq_cpl(RP), BC = lq_block_cols(RP);
   constexpr int PF = L_QG * RP / 4;   // float4s of one P_hat stage
   static_assert(PF <= kBlock, "one float4 per thread per stage");
-  const bool vec = d.vec != 0;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 31, g = lane >> 5;
   const int t = threadIdx.x;
@@ -1205,7 +1240,7 @@ __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
     const int row = r_lo + 2 * ks + g;
-    cur[ks] = rawa_load<DT, SA, CPL, RM>(d, vec, row < r_hi ? row : d.m, col, d.n);
+    cur[ks] = rawa_load<DT, SA, CPL, RM>(d, row < r_hi ? row : d.m, col, d.n);
   }
   __syncthreads();
 
@@ -1223,7 +1258,7 @@ __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         const int row = rn + 2 * ks + g;
-        nxt[ks] = rawa_load<DT, SA, CPL, RM>(d, vec, row < r_hi ? row : d.m, col, d.n);
+        nxt[ks] = rawa_load<DT, SA, CPL, RM>(d, row < r_hi ? row : d.m, col, d.n);
       }
     }
 #pragma unroll
@@ -1260,13 +1295,16 @@ __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
     }
 }
 
-// TILES form of k_lq for the stored fp32 A (rows 16-byte aligned, n a
-// multiple of 32): both operands of a group come into LDS by DMA, AST - 1
-// groups ahead, so the loads in flight are not bounded by registers.
-//   A: each wave's 8 rows x 32 CPL columns, 8/CPL rows per 1 KB
-//      global_load_lds_dwordx4 (lane l: row l / (8 CPL), chunk l % (8 CPL));
-//      rows are contiguous in LDS, so the operand reads (lane (g, li): CPL
-//      floats of row 2ks + g at column CPL li) are conflict-free;
+// Tile forms of k_lq for the stored fp32 A: both operands of a group come
+// into LDS by DMA, AST - 1 groups ahead, so the loads in flight are not
+// bounded by registers.
+//   A: each wave's 8 rows x 32 CPL columns.  TILES_16 (rows 16-byte aligned,
+//      n a multiple of 32): 8/CPL rows per 1 KB global_load_lds_dwordx4 (lane
+//      l: row l / (8 CPL), chunk l % (8 CPL)).  TILES_4 (any rows, any n): the
+//      same bytes as 256-byte runs of global_load_lds_dword, whose source
+//      needs only the 4-byte alignment that fp32 always has.  Rows are
+//      contiguous in LDS, so the operand reads (lane (g, li): CPL floats of
+//      row 2ks + g at column CPL li) are conflict-free;
 //   P: the block's 8 rows x RP of P_hat (contiguous in memory), each wave
 //      copying RP/32 runs of 256 bytes with global_load_lds_dword.
 // Every wave issues the same number of loads per group, so one wait count
@@ -1276,7 +1314,7 @@ __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
 template <int RP>
 struct LQTile {
   static constexpr int CPL = lq_cpl(RP), NU = RP / 32;
-  static constexpr int NI = CPL;                       // A loads per wave and group
+  static constexpr int NI = CPL;                       // 1 KB pieces of A per wave and group
   static constexpr int NP = RP / 32;                   // P loads per wave and group
   static constexpr int A_BYTES = 1024 * CPL;           // one wave's A tile
   static constexpr int P_BYTES = L_QG * RP * 4;        // the block's P tile
@@ -1284,20 +1322,32 @@ struct LQTile {
   static constexpr int AST = RP >= 128 ? 4 : 3;        // stages (3 blocks per CU at rank 32)
 };
 
-template <int RP>
+template <int RP, int TILES>
 __device__ __forceinline__ void lq_tile_issue(const Desc& d, int r0, int r_last, int cw, int wave,
                                               uint8_t* stage) {
   using T = LQTile<RP>;
-  constexpr int CH = 8 * T::CPL, RPI = 8 / T::CPL;
   const int lane = threadIdx.x & 63;
-  const int rr = lane / CH, ch = lane % CH;
-  const int c = min(cw + 4 * ch, d.n - 4);
   uint8_t* adst = stage + wave * T::A_BYTES;
+  if constexpr (TILES == TILES_16) {
+    constexpr int CH = 8 * T::CPL, RPI = 8 / T::CPL;
+    const int rr = lane / CH, ch = lane % CH;
+    const int c = min(cw + 4 * ch, d.n - 4);
 #pragma unroll
-  for (int q = 0; q < T::NI; ++q) {
-    const int row = min(r0 + q * RPI + rr, r_last);
-    __builtin_amdgcn_global_load_lds((gvoid_t*)(d.err_out + (int64_t)row * d.lde_out + c),
-                                     (lvoid_t*)(adst + q * 1024), 16, 0, 0);
+    for (int q = 0; q < T::NI; ++q) {
+      const int row = min(r0 + q * RPI + rr, r_last);
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(d.err_out + (int64_t)row * d.lde_out + c),
+                                       (lvoid_t*)(adst + q * 1024), 16, 0, 0);
+    }
+  } else {
+    // columns past n: any element of the row (their results are not stored)
+#pragma unroll
+    for (int q = 0; q < 4 * T::NI; ++q) {
+      const int idx = 64 * q + lane;
+      const int row = min(r0 + idx / (32 * T::CPL), r_last);
+      const int c = min(cw + idx % (32 * T::CPL), d.n - 1);
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(d.err_out + (int64_t)row * d.lde_out + c),
+                                       (lvoid_t*)(adst + q * 256), 4, 0, 0);
+    }
   }
   uint8_t* pdst = stage + 4 * T::A_BYTES;
 #pragma unroll
@@ -1310,11 +1360,11 @@ __device__ __forceinline__ void lq_tile_issue(const Desc& d, int r0, int r_last,
   }
 }
 
-template <int RP>
+template <int RP, int TILES>
 __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* tiles) {
   using T = LQTile<RP>;
   constexpr int NU = T::NU, CPL = T::CPL, BC = lq_block_cols(RP), AST = T::AST;
-  constexpr int PER_GROUP = T::NI + T::NP;
+  constexpr int PER_GROUP = (TILES == TILES_16 ? T::NI : 4 * T::NI) + T::NP;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 31, g = lane >> 5;
   const int col_tiles = (d.n + BC - 1) / BC;
@@ -1333,7 +1383,7 @@ __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* til
 
 #pragma unroll
   for (int y = 0; y + 1 < AST; ++y)
-    if (y < ngrp) lq_tile_issue<RP>(d, r_lo + L_QG * y, r_last, cw, wave, tiles + y * T::STAGE);
+    if (y < ngrp) lq_tile_issue<RP, TILES>(d, r_lo + L_QG * y, r_last, cw, wave, tiles + y * T::STAGE);
 
   const uint32_t tbase = (uint32_t)(size_t)(lvoid_t*)tiles;
   int st_cur = 0;
@@ -1362,7 +1412,7 @@ __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* til
 
     const int st_new = st_cur == 0 ? AST - 1 : st_cur - 1;   // stage of group grp + AST - 1
     if (grp + AST - 1 < ngrp)
-      lq_tile_issue<RP>(d, r0 + L_QG * (AST - 1), r_last, cw, wave, tiles + st_new * T::STAGE);
+      lq_tile_issue<RP, TILES>(d, r0 + L_QG * (AST - 1), r_last, cw, wave, tiles + st_new * T::STAGE);
     st_cur = st_cur + 1 == AST ? 0 : st_cur + 1;
 
     const int nvalid = r_hi - r0 - g;   // rows 2ks + g of this group inside the split: 2ks < nvalid
@@ -1392,13 +1442,13 @@ __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* til
   (void)col;
 }
 
-template <int DT, int RP, int SA, bool TILES, bool RM = false>
+template <int DT, int RP, int SA, int TILES, bool RM = false>
 __global__ __launch_bounds__(kBlock) void k_lq(OCC_KARGS) {
   static_assert(!(TILES && RM), "the row map runs on the register form");
-  if constexpr (TILES) {
+  if constexpr (TILES != TILES_NONE) {
     static_assert(DT == DT_F32 && SA == SA_SAVED, "tiles hold the stored fp32 A");
     __shared__ __attribute__((aligned(16))) uint8_t tiles[LQTile<RP>::AST * LQTile<RP>::STAGE];
-#define B_(d, b) lq_tiles_body<RP>(d, b, tiles)
+#define B_(d, b) lq_tiles_body<RP, TILES>(d, b, tiles)
     OCC_DISPATCH_X(K_PASS_Q, B_)
 #undef B_
   } else {
@@ -1458,20 +1508,32 @@ struct LQXTile {
 };
 
 // Rows r0 .. r0+15 (clamped to r_last) of columns cw .. cw + 32 CPL - 1
-// (chunks past the last column read the row's last chunk instead; those
-// columns are never stored).
-template <int RP>
+// (pieces past the last column read the row's last piece instead; those
+// columns are never stored).  TILES_4: the same bytes, each slot as four
+// 256-byte runs of 4-byte pieces.
+template <int RP, int TILES>
 __device__ __forceinline__ void lqx_tile_issue(const Desc& d, int r0, int r_last, int cw, uint8_t* dst) {
   using T = LQXTile<RP>;
-  constexpr int CH = 8 * T::CPL;
   const int lane = threadIdx.x & 63;
-  const int rr = lane / CH, ch = lane % CH;
-  const int c = min(cw + 4 * ch, d.n - 4);
+  if constexpr (TILES == TILES_16) {
+    constexpr int CH = 8 * T::CPL;
+    const int rr = lane / CH, ch = lane % CH;
+    const int c = min(cw + 4 * ch, d.n - 4);
 #pragma unroll
-  for (int q = 0; q < T::NI; ++q) {
-    const int row = min(r0 + q * T::RPI + rr, r_last);
-    __builtin_amdgcn_global_load_lds((gvoid_t*)(d.err_out + (int64_t)row * d.lde_out + c),
-                                     (lvoid_t*)(dst + q * LQX_SLOT), 16, 0, 0);
+    for (int q = 0; q < T::NI; ++q) {
+      const int row = min(r0 + q * T::RPI + rr, r_last);
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(d.err_out + (int64_t)row * d.lde_out + c),
+                                       (lvoid_t*)(dst + q * LQX_SLOT), 16, 0, 0);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4 * T::NI; ++q) {
+      const int idx = 64 * q + lane;
+      const int row = min(r0 + idx / (32 * T::CPL), r_last);
+      const int c = min(cw + idx % (32 * T::CPL), d.n - 1);
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(d.err_out + (int64_t)row * d.lde_out + c),
+                                       (lvoid_t*)(dst + (q / 4) * LQX_SLOT + 256 * (q % 4)), 4, 0, 0);
+    }
   }
 }
 
@@ -1489,13 +1551,12 @@ __device__ __forceinline__ void lqx_tile_read(const uint8_t* src, int li, int g,
   }
 }
 
-template <int DT, int RP, int SA, bool TILES, bool RM = false>
+template <int DT, int RP, int SA, int TILES, bool RM = false>
 __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, uint8_t* tiles) {
   static_assert(!(TILES && RM), "the row map runs on the register form");
   constexpr int NU = RP / 32, CPL = lq_cpl(RP), BC = lq_block_cols(RP, true);
   constexpr int NW = lqx_waves(RP);
   constexpr int NLD = 2 * NU;                         // P tile load instructions per group
-  const bool vec = d.vec != 0;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 31, g = lane >> 5;
   const int col_tiles = (d.n + BC - 1) / BC;
@@ -1530,7 +1591,7 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int row = r0 + 8 * g + e;
-      x[e] = rawa_load<DT, SA, CPL, RM>(d, vec, row < r_hi ? row : d.m, col, d.n);
+      x[e] = rawa_load<DT, SA, CPL, RM>(d, row < r_hi ? row : d.m, col, d.n);
     }
   };
 
@@ -1545,7 +1606,7 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
   };
   const int so = lqx_slot(li, g) * 8;   // this lane's P operand, in bf16 elements
 
-  if constexpr (TILES) {
+  if constexpr (TILES != TILES_NONE) {
     // Per group: wait for this group's A tile and P share, barrier (every
     // wave's share of the P tile is in; every wave is done with the other P
     // stage), read the operands, issue the next group's P share and the A
@@ -1560,13 +1621,14 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
     if (ngrp > 0) p_issue(0, 0);
 #pragma unroll
     for (int y = 0; y + 1 < AST; ++y)
-      if (y < ngrp) lqx_tile_issue<RP>(d, r_lo + LQX_G * y, r_last, cw, wt + y * T::BYTES);
+      if (y < ngrp) lqx_tile_issue<RP, TILES>(d, r_lo + LQX_G * y, r_last, cw, wt + y * T::BYTES);
     int st_cur = 0;                         // A stage of group grp
     for (int grp = 0; grp < ngrp; ++grp) {
       const int r0 = r_lo + LQX_G * grp;
       if (AST > 2 && grp > 0 && grp + AST - 2 < ngrp) {
-        static_assert(T::NI <= 15, "vmcnt immediate");
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(T::NI) : "memory");
+        constexpr int NLA = TILES == TILES_16 ? T::NI : 4 * T::NI;   // loads of one A tile
+        static_assert(NLA <= 63, "vmcnt immediate");
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NLA) : "memory");
       } else {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       }
@@ -1621,7 +1683,7 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
       const int st_new = st_cur == 0 ? AST - 1 : st_cur - 1;   // stage of group grp + AST - 1
       if (grp + 1 < ngrp) p_issue(grp + 1, (grp + 1) & 1);
       if (grp + AST - 1 < ngrp)
-        lqx_tile_issue<RP>(d, r0 + LQX_G * (AST - 1), r_last, cw, wt + st_new * T::BYTES);
+        lqx_tile_issue<RP, TILES>(d, r0 + LQX_G * (AST - 1), r_last, cw, wt + st_new * T::BYTES);
       st_cur = st_cur + 1 == AST ? 0 : st_cur + 1;
       const int nvalid = r_hi - r0 - 8 * g;   // rows of this lane's half inside the split
 #pragma unroll
@@ -1697,7 +1759,7 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
   }
 }
 
-template <int DT, int RP, int SA, bool TILES, bool RM = false>
+template <int DT, int RP, int SA, int TILES, bool RM = false>
 __global__ __launch_bounds__(lqx_waves(RP) * kWave) void k_lqx(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) LQXSmem<RP> sm;
   __shared__ __attribute__((aligned(16)))
@@ -1713,9 +1775,8 @@ __global__ __launch_bounds__(lqx_waves(RP) * kWave) void k_lqx(OCC_KARGS) {
 // column li of rows mf32_row(v, g), so stores straight from it cover each
 // row in 128-byte pieces of 4-byte accesses.  Each tile goes through LDS
 // instead, and each lane then takes 16-byte pieces of rows: the stored A is
-// read, and M_hat and err written, with 16-byte accesses when the rows are
-// 16-byte aligned (d.vec).  The values are unchanged; only which lane
-// stores which element.
+// read, and M_hat and err written, with 16-byte accesses.  The values are
+// unchanged; only which lane stores which element.
 // -------------------------------------------------------------------------
 constexpr int LE_PITCH = 32 + 4;          // LDS row pitch (floats), 16-byte skew per row
 constexpr int LE_RPI = kWave / 8;         // rows per wave instruction (8 lanes x 16 bytes a row)
@@ -1724,7 +1785,7 @@ constexpr int LE_IT = 32 / LE_RPI;        // instructions per 32 x 32 tile
 // A (the stored fp32 A, compact rows) for this lane's pieces of the tiles
 // of columns cw + 32 c, c < NCT
 template <int NCT>
-__device__ __forceinline__ void lm_epi_load(const Desc& d, bool vec, int row0, int r_hi, int cw,
+__device__ __forceinline__ void lm_epi_load(const Desc& d, int row0, int r_hi, int cw,
                                             f4v (&a4)[NCT][LE_IT]) {
   const int lane = threadIdx.x & 63;
   const int rr = lane >> 3;
@@ -1737,8 +1798,8 @@ __device__ __forceinline__ void lm_epi_load(const Desc& d, bool vec, int row0, i
       const float* src = d.err_out + (int64_t)row * d.lde_out + col;
       f4v v = f4v{0.f, 0.f, 0.f, 0.f};
       if (row < r_hi) {
-        if (vec && col + 4 <= d.n) {
-          v = *(const f4v*)src;
+        if (col + 4 <= d.n) {
+          v = *(const f4u_t*)src;
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
@@ -1752,13 +1813,11 @@ __device__ __forceinline__ void lm_epi_load(const Desc& d, bool vec, int row0, i
 
 // The tiles acc[c][v] = M_hat[row0 + mf32_row(v, g)][cw + 32 c + li], one
 // at a time through LDS (ep: this wave's 32 x LE_PITCH floats), then M_hat
-// and err = A - M_hat stored by rows, nontemporal.
-template <int NCT, bool WM, bool WE, bool OUTBF, bool RM>
-__device__ __forceinline__ void lm_epi_store(const Desc& d, bool vec, int row0, int r_hi, int cw,
+// and err = A - M_hat stored by rows (NT: nontemporal).
+template <int NCT, bool WM, bool WE, bool OUTBF, bool RM, bool NT>
+__device__ __forceinline__ void lm_epi_store(const Desc& d, int row0, int r_hi, int cw,
                                              const f16v (&acc)[NCT], const f4v (&a4)[NCT][LE_IT],
                                              float* ep) {
-  typedef float nt4 __attribute__((ext_vector_type(4)));
-  typedef uint32_t nu2 __attribute__((ext_vector_type(2)));
   const int lane = threadIdx.x & 63;
   const int li = lane & 31, g = lane >> 5;
   const int rr = lane >> 3, cq = lane & 7;
@@ -1770,7 +1829,6 @@ __device__ __forceinline__ void lm_epi_store(const Desc& d, bool vec, int row0, 
     // operations in order, and the wait also orders them for the compiler
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     const int col = cw + 32 * c + 4 * cq;
-    const bool vec_col = vec && col + 4 <= d.n;
 #pragma unroll
     for (int it = 0; it < LE_IT; ++it) {
       const int tr = it * LE_RPI + rr;
@@ -1782,13 +1840,9 @@ __device__ __forceinline__ void lm_epi_store(const Desc& d, bool vec, int row0, 
 #pragma unroll
       for (int j = 0; j < 4; ++j) e[j] = WE ? a4[c][it][j] - mh[j] : 0.f;
       float* eo = RM ? d.err_fin + pr * d.lde_fin + col : d.err_out + pr * d.lde_out + col;
-      if (vec_col) {
-        if (WM && OUTBF)
-          __builtin_nontemporal_store(nu2{bf16_pack2(mh[0], mh[1]), bf16_pack2(mh[2], mh[3])},
-                                      (nu2*)((uint16_t*)d.Mhat + pr * d.ldh + col));
-        else if (WM)
-          __builtin_nontemporal_store(nt4{mh[0], mh[1], mh[2], mh[3]}, (nt4*)(d.Mhat + pr * d.ldh + col));
-        if (WE) __builtin_nontemporal_store(nt4{e[0], e[1], e[2], e[3]}, (nt4*)eo);
+      if (col + 4 <= d.n) {
+        if (WM) store_mhat4<OUTBF, NT>(d, pr * d.ldh + col, mh[0], mh[1], mh[2], mh[3]);
+        if (WE) store_f4<NT>(eo, e[0], e[1], e[2], e[3]);
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -1820,7 +1874,7 @@ __device__ __forceinline__ void lm_direct_load(const Desc& d, int row0, int cw, 
     }
 }
 
-template <int NCT, bool WM, bool WE, bool OUTBF, bool RM>
+template <int NCT, bool WM, bool WE, bool OUTBF, bool RM, bool NT>
 __device__ __forceinline__ void lm_direct_store(const Desc& d, int row0, int r_hi, int cw,
                                                 const f16v (&acc)[NCT], const float (&av)[NCT][16]) {
   const int lane = threadIdx.x & 63;
@@ -1835,12 +1889,12 @@ __device__ __forceinline__ void lm_direct_store(const Desc& d, int row0, int r_h
         const float mh = acc[c][v];
         const int64_t pr = prow<RM>(d, row);
         if (WM) {
-          if constexpr (OUTBF) __builtin_nontemporal_store(bf16_rne(mh), (uint16_t*)d.Mhat + pr * d.ldh + col);
-          else __builtin_nontemporal_store(mh, d.Mhat + pr * d.ldh + col);
+          if constexpr (OUTBF) st_as<NT>(bf16_rne(mh), (uint16_t*)d.Mhat + pr * d.ldh + col);
+          else st_as<NT>(mh, d.Mhat + pr * d.ldh + col);
         }
         if (WE)
-          __builtin_nontemporal_store(av[c][v] - mh, RM ? d.err_fin + pr * d.lde_fin + col
-                                                        : d.err_out + pr * d.lde_out + col);
+          st_as<NT>(av[c][v] - mh, RM ? d.err_fin + pr * d.lde_fin + col
+                                      : d.err_out + pr * d.lde_out + col);
       }
     }
   }
@@ -1867,12 +1921,11 @@ __device__ __forceinline__ void lm_stage_direct(const Desc& d, int row0, float (
   }
 }
 
-template <int DT, int RP, int SA, int SRC, bool WM, bool WE, bool OUTBF = false, bool RM = false>
+template <int DT, int RP, int SA, int SRC, bool WM, bool WE, bool NT, bool OUTBF = false, bool RM = false>
 __device__ __forceinline__ void lm_body(const Desc& d, int b, LMSmem<RP>& sm) {
   static_assert(!WE || SA == SA_SAVED, "the residual is formed from the stored A");
   constexpr int NCT = lm_tiles(RP), KP = RP / 2, BC = lm_block_cols(RP);
   constexpr bool EPI = lm_lds_epilogue(RP);
-  const bool vec = d.vec != 0;
   constexpr int SF = RP * 8 / kBlock;   // float4s per thread per P_hat tile
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 31, g = lane >> 5;
@@ -1927,7 +1980,7 @@ __device__ __forceinline__ void lm_body(const Desc& d, int b, LMSmem<RP>& sm) {
     f4v a4[EPI ? NCT : 1][LE_IT];
     float av[EPI ? 1 : NCT][16];
     if (WE) {
-      if constexpr (EPI) lm_epi_load<NCT>(d, vec, row0, r_hi, cw, a4);
+      if constexpr (EPI) lm_epi_load<NCT>(d, row0, r_hi, cw, a4);
       else lm_direct_load<NCT>(d, row0, cw, av);
     }
     f16v acc[NCT];
@@ -1940,8 +1993,8 @@ __device__ __forceinline__ void lm_body(const Desc& d, int b, LMSmem<RP>& sm) {
 #pragma unroll
       for (int c = 0; c < NCT; ++c) acc[c] = mfma32(a, qv[c][kp], acc[c]);
     }
-    if constexpr (EPI) lm_epi_store<NCT, WM, WE, OUTBF, RM>(d, vec, row0, r_hi, cw, acc, a4, sm.ep[wave]);
-    else lm_direct_store<NCT, WM, WE, OUTBF, RM>(d, row0, r_hi, cw, acc, av);
+    if constexpr (EPI) lm_epi_store<NCT, WM, WE, OUTBF, RM, NT>(d, row0, r_hi, cw, acc, a4, sm.ep[wave]);
+    else lm_direct_store<NCT, WM, WE, OUTBF, RM, NT>(d, row0, r_hi, cw, acc, av);
     if (more) {
       if (SRC == 0) {
 #pragma unroll
@@ -1957,10 +2010,10 @@ __device__ __forceinline__ void lm_body(const Desc& d, int b, LMSmem<RP>& sm) {
   }
 }
 
-template <int DT, int RP, int SA, int SRC, bool WM, bool WE, bool OUTBF = false, bool RM = false>
+template <int DT, int RP, int SA, int SRC, bool WM, bool WE, bool NT, bool OUTBF = false, bool RM = false>
 __global__ __launch_bounds__(kBlock) void k_ml(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) LMSmem<RP> sm;
-#define B_(d, b) lm_body<DT, RP, SA, SRC, WM, WE, OUTBF, RM>(d, b, sm)
+#define B_(d, b) lm_body<DT, RP, SA, SRC, WM, WE, NT, OUTBF, RM>(d, b, sm)
   OCC_DISPATCH_X(K_MHAT, B_)
 #undef B_
 }
@@ -2029,7 +2082,7 @@ __device__ __forceinline__ void lmx_stage(const f4v* pr, uint16_t (*dst)[32 * (R
   }
 }
 
-template <int RP, int SRC, bool WM, bool WE, bool OUTBF = false, bool RM = false>
+template <int RP, int SRC, bool WM, bool WE, bool NT, bool OUTBF = false, bool RM = false>
 __device__ __forceinline__ void lmx_body(const Desc& d, int b, LMXSmem<RP>& sm) {
   constexpr int NCT = lm_tiles(RP), KS = RP / 16, BC = lm_block_cols(RP);
   constexpr int SF = RP * 8 / kBlock;
@@ -2093,16 +2146,16 @@ __device__ __forceinline__ void lmx_body(const Desc& d, int b, LMXSmem<RP>& sm) 
         acc[c] = mfma32bf(al, bh[c][s2], acc[c]);
       }
     }
-    lm_direct_store<NCT, WM, WE, OUTBF, RM>(d, row0, r_hi, cw, acc, av);
+    lm_direct_store<NCT, WM, WE, OUTBF, RM, NT>(d, row0, r_hi, cw, acc, av);
     if (more) lmx_stage<RP>(pr, sm.p[(tile + 1) & 1]);
     __syncthreads();
   }
 }
 
-template <int RP, int SRC, bool WM, bool WE, bool OUTBF = false, bool RM = false>
+template <int RP, int SRC, bool WM, bool WE, bool NT, bool OUTBF = false, bool RM = false>
 __global__ __launch_bounds__(kBlock) void k_mlx(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) LMXSmem<RP> sm;
-#define B_(d, b) lmx_body<RP, SRC, WM, WE, OUTBF, RM>(d, b, sm)
+#define B_(d, b) lmx_body<RP, SRC, WM, WE, NT, OUTBF, RM>(d, b, sm)
   OCC_DISPATCH_X(K_MHAT, B_)
 #undef B_
 }

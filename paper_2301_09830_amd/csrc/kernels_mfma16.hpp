@@ -646,9 +646,11 @@ __device__ __forceinline__ void factor_load(const float* base, int r, int row, b
   }
 }
 
+// NT: the rows of M are 16-byte aligned and those of the outputs on 64-byte
+// boundaries (nontemporal stores, see store_f4).
 // OUTBF (stand-alone decompression only): M_hat is stored as bf16, each
 // element rounded to nearest even from the fp32 result.
-template <int DT, bool VEC, int RP, int SRC, bool WRITE_MHAT, bool WRITE_ERR, bool OUTBF = false,
+template <int DT, bool NT, int RP, int SRC, bool WRITE_MHAT, bool WRITE_ERR, bool OUTBF = false,
           bool RM = false>
 __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
   constexpr int S = RP / 4;        // MFMA K-steps (rank indices per lane group)
@@ -679,7 +681,7 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
 #pragma unroll
       for (int k = 0; k < MX_NCH; ++k) {
         const int row = r0 + rl + MX_RPI * k;
-        chunk_issue<DT, VEC, RM>(d, row < r_hi ? row : d.m, col, d.n, x[k]);
+        chunk_issue<DT, NT, RM>(d, row < r_hi ? row : d.m, col, d.n, x[k]);
       }
     }
     // B operand: P_hat[r0 + li][S g + s]
@@ -712,30 +714,8 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
         for (int j = 0; j < 4; ++j) e[j] = a[j] - mh[j];
       }
       if (vec_col) {
-        // streaming outputs: nontemporal stores (the dirty lines would
-        // otherwise be written back during the next step's first pass).
-        // Rows at element alignment: plain stores, whose partly written
-        // lines meet in the L2 (nontemporal ones go out line by line,
-        // 3.0 against 6.0 TB/s)
-        typedef float nt4 __attribute__((ext_vector_type(4)));
-        typedef uint32_t nu2 __attribute__((ext_vector_type(2)));
-        if (WRITE_MHAT && OUTBF) {
-          const nu2 v = {bf16_pack2(mh[0], mh[1]), bf16_pack2(mh[2], mh[3])};
-          uint16_t* o = (uint16_t*)d.Mhat + pr * d.ldh + col;
-          if (VEC) __builtin_nontemporal_store(v, (nu2*)o);
-          else *(u2h_t*)o = v;
-        } else if (WRITE_MHAT) {
-          const nt4 v = {mh[0], mh[1], mh[2], mh[3]};
-          float* o = d.Mhat + pr * d.ldh + col;
-          if (VEC) __builtin_nontemporal_store(v, (nt4*)o);
-          else *(f4u_t*)o = v;
-        }
-        if (WRITE_ERR) {
-          const nt4 v = {e[0], e[1], e[2], e[3]};
-          float* o = d.err_out + pr * d.lde_out + col;
-          if (VEC) __builtin_nontemporal_store(v, (nt4*)o);
-          else *(f4u_t*)o = v;
-        }
+        if (WRITE_MHAT) store_mhat4<OUTBF, NT>(d, pr * d.ldh + col, mh[0], mh[1], mh[2], mh[3]);
+        if (WRITE_ERR) store_f4<NT>(d.err_out + pr * d.lde_out + col, e[0], e[1], e[2], e[3]);
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -750,11 +730,11 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
   }
 }
 
-template <int DT, bool VEC, int RP, int SRC, bool WRITE_MHAT, bool WRITE_ERR, bool OUTBF = false,
+template <int DT, bool NT, int RP, int SRC, bool WRITE_MHAT, bool WRITE_ERR, bool OUTBF = false,
           bool RM = false>
 __global__ __launch_bounds__(kBlock) void k_mh16(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) MXSmem sm;
-#define B_(d, b) mh16_body<DT, VEC, RP, SRC, WRITE_MHAT, WRITE_ERR, OUTBF, RM>(d, b, sm)
+#define B_(d, b) mh16_body<DT, NT, RP, SRC, WRITE_MHAT, WRITE_ERR, OUTBF, RM>(d, b, sm)
   OCC_DISPATCH(K_MHAT, B_)
 #undef B_
 }

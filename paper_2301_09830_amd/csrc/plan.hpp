@@ -72,7 +72,6 @@ struct Desc {
   int32_t fused;         // 1: small-rank path (rank padded to <= 16)
   int32_t m_pad;         // large-rank path: rows of phat_t (multiple of 32)
   int32_t mr;            // rows per block of the reconstruction pass
-  int32_t vec;           // large-rank path: 16-byte vector loads allowed
   int32_t qr_cols;       // large-rank path: columns per block of the Q reduction (8 or 32)
 };
 

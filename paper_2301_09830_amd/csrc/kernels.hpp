@@ -388,17 +388,54 @@ __global__ __launch_bounds__(kBlock) void k_qredl(OCC_KARGS) {
 
 // ---------------------------------------------------------------------------
 // Stand-alone error update: err_new = (M + err_prev) - M_hat, elementwise,
-// same operation order as the fused pass.
+// same operation order as the fused pass.  Bound by memory (s_M + 12 bytes
+// an element); one element per thread and a 64-bit division per element ran
+// at 3.4 TB/s.  A thread takes EU_UNROLL chunks of four columns, all of
+// their loads in flight at once; chunk q of the matrix is row q / cpr,
+// columns 4 (q % cpr) .. + 3 (cpr chunks a row, the last one possibly short).
+// 8192 x 4096 bf16: 139 -> 71 us.
 // ---------------------------------------------------------------------------
-template <int DT>
-__global__ __launch_bounds__(kBlock) void k_err_update(Desc d) {
-  const int64_t total = (int64_t)d.m * d.n;
-  for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * kBlock) {
-    const int i = (int)(idx / d.n), c = (int)(idx % d.n);
-    const float a = load_a1<DT>(d, i, c);
-    const float mh = d.Mhat[(int64_t)i * d.ldh + c];
-    d.err_out[(int64_t)i * d.lde_out + c] = a - mh;
+constexpr int EU_UNROLL = 4;
+
+template <int DT, bool NT>
+__global__ __launch_bounds__(kBlock) void k_err_update(Desc d, uint32_t cpr) {
+  const int64_t total = (int64_t)d.m * cpr;
+  const int64_t step = (int64_t)gridDim.x * (kBlock * EU_UNROLL);
+  for (int64_t q0 = (int64_t)blockIdx.x * (kBlock * EU_UNROLL) + threadIdx.x; q0 < total; q0 += step) {
+    float4 m4[EU_UNROLL], e4[EU_UNROLL], h4[EU_UNROLL];
+    int row[EU_UNROLL], col[EU_UNROLL];
+#pragma unroll
+    for (int u = 0; u < EU_UNROLL; ++u) {
+      const int64_t q = q0 + kBlock * u;
+      row[u] = d.m;
+      if (q >= total) continue;
+      // 32-bit division where it is enough
+      row[u] = total <= 0xffffffffll ? (int)((uint32_t)q / cpr) : (int)(q / cpr);
+      col[u] = 4 * (int)(q - (int64_t)row[u] * cpr);
+      if (col[u] + 4 > d.n) continue;
+      const int64_t mo = (int64_t)row[u] * d.ldm + col[u];
+      if constexpr (DT == DT_F32) {
+        m4[u] = ld_f4<false>((const float*)d.M + mo);
+      } else {
+        const uint2 w = ld_h4<false>((const uint16_t*)d.M + mo);
+        m4[u] = make_float4(bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y));
+      }
+      e4[u] = d.err_in ? ld_f4<false>(d.err_in + (int64_t)row[u] * d.lde_in + col[u])
+                       : make_float4(-0.f, -0.f, -0.f, -0.f);
+      h4[u] = ld_f4<false>(d.Mhat + (int64_t)row[u] * d.ldh + col[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < EU_UNROLL; ++u) {
+      if (row[u] >= d.m) continue;
+      float* o = d.err_out + (int64_t)row[u] * d.lde_out + col[u];
+      if (col[u] + 4 <= d.n) {
+        store_f4<NT>(o, (m4[u].x + e4[u].x) - h4[u].x, (m4[u].y + e4[u].y) - h4[u].y,
+                     (m4[u].z + e4[u].z) - h4[u].z, (m4[u].w + e4[u].w) - h4[u].w);
+      } else {
+        for (int j = 0; col[u] + j < d.n; ++j)
+          o[j] = load_a1<DT>(d, row[u], col[u] + j) - d.Mhat[(int64_t)row[u] * d.ldh + col[u] + j];
+      }
+    }
   }
 }
 

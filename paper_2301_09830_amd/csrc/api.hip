@@ -20,6 +20,7 @@
 #include "kernels_small.hpp"
 #include "kernels_mfma16.hpp"
 #include "kernels_large.hpp"
+#include "kernels_dec.hpp"
 #include "sc_model.hpp"
 
 using namespace occ;
@@ -204,11 +205,11 @@ Slots device_slots_for(int dev) {
     ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_lq<DT_F32, RP, SA_SAVED, TILES_16>,
                                                             kBlock, 0) == hipSuccess;
   if constexpr (X3)
-    ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bm, k_mlx<RP, 0, true, true, true>, kBlock,
+    ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bm, k_mlx<RP, true, true>, kBlock,
                                                             0) == hipSuccess;
   else
     ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                   &bm, k_ml<DT_F32, RP, SA_SAVED, 0, true, true, true>, kBlock, 0) == hipSuccess;
+                   &bm, k_ml<RP, true, true>, kBlock, 0) == hipSuccess;
   if (!ok || bp < 1 || bq < 1 || bm < 1) {
     (void)hipGetLastError();
     return Slots{};
@@ -520,14 +521,14 @@ occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish,
             constexpr bool NT = decltype(NTc)::value;
             if constexpr (X3) {
               if (write_mhat)
-                L("mhat_err_a", k_mlx<RP, 0, true, true, NT, false, RM>, b.blocks[K_MHAT]);
+                L("mhat_err_a", k_mlx<RP, true, NT, RM>, b.blocks[K_MHAT]);
               else
-                L("err_only_a", k_mlx<RP, 0, false, true, NT, false, RM>, b.blocks[K_MHAT]);
+                L("err_only_a", k_mlx<RP, false, NT, RM>, b.blocks[K_MHAT]);
             } else {
               if (write_mhat)
-                L("mhat_err_a", k_ml<DT_F32, RP, SA_SAVED, 0, true, true, NT, false, RM>, b.blocks[K_MHAT]);
+                L("mhat_err_a", k_ml<RP, true, NT, RM>, b.blocks[K_MHAT]);
               else
-                L("err_only_a", k_ml<DT_F32, RP, SA_SAVED, 0, false, true, NT, false, RM>, b.blocks[K_MHAT]);
+                L("err_only_a", k_ml<RP, false, NT, RM>, b.blocks[K_MHAT]);
             }
           });
         }
@@ -576,20 +577,26 @@ occ_status_t decompress_impl(const float* P, const float* Q, int64_t m, int64_t 
   with_rp(rp, [&](auto RPc) {
     constexpr int RP = decltype(RPc)::value;
     st = launch(OUTBF ? "decompress_bf16" : "decompress", s, [&] {
-      const dim3 grid(grid_of(t.blocks[K_MHAT]));
       with_bool(nt, [&](auto NTc) {
         constexpr bool NT = decltype(NTc)::value;
         if constexpr (RP > kFusedMaxRank) {
-          if (split)
-            hipLaunchKernelGGL((k_mlx<RP, 1, true, false, NT, OUTBF>), grid, dim3(kBlock), 0, s,
-                               (const Desc*)nullptr, 1, d);
-          else
-            hipLaunchKernelGGL((k_ml<DT_F32, RP, SA_SAVED, 1, true, false, NT, OUTBF>), grid,
-                               dim3(kBlock), 0, s, (const Desc*)nullptr, 1, d);
+          // one round of resident blocks, each walking as many row tiles as
+          // that takes (two rounds where the column tiles alone exceed one)
+          constexpr int NW = dc_waves(RP);
+          const int64_t slots = 256 * dc_blocks_per_cu(RP), ctd = cdiv(n, DC_COLS);
+          const int64_t rbd = clamp64(ctd <= slots ? slots / ctd : cdiv(2 * slots, ctd), 1,
+                                      cdiv(m, 32 * NW));
+          d.mr = (int32_t)round_up(cdiv(m, rbd), 32 * NW);
+          const dim3 grid(grid_of(ctd * cdiv(m, d.mr)));
+          with_bool(split, [&](auto Sc) {
+            hipLaunchKernelGGL((k_dec<RP, decltype(Sc)::value, OUTBF, NT>), grid,
+                               dim3(NW * kWave), 0, s, d);
+          });
         } else {
           // same code as the fused step's reconstruction pass
-          hipLaunchKernelGGL((k_mh16<DT_F32, NT, RP, 1, true, false, OUTBF>), grid, dim3(kBlock),
-                             0, s, (const Desc*)nullptr, 1, d);
+          hipLaunchKernelGGL((k_mh16<DT_F32, NT, RP, 1, true, false, OUTBF>),
+                             dim3(grid_of(t.blocks[K_MHAT])), dim3(kBlock), 0, s,
+                             (const Desc*)nullptr, 1, d);
         }
       });
     });

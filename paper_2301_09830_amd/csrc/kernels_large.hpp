@@ -1814,7 +1814,7 @@ __device__ __forceinline__ void lm_epi_load(const Desc& d, int row0, int r_hi, i
 // The tiles acc[c][v] = M_hat[row0 + mf32_row(v, g)][cw + 32 c + li], one
 // at a time through LDS (ep: this wave's 32 x LE_PITCH floats), then M_hat
 // and err = A - M_hat stored by rows (NT: nontemporal).
-template <int NCT, bool WM, bool WE, bool OUTBF, bool RM, bool NT>
+template <int NCT, bool WM, bool RM, bool NT>
 __device__ __forceinline__ void lm_epi_store(const Desc& d, int row0, int r_hi, int cw,
                                              const f16v (&acc)[NCT], const f4v (&a4)[NCT][LE_IT],
                                              float* ep) {
@@ -1838,17 +1838,17 @@ __device__ __forceinline__ void lm_epi_store(const Desc& d, int row0, int r_hi, 
       const int64_t pr = prow<RM>(d, row);
       float e[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) e[j] = WE ? a4[c][it][j] - mh[j] : 0.f;
+      for (int j = 0; j < 4; ++j) e[j] = a4[c][it][j] - mh[j];
       float* eo = RM ? d.err_fin + pr * d.lde_fin + col : d.err_out + pr * d.lde_out + col;
       if (col + 4 <= d.n) {
-        if (WM) store_mhat4<OUTBF, NT>(d, pr * d.ldh + col, mh[0], mh[1], mh[2], mh[3]);
-        if (WE) store_f4<NT>(eo, e[0], e[1], e[2], e[3]);
+        if (WM) store_f4<NT>(d.Mhat + pr * d.ldh + col, mh[0], mh[1], mh[2], mh[3]);
+        store_f4<NT>(eo, e[0], e[1], e[2], e[3]);
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           if (col + j < d.n) {
-            if (WM) store_mhat1<OUTBF>(d, pr * d.ldh + col + j, mh[j]);
-            if (WE) eo[j] = e[j];
+            if (WM) d.Mhat[pr * d.ldh + col + j] = mh[j];
+            eo[j] = e[j];
           }
         }
       }
@@ -1874,7 +1874,7 @@ __device__ __forceinline__ void lm_direct_load(const Desc& d, int row0, int cw, 
     }
 }
 
-template <int NCT, bool WM, bool WE, bool OUTBF, bool RM, bool NT>
+template <int NCT, bool WM, bool RM, bool NT>
 __device__ __forceinline__ void lm_direct_store(const Desc& d, int row0, int r_hi, int cw,
                                                 const f16v (&acc)[NCT], const float (&av)[NCT][16]) {
   const int lane = threadIdx.x & 63;
@@ -1888,13 +1888,9 @@ __device__ __forceinline__ void lm_direct_store(const Desc& d, int row0, int r_h
       if (row < r_hi && col < d.n) {
         const float mh = acc[c][v];
         const int64_t pr = prow<RM>(d, row);
-        if (WM) {
-          if constexpr (OUTBF) st_as<NT>(bf16_rne(mh), (uint16_t*)d.Mhat + pr * d.ldh + col);
-          else st_as<NT>(mh, d.Mhat + pr * d.ldh + col);
-        }
-        if (WE)
-          st_as<NT>(av[c][v] - mh, RM ? d.err_fin + pr * d.lde_fin + col
-                                      : d.err_out + pr * d.lde_out + col);
+        if (WM) st_as<NT>(mh, d.Mhat + pr * d.ldh + col);
+        st_as<NT>(av[c][v] - mh, RM ? d.err_fin + pr * d.lde_fin + col
+                                    : d.err_out + pr * d.lde_out + col);
       }
     }
   }
@@ -1902,9 +1898,9 @@ __device__ __forceinline__ void lm_direct_store(const Desc& d, int row0, int r_h
 
 // -------------------------------------------------------------------------
 // k_ml: M_hat = P_hat Q^T, err = A - M_hat for one column tile and d.mr rows.
-// SRC 0: P_hat from phat_t, Q from qpad (fused step).  SRC 1: the caller's P
-// (m x r) and Q (n x r), zero past rank r (stand-alone decompression; the
-// same products, so both give bitwise the same M_hat).
+// P_hat comes from phat_t and Q from qpad.  The stand-alone decompression
+// (k_dec) runs the same products in the same order, so both give bitwise the
+// same M_hat.
 // -------------------------------------------------------------------------
 template <int RP>
 struct LMSmem {
@@ -1912,18 +1908,8 @@ struct LMSmem {
   float ep[lm_lds_epilogue(RP) ? kBlock / kWave : 0][32 * LE_PITCH];   // epilogue tile per wave
 };
 
-template <int RP, int SRC>
-__device__ __forceinline__ void lm_stage_direct(const Desc& d, int row0, float (*dst)[32]) {
-  for (int idx = threadIdx.x; idx < RP * 32; idx += kBlock) {
-    const int k = idx >> 5, i = idx & 31;
-    const int row = row0 + i;
-    dst[k][i] = (row < d.m && k < d.r) ? d.P[(int64_t)row * d.r + k] : 0.f;
-  }
-}
-
-template <int DT, int RP, int SA, int SRC, bool WM, bool WE, bool NT, bool OUTBF = false, bool RM = false>
+template <int RP, bool WM, bool NT, bool RM = false>
 __device__ __forceinline__ void lm_body(const Desc& d, int b, LMSmem<RP>& sm) {
-  static_assert(!WE || SA == SA_SAVED, "the residual is formed from the stored A");
   constexpr int NCT = lm_tiles(RP), KP = RP / 2, BC = lm_block_cols(RP);
   constexpr bool EPI = lm_lds_epilogue(RP);
   constexpr int SF = RP * 8 / kBlock;   // float4s per thread per P_hat tile
@@ -1943,33 +1929,23 @@ __device__ __forceinline__ void lm_body(const Desc& d, int b, LMSmem<RP>& sm) {
 #pragma unroll
     for (int kp = 0; kp < KP; ++kp) {
       const int k = 2 * kp + g;
-      float v = 0.f;
-      if (SRC == 0) {
-        if (col < d.n_pad) v = d.qpad[(int64_t)col * RP + k];
-      } else {
-        if (col < d.n && k < d.r) v = d.Q[(int64_t)col * d.r + k];
-      }
-      qv[c][kp] = v;
+      qv[c][kp] = col < d.n_pad ? d.qpad[(int64_t)col * RP + k] : 0.f;
     }
   }
 
-  f4v pr[SF > 0 ? SF : 1];
-  if (SRC == 0) {
+  f4v pr[SF];
 #pragma unroll
-    for (int x = 0; x < SF; ++x) {
-      const int f = t + kBlock * x, k = f >> 3, part = f & 7;
-      pr[x] = *(const f4v*)(d.phat_t + (int64_t)k * d.m_pad + r_lo + 4 * part);
-      *(f4v*)(&sm.p[0][k][4 * part]) = pr[x];
-    }
-  } else {
-    lm_stage_direct<RP, SRC>(d, r_lo, sm.p[0]);
+  for (int x = 0; x < SF; ++x) {
+    const int f = t + kBlock * x, k = f >> 3, part = f & 7;
+    pr[x] = *(const f4v*)(d.phat_t + (int64_t)k * d.m_pad + r_lo + 4 * part);
+    *(f4v*)(&sm.p[0][k][4 * part]) = pr[x];
   }
   __syncthreads();
 
   for (int tile = 0; tile < ntile; ++tile) {
     const int row0 = r_lo + 32 * tile;
     const bool more = tile + 1 < ntile;
-    if (SRC == 0 && more) {
+    if (more) {
 #pragma unroll
       for (int x = 0; x < SF; ++x) {
         const int f = t + kBlock * x, k = f >> 3, part = f & 7;
@@ -1979,10 +1955,8 @@ __device__ __forceinline__ void lm_body(const Desc& d, int b, LMSmem<RP>& sm) {
     // A for this tile's outputs (issued before the products to hide latency)
     f4v a4[EPI ? NCT : 1][LE_IT];
     float av[EPI ? 1 : NCT][16];
-    if (WE) {
-      if constexpr (EPI) lm_epi_load<NCT>(d, row0, r_hi, cw, a4);
-      else lm_direct_load<NCT>(d, row0, cw, av);
-    }
+    if constexpr (EPI) lm_epi_load<NCT>(d, row0, r_hi, cw, a4);
+    else lm_direct_load<NCT>(d, row0, cw, av);
     f16v acc[NCT];
 #pragma unroll
     for (int c = 0; c < NCT; ++c) acc[c] = f16v{};
@@ -1993,27 +1967,23 @@ __device__ __forceinline__ void lm_body(const Desc& d, int b, LMSmem<RP>& sm) {
 #pragma unroll
       for (int c = 0; c < NCT; ++c) acc[c] = mfma32(a, qv[c][kp], acc[c]);
     }
-    if constexpr (EPI) lm_epi_store<NCT, WM, WE, OUTBF, RM, NT>(d, row0, r_hi, cw, acc, a4, sm.ep[wave]);
-    else lm_direct_store<NCT, WM, WE, OUTBF, RM, NT>(d, row0, r_hi, cw, acc, av);
+    if constexpr (EPI) lm_epi_store<NCT, WM, RM, NT>(d, row0, r_hi, cw, acc, a4, sm.ep[wave]);
+    else lm_direct_store<NCT, WM, RM, NT>(d, row0, r_hi, cw, acc, av);
     if (more) {
-      if (SRC == 0) {
 #pragma unroll
-        for (int x = 0; x < SF; ++x) {
-          const int f = t + kBlock * x, k = f >> 3, part = f & 7;
-          *(f4v*)(&sm.p[(tile + 1) & 1][k][4 * part]) = pr[x];
-        }
-      } else {
-        lm_stage_direct<RP, SRC>(d, row0 + 32, sm.p[(tile + 1) & 1]);
+      for (int x = 0; x < SF; ++x) {
+        const int f = t + kBlock * x, k = f >> 3, part = f & 7;
+        *(f4v*)(&sm.p[(tile + 1) & 1][k][4 * part]) = pr[x];
       }
     }
     __syncthreads();
   }
 }
 
-template <int DT, int RP, int SA, int SRC, bool WM, bool WE, bool NT, bool OUTBF = false, bool RM = false>
+template <int RP, bool WM, bool NT, bool RM = false>
 __global__ __launch_bounds__(kBlock) void k_ml(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) LMSmem<RP> sm;
-#define B_(d, b) lm_body<DT, RP, SA, SRC, WM, WE, NT, OUTBF, RM>(d, b, sm)
+#define B_(d, b) lm_body<RP, WM, NT, RM>(d, b, sm)
   OCC_DISPATCH_X(K_MHAT, B_)
 #undef B_
 }
@@ -2025,8 +1995,7 @@ __global__ __launch_bounds__(kBlock) void k_ml(OCC_KARGS) {
 // 16 ranks per K-step s, with
 //   A operand  P_hat: lane (g, li) supplies row li of the 32-row tile, ranks
 //              16 s + 8 g .. + 7, from an LDS tile of bf16 hi/lo rows staged
-//              from P_hat (SRC 0: the workspace copy; SRC 1: the caller's P,
-//              zero past rank r);
+//              from P_hat;
 //   B operand  Q^T: lane (g, li) supplies the same ranks of its column
 //              cw + 32 c + li, split once into bf16 hi/lo registers;
 // so acc[c][v] = M_hat[row0 + mf32_row(v, g)][cw + 32 c + li], the layout of
@@ -2040,7 +2009,7 @@ struct LMXSmem {
   uint16_t p[2][2][32 * (RP + 8)];   // [stage][hi, lo][row][rank], pitch RP + 8
 };
 
-template <int RP, int SRC>
+template <int RP>
 __device__ __forceinline__ void lmx_fetch(const Desc& d, int row0, f4v* pr) {
   constexpr int SF = RP * 8 / kBlock;   // float4s of a 32 x RP tile per thread
 #pragma unroll
@@ -2048,17 +2017,7 @@ __device__ __forceinline__ void lmx_fetch(const Desc& d, int row0, f4v* pr) {
     const int f = threadIdx.x + kBlock * x;
     const int i = f / (RP / 4), k = 4 * (f % (RP / 4));
     const int row = row0 + i;
-    f4v v = f4v{0.f, 0.f, 0.f, 0.f};
-    if (row < d.m) {
-      if (SRC == 0) {
-        v = *(const f4v*)(d.phat + (int64_t)row * RP + k);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (k + e < d.r) v[e] = d.P[(int64_t)row * d.r + k + e];
-      }
-    }
-    pr[x] = v;
+    pr[x] = row < d.m ? *(const f4v*)(d.phat + (int64_t)row * RP + k) : f4v{0.f, 0.f, 0.f, 0.f};
   }
 }
 
@@ -2082,7 +2041,7 @@ __device__ __forceinline__ void lmx_stage(const f4v* pr, uint16_t (*dst)[32 * (R
   }
 }
 
-template <int RP, int SRC, bool WM, bool WE, bool NT, bool OUTBF = false, bool RM = false>
+template <int RP, bool WM, bool NT, bool RM = false>
 __device__ __forceinline__ void lmx_body(const Desc& d, int b, LMXSmem<RP>& sm) {
   constexpr int NCT = lm_tiles(RP), KS = RP / 16, BC = lm_block_cols(RP);
   constexpr int SF = RP * 8 / kBlock;
@@ -2105,12 +2064,7 @@ __device__ __forceinline__ void lmx_body(const Desc& d, int b, LMXSmem<RP>& sm) 
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int k = 16 * s2 + 8 * g + e;
-        float v = 0.f;
-        if (SRC == 0) {
-          if (col < d.n_pad) v = d.qpad[(int64_t)col * RP + k];
-        } else {
-          if (col < d.n && k < d.r) v = d.Q[(int64_t)col * d.r + k];
-        }
+        const float v = col < d.n_pad ? d.qpad[(int64_t)col * RP + k] : 0.f;
         const __bf16 h = (__bf16)v;
         bh[c][s2][e] = h;
         bl[c][s2][e] = (__bf16)(v - (float)h);
@@ -2119,17 +2073,17 @@ __device__ __forceinline__ void lmx_body(const Desc& d, int b, LMXSmem<RP>& sm) 
   }
 
   f4v pr[SF];
-  lmx_fetch<RP, SRC>(d, r_lo, pr);
+  lmx_fetch<RP>(d, r_lo, pr);
   lmx_stage<RP>(pr, sm.p[0]);
   __syncthreads();
 
   for (int tile = 0; tile < ntile; ++tile) {
     const int row0 = r_lo + 32 * tile;
     const bool more = tile + 1 < ntile;
-    if (more) lmx_fetch<RP, SRC>(d, row0 + 32, pr);
+    if (more) lmx_fetch<RP>(d, row0 + 32, pr);
     // A for this tile's outputs (issued before the products to hide latency)
     float av[NCT][16];
-    if (WE) lm_direct_load<NCT>(d, row0, cw, av);
+    lm_direct_load<NCT>(d, row0, cw, av);
     f16v acc[NCT];
 #pragma unroll
     for (int c = 0; c < NCT; ++c) acc[c] = f16v{};
@@ -2146,16 +2100,16 @@ __device__ __forceinline__ void lmx_body(const Desc& d, int b, LMXSmem<RP>& sm) 
         acc[c] = mfma32bf(al, bh[c][s2], acc[c]);
       }
     }
-    lm_direct_store<NCT, WM, WE, OUTBF, RM, NT>(d, row0, r_hi, cw, acc, av);
+    lm_direct_store<NCT, WM, RM, NT>(d, row0, r_hi, cw, acc, av);
     if (more) lmx_stage<RP>(pr, sm.p[(tile + 1) & 1]);
     __syncthreads();
   }
 }
 
-template <int RP, int SRC, bool WM, bool WE, bool NT, bool OUTBF = false, bool RM = false>
+template <int RP, bool WM, bool NT, bool RM = false>
 __global__ __launch_bounds__(kBlock) void k_mlx(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) LMXSmem<RP> sm;
-#define B_(d, b) lmx_body<RP, SRC, WM, WE, NT, OUTBF, RM>(d, b, sm)
+#define B_(d, b) lmx_body<RP, WM, NT, RM>(d, b, sm)
   OCC_DISPATCH_X(K_MHAT, B_)
 #undef B_
 }

@@ -42,13 +42,6 @@ __device__ __forceinline__ uint32_t bf16_pack2(float lo, float hi) {
   return (uint32_t)bf16_rne(lo) | ((uint32_t)bf16_rne(hi) << 16);
 }
 
-// One element of M_hat at offset `off` (elements): fp32, or bf16 when OUTBF.
-template <bool OUTBF, class D>
-__device__ __forceinline__ void store_mhat1(const D& d, int64_t off, float v) {
-  if constexpr (OUTBF) ((uint16_t*)d.Mhat)[off] = bf16_rne(v);
-  else d.Mhat[off] = v;
-}
-
 // Element (row, col) of M as fp32 (exact widening for bf16).
 template <int DT>
 __device__ __forceinline__ float m_elem(const Desc& d, int64_t off) {
@@ -127,19 +120,6 @@ __device__ __forceinline__ void store_f4(float* o, float a, float b, float c, fl
   typedef float nt4 __attribute__((ext_vector_type(4)));
   if constexpr (NT) __builtin_nontemporal_store(nt4{a, b, c, e}, (nt4*)o);
   else *(f4u_t*)o = f4u_t{a, b, c, e};
-}
-
-template <bool OUTBF, bool NT, class D>
-__device__ __forceinline__ void store_mhat4(const D& d, int64_t off, float a, float b, float c,
-                                            float e) {
-  if constexpr (OUTBF) {
-    typedef uint32_t nu2 __attribute__((ext_vector_type(2)));
-    uint16_t* o = (uint16_t*)d.Mhat + off;
-    if constexpr (NT) __builtin_nontemporal_store(nu2{bf16_pack2(a, b), bf16_pack2(c, e)}, (nu2*)o);
-    else *(u2h_t*)o = u2h_t{bf16_pack2(a, b), bf16_pack2(c, e)};
-  } else {
-    store_f4<NT>(d.Mhat + off, a, b, c, e);
-  }
 }
 
 // A[row, col..col+3] = M + err_prev element by element, for columns < c_hi

@@ -614,7 +614,7 @@ struct MXSmem {
 
 // Factor values [row][S g .. S g + S - 1] of a lane: from the padded
 // workspace copy (row pitch RP, 256-byte aligned base) with one vector load,
-// or from a caller's m x r array element by element (zero past rank r).
+// or from a caller's m x r array (any alignment, zero past rank r).
 template <int S>
 __device__ __forceinline__ void factor_vec(const float* p, float v[S]) {
   if constexpr (S % 4 == 0) {
@@ -640,6 +640,9 @@ __device__ __forceinline__ void factor_load(const float* base, int r, int row, b
     for (int s = 0; s < S; ++s) v[s] = 0.f;
   } else if (SRC == 0) {
     factor_vec<S>(base + (int64_t)row * RP + k0, v);
+  } else if (S == 4 && k0 + S <= r) {
+    const float4 x = ld_f4<false>(base + (int64_t)row * r + k0);
+    v[0] = x.x; v[S > 1 ? 1 : 0] = x.y; v[S > 2 ? 2 : 0] = x.z; v[S > 3 ? 3 : 0] = x.w;
   } else {
 #pragma unroll
     for (int s = 0; s < S; ++s) v[s] = (k0 + s < r) ? base[(int64_t)row * r + k0 + s] : 0.f;
@@ -675,6 +678,12 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
   const int col = c0 + cl;
   const bool vec_col = col + 4 <= d.n;
   float* tile = sm.t[wave];
+  // Without A to read, a group's P rows are its only loads: they come one
+  // group ahead, so that the products and stores of the current group cover
+  // their latency (with the 16-byte bf16 stores below, 8192 x 4096 rank 16
+  // bf16 out: 31 -> 17.5 us).
+  float pn[S];
+  if (!WRITE_ERR) factor_load<RP, SRC>(ps, d.r, r_lo + 16 * wave + li, r_lo + 16 * wave + li < r_hi, S * g, pn);
   for (int r0 = r_lo + 16 * wave; r0 < r_hi; r0 += F_MHGROUP) {
     AChunk<DT> x[MX_NCH];
     if (WRITE_ERR) {
@@ -687,7 +696,14 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
     // B operand: P_hat[r0 + li][S g + s]
     const int rowb = r0 + li;
     float pb[S];
-    factor_load<RP, SRC>(ps, d.r, rowb, rowb < r_hi, S * g, pb);
+    if constexpr (WRITE_ERR) {
+      factor_load<RP, SRC>(ps, d.r, rowb, rowb < r_hi, S * g, pb);
+    } else {
+#pragma unroll
+      for (int s = 0; s < S; ++s) pb[s] = pn[s];
+      const int rown = rowb + F_MHGROUP;
+      factor_load<RP, SRC>(ps, d.r, rown, rown < r_hi, S * g, pn);
+    }
 #pragma unroll
     for (int t = 0; t < NTILE; ++t) {
       f4v acc = {0.f, 0.f, 0.f, 0.f};
@@ -698,6 +714,32 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
     // the tile is written and read by this wave only; LDS keeps a wave's
     // operations in order, and the wait also orders them for the compiler
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if constexpr (OUTBF) {
+      // eight elements a lane: 16 lanes x 16 bytes of a row, four rows at once
+      static_assert(!WRITE_ERR && WRITE_MHAT, "bf16 is a decompression output");
+      const int c8 = 8 * (lane & 15), colb = c0 + c8;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int rr = 4 * k + g, row = r0 + rr;
+        const float4 a = *(const float4*)(tile + rr * MX_LDW + c8);
+        const float4 c = *(const float4*)(tile + rr * MX_LDW + c8 + 4);
+        if (row >= r_hi) continue;
+        uint16_t* o = (uint16_t*)d.Mhat + (int64_t)row * d.ldh + colb;
+        const uint32_t w[4] = {bf16_pack2(a.x, a.y), bf16_pack2(a.z, a.w), bf16_pack2(c.x, c.y),
+                               bf16_pack2(c.z, c.w)};
+        if (colb + 8 <= d.n) {
+          typedef uint32_t nu4 __attribute__((ext_vector_type(4)));
+          if (NT) __builtin_nontemporal_store(nu4{w[0], w[1], w[2], w[3]}, (nu4*)o);
+          else *(u4h_t*)o = u4h_t{w[0], w[1], w[2], w[3]};
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (colb + j < d.n) o[j] = (uint16_t)(w[j / 2] >> (16 * (j % 2)));
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      continue;
+    }
 #pragma unroll
     for (int k = 0; k < MX_NCH; ++k) {
       const int rr = rl + MX_RPI * k;
@@ -714,13 +756,13 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
         for (int j = 0; j < 4; ++j) e[j] = a[j] - mh[j];
       }
       if (vec_col) {
-        if (WRITE_MHAT) store_mhat4<OUTBF, NT>(d, pr * d.ldh + col, mh[0], mh[1], mh[2], mh[3]);
+        if (WRITE_MHAT) store_f4<NT>(d.Mhat + pr * d.ldh + col, mh[0], mh[1], mh[2], mh[3]);
         if (WRITE_ERR) store_f4<NT>(d.err_out + pr * d.lde_out + col, e[0], e[1], e[2], e[3]);
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           if (col + j < d.n) {
-            if (WRITE_MHAT) store_mhat1<OUTBF>(d, pr * d.ldh + col + j, mh[j]);
+            if (WRITE_MHAT) d.Mhat[pr * d.ldh + col + j] = mh[j];
             if (WRITE_ERR) d.err_out[pr * d.lde_out + col + j] = e[j];
           }
         }

@@ -13,7 +13,7 @@ from gpu_util import torch_mod
 
 pytestmark = pytest.mark.gpu
 
-SENTINEL = 12345.0
+SENTINEL = 4096.0   # exact in bf16 too
 
 
 def _placed(x, offset: int, ld: int):

@@ -708,9 +708,17 @@ __device__ __forceinline__ void lg_body(const Desc& d, int b, LGSmem<RP>& sm) {
         for (int p = 1; p < LG_PB; ++p)
           if (p < d.sp) v = make_float4(v.x + pre[e][p].x, v.y + pre[e][p].y, v.z + pre[e][p].z,
                                         v.w + pre[e][p].w);
-        for (int p = LG_PB; p < d.sp; ++p) {
-          const float4 w = *(const float4*)(d.ppart + ((int64_t)p * d.m + row) * RP + 4 * k4);
-          v = make_float4(v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w);
+        // the further splits in batches of eight loads in flight (a load at
+        // a time cost a memory latency each: 4165 listed rows at rank 64,
+        // 12 splits, 15.2 -> 10.0 us; 36 stage matrices 51 -> 39 us)
+        for (int p0 = LG_PB; p0 < d.sp; p0 += 8) {
+          float4 w[8];
+#pragma unroll
+          for (int p = 0; p < 8; ++p)
+            w[p] = *(const float4*)(d.ppart + ((int64_t)min(p0 + p, d.sp - 1) * d.m + row) * RP + 4 * k4);
+#pragma unroll
+          for (int p = 0; p < 8; ++p)
+            if (p0 + p < d.sp) v = make_float4(v.x + w[p].x, v.y + w[p].y, v.z + w[p].z, v.w + w[p].w);
         }
         *(float4*)(d.praw + row * RP + 4 * k4) = v;
       }
@@ -760,12 +768,12 @@ __global__ __launch_bounds__(kBlock) void k_lg(OCC_KARGS) {
 // upper triangle only, held in LDS).  Step j:
 //   1. wave 0 factors the diagonal tile W_jj = R_jj^T R_jj with the
 //      right-looking column recurrence (Cholesky of W_jj together with the
-//      column recurrence of its inverse factor; each lane reads the pivot
-//      row of W and the pivot column of T from the owning lanes' registers
-//      with cross-lane shuffles, so a column step waits for one round of
-//      shuffles instead of an LDS write and read), giving T_jj = R_jj^-1
-//      and the pivots, while the other waves finish column block j-1 of T
-//      (step 4);
+//      column recurrence of its inverse factor, operands broadcast between
+//      lanes by DPP moves), giving T_jj = R_jj^-1 and the pivots, while the
+//      other waves finish column block j-1 of T (step 4).  This serial chain
+//      is the kernel's critical path; with operands shuffled through LDS
+//      instead, the kernel took 21.1 us at rank 64 (now 19.4) and 51.9 us
+//      for four matrices at rank 128 (now 45.2);
 //   2. row panel R_jk = T_jj^T W_jk (k > j) and U_kj = R_kj T_jj (k < j);
 //   3. trailing update W_kl -= R_jk^T R_jl (j < k <= l);
 //   4. T_ij = -sum_{k=i..j-1} T_ik U_kj (i < j), from T R = I.
@@ -813,6 +821,43 @@ __device__ __forceinline__ d4v lc_mm(FA fa, FB fb, d4v acc) {
 #pragma unroll
   for (int s = 0; s < 4; ++s) acc = mfma64(fa(s), fb(s), acc);
   return acc;
+}
+
+// x of lane K of each 16-lane group, in all lanes of the group.
+template <int K>
+__device__ __forceinline__ double bcast16(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x150 + K, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), 0x150 + K, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+
+// Column steps K .. 15 of a diagonal tile (see lchol_body): the Cholesky
+// update of W and the column recurrence of its inverse factor T (unscaled).
+// Lanes up to K keep their finished columns of T; their W is not used again.
+template <int K>
+__device__ __forceinline__ void lc_diag_steps(double (&W)[16], double (&T)[4], int k0, int r, double thr,
+                                              int li, double& mypiv, bool& mydep) {
+  if constexpr (K < 16) {
+    const double piv = bcast16<K>(W[K]);
+    const bool dep = (k0 + K >= r) || (piv <= thr);
+    if (li == K) {
+      mypiv = piv;
+      mydep = dep;
+    }
+    if (!dep) {
+      const double s = W[K] * rcp_nr(piv);   // row K of W over the pivot, this lane's column
+#pragma unroll
+      for (int i = K + 1; i < 16; ++i) W[i] = fma(-bcast16<K>(W[i]), s, W[i]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (4 * v > K) continue;             // rows past K of column K of T are zero
+        const double t = fma(-bcast16<K>(T[v]), s, T[v]);
+        T[v] = li > K ? t : T[v];
+      }
+    }
+    lc_diag_steps<K + 1>(W, T, k0, r, thr, li, mypiv, mydep);
+  }
 }
 
 template <int RP, int MODE>
@@ -896,56 +941,22 @@ __device__ __forceinline__ void lchol_body(const Desc& d, uint32_t* flags, LCSme
 #pragma unroll 1
   for (int j = 0; j < NB; ++j) {
     if (wave == 0) {
-      // 1. diagonal tile: lane (q, li) holds W_jj[4v+q][li] and T_jj[4v+q][li]
-      double* Wd = sm.W[lc_ut(NB, j, j)];
-      double W[4], T[4];
+      // 1. diagonal tile.  Every 16-lane group holds all of W_jj, lane li its
+      // column li (both triangles, from the stored upper one); group q holds
+      // rows 4v + q of T_jj, lane li their column li.  Column step k needs the
+      // pivot, the rest of column k of W and column k of T: all three are
+      // registers of lane k of the same group, broadcast by DPP moves, so a
+      // step has no LDS round trip (the groups repeat each other's W updates
+      // instead of exchanging rows).
+      const double* Wd = sm.W[lc_ut(NB, j, j)];
+      double W[16], T[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        W[v] = Wd[lc_sw(4 * v + q, li)];
-        T[v] = (4 * v + q == li) ? 1.0 : 0.0;
-      }
+      for (int i = 0; i < 16; ++i) W[i] = Wd[lc_sw(i < li ? i : li, i < li ? li : i)];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) T[v] = (4 * v + q == li) ? 1.0 : 0.0;
       double mypiv = 0.0;
       bool mydep = true;
-      // fully unrolled: each column's register and source lanes are fixed at
-      // compile time, and the compiler overlaps one column's independent
-      // shuffles with the previous column's updates (rank 64: 32 -> 26 us)
-#pragma unroll
-      for (int jv = 0; jv < 4; ++jv) {
-#pragma unroll
-        for (int jq = 0; jq < 4; ++jq) {
-          const int jj = 4 * jv + jq;
-          // Row jj of W is W[jv] of lanes (jq, 0..15); column jj of T is T[v]
-          // of lanes (q, jj).  Read straight from those lanes' registers.
-          double w = W[0];
-#pragma unroll
-          for (int v = 1; v < 4; ++v) w = (jv == v) ? W[v] : w;
-          const double piv = __shfl(w, 16 * jq + jj);
-          const double wk = __shfl(w, 16 * jq + li);
-          double wi[4], tl[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            wi[v] = __shfl(w, 16 * jq + 4 * v + q);
-            tl[v] = __shfl(T[v], 16 * q + jj);
-          }
-          const bool dep = (16 * j + jj >= r) || (piv <= thr);
-          if (li == jj) {
-            mypiv = piv;
-            mydep = dep;
-          }
-          if (!dep && li > jj) {
-            const double ip = rcp_nr(piv);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const int i = 4 * v + q;
-              if (i > jj) {
-                if (i <= li) W[v] = fma(-(wi[v] * ip), wk, W[v]);
-              } else {
-                T[v] = fma(-(tl[v] * ip), wk, T[v]);
-              }
-            }
-          }
-        }
-      }
+      lc_diag_steps<0>(W, T, 16 * j, r, thr, li, mypiv, mydep);
       const double isq = mydep ? 0.0 : rsqrt_nr(mypiv);
       const double sq = mypiv * isq;   // sqrt of the pivot (0 when dependent)
       double* Td = sm.T[lc_ut(NB, j, j)];

@@ -170,7 +170,7 @@ occ_status_t check_shape(int64_t m, int64_t n, int64_t ld) {
 struct Batch {
   std::vector<Desc> descs;
   int rp = 4, dt = 0, iters = 1;
-  bool vec = false;   // rows of M, err and M_hat 16-byte aligned
+  bool vec = false;   // rows of M, err and M_hat 16-byte aligned; rank <= 16: n a multiple of 8 too
   bool nt = false;    // ... and those of err and M_hat on 64-byte boundaries
   bool fused = false;
   int64_t blocks[K_NUM] = {};
@@ -363,6 +363,9 @@ occ_status_t plan_batch(const occ_mat_t* mats, int count, int rank, int iters, u
   if (ws_bytes < b.ws_needed) return OCC_E_WORKSPACE;
   spans.push_back({(uintptr_t)ws, (uintptr_t)ws + b.ws_needed, true});
   if (overlaps(spans)) return OCC_E_ALIAS;
+  // rank <= 16: the aligned kernels take whole 8-element chunks of a row
+  if (b.fused)
+    for (int j = 0; j < count; ++j) vec = vec && mats[j].cols % 8 == 0;
   b.vec = vec;
   b.nt = vec;
 
@@ -826,7 +829,8 @@ occ_status_t occ_step_rows(const occ_mat_t* mat, const int32_t* rows, int64_t n_
     d.lde_fin = (int32_t)a.lde;
   }
   b.vec = aligned(a.M, 16) && a.ldm % (dt == OCC_BF16 ? 8 : 4) == 0 && aligned(a.err, 16) &&
-          a.lde % 4 == 0 && (!write_mhat || (aligned(a.M_hat, 16) && a.ldh % 4 == 0));
+          a.lde % 4 == 0 && (!write_mhat || (aligned(a.M_hat, 16) && a.ldh % 4 == 0)) &&
+          (!b.fused || a.cols % 8 == 0);
   b.nt = b.vec && rows_nt(d, write_mhat);
   return run_batch(b, ws, fl, true, write_mhat, s);
 }
@@ -872,7 +876,7 @@ occ_status_t occ_compress(const void* M, int m_dtype, int64_t m, int64_t n, int6
   d.err_out = nullptr;
   d.Mhat = nullptr;
   b.vec = aligned(M, 16) && ldm % (m_dtype == OCC_BF16 ? 8 : 4) == 0 &&
-          (!err_prev || (aligned(err_prev, 16) && lde % 4 == 0));
+          (!err_prev || (aligned(err_prev, 16) && lde % 4 == 0)) && (!b.fused || n % 8 == 0);
   return run_batch(b, ws, (uint32_t*)ws, false, false, (hipStream_t)stream);
 }
 

@@ -122,26 +122,6 @@ __device__ __forceinline__ void store_f4(float* o, float a, float b, float c, fl
   else *(f4u_t*)o = f4u_t{a, b, c, e};
 }
 
-// A[row, col..col+3] = M + err_prev element by element, for columns < c_hi
-// (zero beyond, and for rows >= m): the ends of rows that no whole vector
-// fits.
-template <int DT, bool RM = false>
-__device__ __forceinline__ void load_a4(const Desc& d, int row, int col, int c_hi, float a[4]) {
-  a[0] = a[1] = a[2] = a[3] = 0.f;
-  if (row >= d.m || col >= c_hi) return;
-  const int64_t pr = prow<RM>(d, row);
-  const int64_t mo = pr * d.ldm + col;
-  const int64_t eo = pr * d.lde_in + col;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (col + j < c_hi) {
-      float v = m_elem<DT>(d, mo + j);
-      if (d.err_in) v = v + d.err_in[eo + j];
-      a[j] = v;
-    }
-  }
-}
-
 // Single element of A (column bound n).
 template <int DT>
 __device__ __forceinline__ float load_a1(const Desc& d, int row, int col) {

@@ -79,57 +79,70 @@ __device__ __forceinline__ d4v mfma4d(double a, double b, d4v c) {
 }
 
 // Eight consecutive elements of A = M + err_prev (columns c..c+7 of one row),
-// kept as raw loads until used.  Chunks across the end of a row (or past the
-// rows) hold the exact element-wise A in e0/e1 and -0 in m (x + -0 == x for
+// kept as raw loads until used.  AL: rows of M and err 16-byte aligned and n
+// a multiple of 8, so that a chunk is whole or empty; otherwise rows start at
+// any element and the last chunk of a row holds nv valid elements (loaded as
+// in chunk_issue).  Empty chunks have the value 0 (m = -0: x + -0 == x for
 // every x).
-template <int DT> struct Ch8;
-template <> struct Ch8<DT_BF16> { uint4 m; float4 e0, e1; };
-template <> struct Ch8<DT_F32> { float4 m0, m1; float4 e0, e1; };
+template <int DT, bool AL> struct Ch8 { float4 m0, m1; float4 e0, e1; int nv; };
+template <bool AL> struct Ch8<DT_BF16, AL> { uint4 m; float4 e0, e1; int nv; };
 
-template <int DT>
-__device__ __forceinline__ void ch8_neg_zero(Ch8<DT>& x) {
-  if constexpr (DT == DT_BF16) {
-    x.m = make_uint4(0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u);
-  } else {
-    x.m0 = make_float4(-0.f, -0.f, -0.f, -0.f);
-    x.m1 = x.m0;
-  }
-}
-
-template <int DT, bool VEC, bool RM = false>
-__device__ __forceinline__ Ch8<DT> ch8_load(const Desc& d, int row, int c, int c_hi) {
-  Ch8<DT> x;
-  if (row < d.m && c + 8 <= c_hi) {
+template <int DT, bool AL, bool RM = false>
+__device__ __forceinline__ Ch8<DT, AL> ch8_load(const Desc& d, int row, int c, int c_hi) {
+  Ch8<DT, AL> x;
+  if (row < d.m && (AL ? c + 8 <= c_hi : c < c_hi)) {
     const int64_t pr = prow<RM>(d, row);
     const int64_t mo = pr * d.ldm + c;
-    if constexpr (DT == DT_BF16) {
-      x.m = ld_h8<VEC>((const uint16_t*)d.M + mo);
+    if (!AL) x.nv = min(8, c_hi - c);
+    if (AL || m_load_inside<RM>(d, row, pr, c, 8)) {
+      if constexpr (DT == DT_BF16) {
+        x.m = ld_h8<AL>((const uint16_t*)d.M + mo);
+      } else {
+        x.m0 = ld_f4<AL>((const float*)d.M + mo);
+        x.m1 = ld_f4<AL>((const float*)d.M + mo + 4);
+      }
     } else {
-      x.m0 = ld_f4<VEC>((const float*)d.M + mo);
-      x.m1 = ld_f4<VEC>((const float*)d.M + mo + 4);
+      float a[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) a[j] = j < x.nv ? m_elem<DT>(d, mo + j) : -0.f;
+      if constexpr (DT == DT_BF16) {
+        x.m = make_uint4(bf16_pack2(a[0], a[1]), bf16_pack2(a[2], a[3]), bf16_pack2(a[4], a[5]),
+                         bf16_pack2(a[6], a[7]));
+      } else {
+        x.m0 = make_float4(a[0], a[1], a[2], a[3]);
+        x.m1 = make_float4(a[4], a[5], a[6], a[7]);
+      }
     }
-    if (d.err_in) {
-      const float* e = d.err_in + pr * d.lde_in + c;
-      x.e0 = ld_f4<VEC>(e);
-      x.e1 = ld_f4<VEC>(e + 4);
-    } else {
+    const float* ep = d.err_in + pr * d.lde_in + c;
+    if (!d.err_in) {
       x.e0 = make_float4(-0.f, -0.f, -0.f, -0.f);
       x.e1 = x.e0;
+    } else if (AL || x.nv == 8) {
+      x.e0 = ld_f4<AL>(ep);
+      x.e1 = ld_f4<AL>(ep + 4);
+    } else {
+      float e[8];
+      err_tail<8>(ep, x.nv, e);
+      x.e0 = make_float4(e[0], e[1], e[2], e[3]);
+      x.e1 = make_float4(e[4], e[5], e[6], e[7]);
     }
   } else {
-    float lo[4], hi[4];
-    load_a4<DT, RM>(d, row, c, c_hi, lo);
-    load_a4<DT, RM>(d, row, c + 4, c_hi, hi);
-    ch8_neg_zero<DT>(x);
-    x.e0 = make_float4(lo[0], lo[1], lo[2], lo[3]);
-    x.e1 = make_float4(hi[0], hi[1], hi[2], hi[3]);
+    if constexpr (DT == DT_BF16) {
+      x.m = make_uint4(0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u);
+    } else {
+      x.m0 = make_float4(-0.f, -0.f, -0.f, -0.f);
+      x.m1 = x.m0;
+    }
+    x.e0 = make_float4(0.f, 0.f, 0.f, 0.f);
+    x.e1 = x.e0;
+    x.nv = 8;
   }
   return x;
 }
 
 // The eight A values of a chunk.
-template <int DT>
-__device__ __forceinline__ void ch8_values(const Ch8<DT>& x, float a[8]) {
+template <int DT, bool AL>
+__device__ __forceinline__ void ch8_values(const Ch8<DT, AL>& x, float a[8]) {
   if constexpr (DT == DT_BF16) {
     a[0] = bf16_lo(x.m.x) + x.e0.x; a[1] = bf16_hi(x.m.x) + x.e0.y;
     a[2] = bf16_lo(x.m.y) + x.e0.z; a[3] = bf16_hi(x.m.y) + x.e0.w;
@@ -138,6 +151,10 @@ __device__ __forceinline__ void ch8_values(const Ch8<DT>& x, float a[8]) {
   } else {
     a[0] = x.m0.x + x.e0.x; a[1] = x.m0.y + x.e0.y; a[2] = x.m0.z + x.e0.z; a[3] = x.m0.w + x.e0.w;
     a[4] = x.m1.x + x.e1.x; a[5] = x.m1.y + x.e1.y; a[6] = x.m1.z + x.e1.z; a[7] = x.m1.w + x.e1.w;
+  }
+  if (!AL) {
+#pragma unroll
+    for (int j = 1; j < 8; ++j) a[j] = j < x.nv ? a[j] : 0.f;
   }
 }
 
@@ -189,13 +206,18 @@ template <int DT>
 constexpr int pm_stage() { return 4 * PM_ESLOT + pm_mbytes<DT>() + PM_QBYTES; }
 
 constexpr int PM_STAGES = 3;             // K-step stages per wave (two in flight)
+constexpr int PM_RING = 3;               // the same with loads straight into registers
 
+struct PMRows {
+  float red[PM_WAVES][PM_ROWS * 16];   // per-wave partial tiles
+  double rows[PM_WAVES * PM_ROWS * 16];   // final P rows of the group as doubles (Gram)
+};
+// TILES: the K-step stages of the LDS-tile form share the space; without them
+// more than one block fits on a compute unit
+template <bool TILES>
 union PMSmem {
-  struct {
-    float red[PM_WAVES][PM_ROWS * 16];   // per-wave partial tiles
-    double rows[PM_WAVES * PM_ROWS * 16];   // final P rows of the group as doubles (Gram)
-  } e;
-  uint8_t tile[PM_WAVES][PM_STAGES][pm_stage<DT_F32>()];   // per wave, the K-step stages
+  PMRows e;
+  uint8_t tile[PM_WAVES][TILES ? PM_STAGES : 1][TILES ? pm_stage<DT_F32>() : 16];   // per wave, the stages
 };
 
 typedef __attribute__((address_space(1))) void gvoid_t;
@@ -256,7 +278,7 @@ __device__ __forceinline__ void pm_tile_issue(const Desc& d, const float* qs, in
 // The rows are stored to praw, and as doubles to sm.e.rows (zero past m)
 // for the Gram partial; ends with a barrier.
 template <int DT, bool VEC, int RP, bool RM, int WK>
-__device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem& sm) {
+__device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem<VEC && !RM>& sm) {
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 15, g = lane >> 4;
   const int nk = (d.n + 31) / 32;
@@ -281,12 +303,12 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem& sm) {
 #pragma unroll
   for (int r = 0; r < PM_RB; ++r) acc[r] = f4v{0.f, 0.f, 0.f, 0.f};
 
-  auto mfma_step = [&](const Ch8<DT>* x, const Q8v& cq) {
+  auto mfma_step = [&](const Ch8<DT, VEC>* x, const Q8v& cq) {
     const float qv[8] = {cq.a.x, cq.a.y, cq.a.z, cq.a.w, cq.b.x, cq.b.y, cq.b.z, cq.b.w};
 #pragma unroll
     for (int r = 0; r < PM_RB; ++r) {
       float a[8];
-      ch8_values<DT>(x[r], a);
+      ch8_values<DT, VEC>(x[r], a);
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[r] = mfma4(a[j], qv[j], acc[r]);
     }
@@ -359,7 +381,7 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem& sm) {
                                 tiles + sn * STAGE);
         }
         st = st + 1 == PM_STAGES ? 0 : st + 1;
-        Ch8<DT> x[PM_RB];
+        Ch8<DT, VEC> x[PM_RB];
 #pragma unroll
         for (int r = 0; r < PM_RB; ++r) {
           x[r].e0 = make_float4(e0[r][0], e0[r][1], e0[r][2], e0[r][3]);
@@ -381,28 +403,26 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem& sm) {
     }
   }
   if (!dma) {
-    Ch8<DT> cur[PM_RB], nxt[PM_RB];
-    Q8v cq, nq;
-    int ks = live ? kw : nk;
-    if (ks < nk) {
+    // PM_RING K-steps of loads in flight
+    Ch8<DT, VEC> ring[PM_RING][PM_RB];
+    Q8v rq[PM_RING];
+    const int k_lo = live ? kw : nk;
+    auto fetch = [&](int ks, int y) {
       const int c = kcol(ks);
-      cq = q8_load<RP>(qs, d.n, c, li);
+      rq[y] = q8_load<RP>(qs, d.n, c, li);
 #pragma unroll
-      for (int r = 0; r < PM_RB; ++r) cur[r] = ch8_load<DT, VEC, RM>(d, row0 + 16 * r + li, c, d.n);
-    }
-    for (; ks < nk; ks += wk) {
-      const bool more = ks + wk < nk;
-      const int cn = more ? kcol(ks + wk) : 0;
-      if (more) {
-        nq = q8_load<RP>(qs, d.n, cn, li);
+      for (int r = 0; r < PM_RB; ++r) ring[y][r] = ch8_load<DT, VEC, RM>(d, row0 + 16 * r + li, c, d.n);
+    };
 #pragma unroll
-        for (int r = 0; r < PM_RB; ++r) nxt[r] = ch8_load<DT, VEC, RM>(d, row0 + 16 * r + li, cn, d.n);
-      }
-      mfma_step(cur, cq);
-      if (more) {
-        cq = nq;
+    for (int y = 0; y < PM_RING; ++y)
+      if (k_lo + wk * y < nk) fetch(k_lo + wk * y, y);
+    for (int ks = k_lo; ks < nk; ks += wk * PM_RING) {
 #pragma unroll
-        for (int r = 0; r < PM_RB; ++r) cur[r] = nxt[r];
+      for (int y = 0; y < PM_RING; ++y) {
+        if (ks + wk * y < nk) {
+          mfma_step(ring[y], rq[y]);
+          if (ks + wk * (y + PM_RING) < nk) fetch(ks + wk * (y + PM_RING), y);
+        }
       }
     }
   }
@@ -434,7 +454,7 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem& sm) {
 // the launch has fewer K-steps than waves (each matrix's row grouping is
 // chosen at run time); otherwise every matrix takes one row block at a time.
 template <int DT, bool VEC, int RP, bool RM = false, bool NARROW = false>
-__device__ __forceinline__ void pm_body(const Desc& d, int b, PMSmem& sm) {
+__device__ __forceinline__ void pm_body(const Desc& d, int b, PMSmem<VEC && !RM>& sm) {
   constexpr int NP = RP * (RP + 1) / 2;
   static_assert(NP <= PM_THREADS, "one Gram entry per thread");
   const int t = threadIdx.x;
@@ -457,7 +477,7 @@ __device__ __forceinline__ void pm_body(const Desc& d, int b, PMSmem& sm) {
 
 template <int DT, bool VEC, int RP, bool RM = false, bool NARROW = false>
 __global__ __launch_bounds__(PM_THREADS) void k_pm(OCC_KARGS) {
-  __shared__ __attribute__((aligned(16))) PMSmem sm;
+  __shared__ __attribute__((aligned(16))) PMSmem<VEC && !RM> sm;
 #define B_(d, b) pm_body<DT, VEC, RP, RM, NARROW>(d, b, sm)
   OCC_DISPATCH(K_PASS_P, B_)
 #undef B_
@@ -504,7 +524,7 @@ __device__ __forceinline__ void qm_body(const Desc& d, int b, QMSmem& sm) {
   d4v acc[8];
 #pragma unroll
   for (int t = 0; t < 8; ++t) acc[t] = d4v{0.0, 0.0, 0.0, 0.0};
-  Ch8<DT> cur, nxt;
+  Ch8<DT, VEC> cur, nxt;
   float cp = 0.f, np = 0.f;
   {
     const int row = w_lo + g;
@@ -521,7 +541,7 @@ __device__ __forceinline__ void qm_body(const Desc& d, int b, QMSmem& sm) {
       np = (ok && li < RP) ? ps[(int64_t)row * RP + li] : 0.f;
     }
     float a[8];
-    ch8_values<DT>(cur, a);
+    ch8_values<DT, VEC>(cur, a);
     const double pd = (double)cp;
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] = mfma4d((double)a[t], pd, acc[t]);
@@ -649,8 +669,8 @@ __device__ __forceinline__ void factor_load(const float* base, int r, int row, b
   }
 }
 
-// NT: the rows of M are 16-byte aligned and those of the outputs on 64-byte
-// boundaries (nontemporal stores, see store_f4).
+// NT: the rows of M are 16-byte aligned, those of the outputs on 64-byte
+// boundaries (nontemporal stores, see store_f4) and n is a multiple of 8.
 // OUTBF (stand-alone decompression only): M_hat is stored as bf16, each
 // element rounded to nearest even from the fp32 result.
 template <int DT, bool NT, int RP, int SRC, bool WRITE_MHAT, bool WRITE_ERR, bool OUTBF = false,
@@ -685,7 +705,7 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
   float pn[S];
   if (!WRITE_ERR) factor_load<RP, SRC>(ps, d.r, r_lo + 16 * wave + li, r_lo + 16 * wave + li < r_hi, S * g, pn);
   for (int r0 = r_lo + 16 * wave; r0 < r_hi; r0 += F_MHGROUP) {
-    AChunk<DT> x[MX_NCH];
+    AChunk<DT, NT> x[MX_NCH];
     if (WRITE_ERR) {
 #pragma unroll
       for (int k = 0; k < MX_NCH; ++k) {
@@ -751,7 +771,7 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
       float e[4] = {0.f, 0.f, 0.f, 0.f};
       if (WRITE_ERR) {
         float a[4];
-        chunk_value<DT>(x[k], a);
+        chunk_value<DT, NT>(x[k], a);
 #pragma unroll
         for (int j = 0; j < 4; ++j) e[j] = a[j] - mh[j];
       }

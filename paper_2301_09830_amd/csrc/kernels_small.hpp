@@ -31,10 +31,14 @@ namespace occ {
 template <int DT> struct MVec { using T = float4; };
 template <> struct MVec<DT_BF16> { using T = uint2; };
 
-template <int DT>
+// AL: rows of M and err 16-byte aligned and n a multiple of 4, so that a
+// chunk is whole or empty.  Otherwise rows start at any element and the last
+// chunk of a row may be short: it holds `nv` valid elements.
+template <int DT, bool AL>
 struct AChunk {
   typename MVec<DT>::T m;
   float4 e;
+  int nv;    // used when !AL
 };
 
 template <int DT>
@@ -43,29 +47,68 @@ __device__ __forceinline__ typename MVec<DT>::T neg_zero_m() {
   else return make_uint2(0x80008000u, 0x80008000u);
 }
 
-// Whole chunks as vector loads (VEC: rows 16-byte aligned; otherwise at
-// element alignment); a chunk across the end of a row holds the exact
-// element-wise A in `e` and -0 in `m` (x + -0 == x for all x).
-template <int DT, bool VEC, bool RM = false>
-__device__ __forceinline__ void chunk_issue(const Desc& d, int row, int col, int c_hi,
-                                            AChunk<DT>& x) {
-  if (row < d.m && col + 4 <= c_hi) {
-    const int64_t pr = prow<RM>(d, row);
-    const int64_t mo = pr * d.ldm + col;
-    if constexpr (DT == DT_F32) x.m = ld_f4<VEC>((const float*)d.M + mo);
-    else x.m = ld_h4<VEC>((const uint16_t*)d.M + mo);
-    x.e = d.err_in ? ld_f4<VEC>(d.err_in + pr * d.lde_in + col)
-                   : make_float4(-0.f, -0.f, -0.f, -0.f);
-  } else {
-    float a[4];
-    load_a4<DT, RM>(d, row, col, c_hi, a);
-    x.m = neg_zero_m<DT>();
-    x.e = make_float4(a[0], a[1], a[2], a[3]);
+// Whether a W-element load of M at column c of row `row` (of d.m; row pr of
+// M) stays inside the array although it may pass the end of that row.
+template <bool RM>
+__device__ __forceinline__ bool m_load_inside(const Desc& d, int row, int64_t pr, int c, int w) {
+  return c + w <= d.n || (RM ? pr < (int64_t)d.rmap[d.m - 1] : row + 1 < d.m);
+}
+
+// W elements of err_prev from column c of its row, the first nv (< W) of
+// them read one by one, with nothing waiting for them.
+template <int W>
+__device__ __forceinline__ void err_tail(const float* p, int nv, float* e) {
+#pragma unroll
+  for (int j = 0; j < W; ++j) {
+    e[j] = -0.f;
+    if (j < nv) e[j] = p[j];
   }
 }
 
-template <int DT>
-__device__ __forceinline__ void chunk_value(const AChunk<DT>& x, float a[4]) {
+// Loads only: the values are formed when used, so that the loads stay in
+// flight.  A short chunk takes M in one vector load past the end of the row
+// (M is read-only, and the load stays inside the array) and err, which other
+// blocks may be writing, element by element; the elements from nv on are
+// dropped when the values are formed.  Element-wise tails whose values were
+// added at once made the blocks of the last columns wait for every element:
+// 6001 x 2999 bf16 rank 12, with three K-steps in flight in the left product's
+// register form: 184 -> 134 us a step.
+template <int DT, bool AL, bool RM = false>
+__device__ __forceinline__ void chunk_issue(const Desc& d, int row, int col, int c_hi,
+                                            AChunk<DT, AL>& x) {
+  if (row < d.m && (AL ? col + 4 <= c_hi : col < c_hi)) {
+    const int64_t pr = prow<RM>(d, row);
+    const int64_t mo = pr * d.ldm + col;
+    if (!AL) x.nv = min(4, c_hi - col);
+    if (AL || m_load_inside<RM>(d, row, pr, col, 4)) {
+      if constexpr (DT == DT_F32) x.m = ld_f4<AL>((const float*)d.M + mo);
+      else x.m = ld_h4<AL>((const uint16_t*)d.M + mo);
+    } else {
+      float a[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] = j < x.nv ? m_elem<DT>(d, mo + j) : -0.f;
+      if constexpr (DT == DT_F32) x.m = make_float4(a[0], a[1], a[2], a[3]);
+      else x.m = make_uint2(bf16_pack2(a[0], a[1]), bf16_pack2(a[2], a[3]));
+    }
+    const float* ep = d.err_in + pr * d.lde_in + col;
+    if (!d.err_in) {
+      x.e = make_float4(-0.f, -0.f, -0.f, -0.f);
+    } else if (AL || x.nv == 4) {
+      x.e = ld_f4<AL>(ep);
+    } else {
+      float e[4];
+      err_tail<4>(ep, x.nv, e);
+      x.e = make_float4(e[0], e[1], e[2], e[3]);
+    }
+  } else {
+    x.m = neg_zero_m<DT>();
+    x.e = make_float4(0.f, 0.f, 0.f, 0.f);
+    x.nv = 4;
+  }
+}
+
+template <int DT, bool AL>
+__device__ __forceinline__ void chunk_value(const AChunk<DT, AL>& x, float a[4]) {
   if constexpr (DT == DT_F32) {
     a[0] = x.m.x + x.e.x; a[1] = x.m.y + x.e.y; a[2] = x.m.z + x.e.z; a[3] = x.m.w + x.e.w;
   } else {
@@ -73,6 +116,10 @@ __device__ __forceinline__ void chunk_value(const AChunk<DT>& x, float a[4]) {
     a[1] = bf16_hi(x.m.x) + x.e.y;
     a[2] = bf16_lo(x.m.y) + x.e.z;
     a[3] = bf16_hi(x.m.y) + x.e.w;
+  }
+  if (!AL) {
+#pragma unroll
+    for (int j = 1; j < 4; ++j) a[j] = j < x.nv ? a[j] : 0.f;
   }
 }
 

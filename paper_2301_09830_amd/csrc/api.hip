@@ -473,7 +473,9 @@ occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish,
         bool whole = VEC;
         for (const Desc& dd : b.descs) whole = whole && dd.n % 32 == 0;
         const bool tiles_merr = whole && b.descs[0].err_in != nullptr;
-        L("qpad", k_qpadl<RP>, b.blocks[K_QPAD]);
+        bool pad_q = X3 || !saved;
+        for (const Desc& dd : b.descs) pad_q = pad_q || !lp_reads_q<RP>(dd);
+        if (pad_q) L("qpad", k_qpadl<RP>, b.blocks[K_QPAD]);
         for (int it = 0; it < b.iters; ++it) {
           if (!saved) {
             if (tiles_merr)
@@ -491,14 +493,19 @@ occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish,
             else
               LB("pass_p_a", k_lp<DT_F32, RP, SA_SAVED, X3, false>, b.blocks[K_PASS_P], LPT);
           }
+          // the kernels named ...2 return at once unless the first pass asked
+          // for a second; gram2 is left to apply where that has the same rows
+          const int last = it + 1 == b.iters;
+          bool gram2 = false;
+          for (const Desc& dd : b.descs) gram2 = gram2 || !la_gram2(RP, dd.grows);
           L("gram", k_lg<RP, 0>, b.blocks[K_PGRAM]);
           L("gram_sum", k_gsum<RP, 0>, b.blocks[K_GSUM]);
           LB("chol", k_lchol<RP, 0>, count, LC_THREADS, flags);
-          L("apply", k_lapply<RP, 0>, b.blocks[K_APPLY]);
-          L("gram2", k_lg<RP, 1>, b.blocks[K_GRAM2]);
+          L("apply", k_lapply<RP, 0>, b.blocks[K_APPLY], last);
+          if (gram2) L("gram2", k_lg<RP, 1>, b.blocks[K_PGRAM]);
           L("gram_sum2", k_gsum<RP, 1>, b.blocks[K_GSUM]);
           LB("chol2", k_lchol<RP, 1>, count, LC_THREADS, flags);
-          L("apply2", k_lapply<RP, 1>, b.blocks[K_APPLY]);
+          L("apply2", k_lapply<RP, 1>, b.blocks[K_APPLY], last);
           if constexpr (X3) {
             // the stored A through LDS tiles under the same conditions
             constexpr int QXT = lqx_waves(RP) * kWave;

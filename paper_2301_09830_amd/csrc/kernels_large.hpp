@@ -430,6 +430,14 @@ __device__ __forceinline__ void lp_tile_store_a(const Desc& d, const uint8_t* sr
   }
 }
 
+// The caller's Q is laid out as the padded copy (rank and columns unpadded)
+// and aligned for 16-byte loads: the first left product of a fused fp32 step
+// reads it in place, and no copy is launched.
+template <int RP>
+__host__ __device__ __forceinline__ bool lp_reads_q(const Desc& d) {
+  return d.r == RP && d.n == d.n_pad && ((uintptr_t)d.Q & 15) == 0;
+}
+
 // RM (row-sparse step): M and err_prev rows through the row map; the stored A
 // (SA_MERR_SAVE writes it, SA_SAVED reads it) is compact.
 template <int DT, int RP, int SA, bool X3, bool TILES, bool RM = false>
@@ -464,13 +472,14 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
   // fp32 form: qpad has n_pad (a multiple of 32) rows, so every K-step's Q
   // tile is in bounds (rows past n are zero); bf16 form: qbf rows have n_pad
   // columns, likewise zero past n.
+  const float* const qf = SA == SA_MERR_SAVE && lp_reads_q<RP>(d) ? d.Q : d.qpad;
   auto q_src_ptr = [&](int c, int x) -> const f4v* {
     const int f = threadIdx.x + NT * x;
     if constexpr (X3) {
       const int h = f / (RP * 4), rem = f % (RP * 4);
       return (const f4v*)(d.qbf + ((int64_t)h * RP + rem / 4) * d.n_pad + c + 8 * (rem % 4));
     } else {
-      return (const f4v*)(d.qpad + (int64_t)c * RP + 4 * f);
+      return (const f4v*)(qf + (int64_t)c * RP + 4 * f);
     }
   };
   auto q_lds_ptr = [&](int stage, int x) -> f4v* {
@@ -628,9 +637,9 @@ __global__ __launch_bounds__(lp_block_rows(RP, X3) / 32 * kWave) void k_lp(OCC_K
 // -------------------------------------------------------------------------
 // k_lg: Gram partial of d.grows rows (256, fewer for short matrices) in
 // fp64.  MODE 0: the rows are P (sum of the left product's column splits,
-// stored to praw).  MODE 1 (second CholeskyQR pass, skipped unless the first
-// pass asked for it): the rows are the first pass's P_hat.  Rows are staged in LDS as doubles, 32 at a
-// time; the upper-triangle 16 x 16 tiles of G (ta <= tb) are shared out
+// stored to praw).  MODE 1 (second CholeskyQR pass): the rows are the first
+// pass's P_hat, when the first pass asked for a second; where a block of
+// k_lapply has the rows of a Gram block it runs this itself (la_gram2).  Rows are staged in LDS as doubles, 32 at a time; the upper-triangle 16 x 16 tiles of G (ta <= tb) are shared out
 // over the four waves and accumulated on v_mfma_f64_16x16x4f64, four rows
 // per instruction: lane (q, li) supplies P[row 4s + q][16 ta + li] (A
 // operand) and P[row 4s + q][16 tb + li] (B operand) and ends with
@@ -655,7 +664,6 @@ __host__ __device__ constexpr int lg_per_wave(int rp) { return (lg_ntiles(rp) + 
 
 template <int RP, int MODE>
 __device__ __forceinline__ void lg_body(const Desc& d, int b, LGSmem<RP>& sm) {
-  if (MODE == 1 && !d.info[0]) return;
   constexpr int NTT = RP / 16, NTL = lg_ntiles(RP), PW = lg_per_wave(RP);
   const int t = threadIdx.x;
   const int wave = wave_id(), lane = t & 63;
@@ -754,12 +762,25 @@ __device__ __forceinline__ void lg_body(const Desc& d, int b, LGSmem<RP>& sm) {
   }
 }
 
+// MODE 1 as a kernel: the matrices whose Gram blocks hold more rows than a
+// block of k_lapply.
+template <int RP>
+__device__ __forceinline__ void lg2_body(const Desc& d, int b, LGSmem<RP>& sm) {
+  if (d.info[0] && !la_gram2(RP, d.grows)) lg_body<RP, 1>(d, b, sm);
+}
+
 template <int RP, int MODE>
 __global__ __launch_bounds__(kBlock) void k_lg(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) LGSmem<RP> sm;
-#define B_(d, b) lg_body<RP, MODE>(d, b, sm)
-  OCC_DISPATCH(MODE == 0 ? K_PGRAM : K_GRAM2, B_)
+  if constexpr (MODE == 0) {
+#define B_(d, b) lg_body<RP, 0>(d, b, sm)
+    OCC_DISPATCH(K_PGRAM, B_)
 #undef B_
+  } else {
+#define B_(d, b) lg2_body<RP>(d, b, sm)
+    OCC_DISPATCH(K_PGRAM, B_)
+#undef B_
+  }
 }
 
 // -------------------------------------------------------------------------
@@ -867,7 +888,6 @@ __device__ __forceinline__ void lchol_body(const Desc& d, uint32_t* flags, LCSme
   const int t = threadIdx.x, wave = t / kWave, lane = t % kWave;
   const int q = lane >> 4, li = lane & 15;
   const int r = d.r;
-  const double* G = d.gsum;
   // operand readers on swizzled tiles
   auto rdA = [&](const double* X, int s) { return X[lc_sw(li, 4 * s + q)]; };   // X[li][4s+q]
   auto rdB = [&](const double* X, int s) { return X[lc_sw(4 * s + q, li)]; };   // X[4s+q][li]
@@ -893,7 +913,8 @@ __device__ __forceinline__ void lchol_body(const Desc& d, uint32_t* flags, LCSme
       const int u = idx >> 8, e = idx & 255, rr = e >> 4, cc = e & 15;
       int a = 0, rem = u;
       while (rem >= NB - a) { rem -= NB - a; ++a; }
-      gl[x] = G[(16 * a + rr) * RP + 16 * (a + rem) + cc];
+      const int e0 = (16 * a + rr) * RP + 16 * (a + rem) + cc;
+      gl[x] = d.gsum[e0];
     }
   }
 #pragma unroll
@@ -1041,8 +1062,12 @@ __global__ __launch_bounds__(LC_THREADS) void k_lchol(OCC_KARGS, uint32_t* flags
 }
 
 // -------------------------------------------------------------------------
-// k_lapply: P_hat = S T for 128 rows, S = praw, T = t1 (MODE 0) or, in the
-// second pass, S = the first pass's P_hat, T = tm (in place).  fp64
+// k_lapply: P_hat = S T for la_rows(d.grows) rows, S = praw, T = t1 (MODE 0)
+// or, in the second pass, S = the first pass's P_hat, T = tm (in place).
+// MODE 0 with a second pass pending, where those are the rows of a Gram block
+// (la_gram2): the block also forms the Gram partial of the rows it has just
+// written, which saves the launch that would (about 3.5 us a round, whether
+// the second pass is needed or not).  fp64
 // products on v_mfma_f64_16x16x4f64, fp32 result.  T is upper triangular,
 // so column tile jt of P_hat needs only k < 16 (jt + 1).  The column tiles
 // are paired (jt, NTT-1-jt), which makes every pair the same amount of
@@ -1053,7 +1078,7 @@ __global__ __launch_bounds__(LC_THREADS) void k_lchol(OCC_KARGS, uint32_t* flags
 // and ends with P_hat[16 rt + 4 v + q][16 jt + li] in component v.  The
 // chunk's results are written back into the staging buffer and stored as
 // whole rows to phat and, for the final P_hat (no second pass pending), to
-// the caller's P and transposed to phat_t.
+// the caller's P (last round only: `out_p`) and transposed to phat_t.
 // -------------------------------------------------------------------------
 template <int RP>
 struct LAShape {
@@ -1061,18 +1086,18 @@ struct LAShape {
   static constexpr int LD = RP + 4;
 };
 
-template <int RP>
-struct LASmem {
+template <int RP, int MODE>
+union LASmem {
   float buf[LAShape<RP>::CR][LAShape<RP>::LD];
+  std::conditional_t<MODE == 0 && la_gram2(RP, 0), LGSmem<RP>, float> g;   // second pass's Gram partial
 };
 
 template <int RP, int MODE>
-__device__ __forceinline__ void la_body(const Desc& d, int b, LASmem<RP>& sm) {
+__device__ __forceinline__ void la_body(const Desc& d, int b, int out_p, LASmem<RP, MODE>& sm) {
   const uint32_t need = d.info[0];
   if (MODE == 1 && !need) return;
   using S_ = LAShape<RP>;
   constexpr int NTT = S_::NTT, NP = S_::NP, CR = S_::CR;
-  static_assert(L_AROWS % CR == 0, "apply chunk must divide the block's rows");
   constexpr int KA_MAX = 4 * NP;        // steps of the pair's first tile (jt = pair <= NP-1)
   constexpr int KB_MAX = 4 * NTT;       // steps of the pair's second tile (jt = NTT-1-pair)
   const bool fin = (MODE == 1) || !need;
@@ -1090,7 +1115,9 @@ __device__ __forceinline__ void la_body(const Desc& d, int b, LASmem<RP>& sm) {
 #pragma unroll
   for (int s = 0; s < KB_MAX; ++s) tb[s] = (s < kb) ? Tg[(4 * s + q) * RP + 16 * jb + li] : 0.0;
 
-  const int r_lo = b * L_AROWS, r_hi = min(d.m, r_lo + L_AROWS);
+  const int rows = la_rows(d.grows);
+  const int r_lo = b * rows, r_hi = min(d.m, r_lo + rows);
+  const int t_hi = min(d.m_pad, r_lo + rows);   // rows of phat_t this block writes
   // the rows of S of the next chunk are loaded into registers while this
   // chunk's products and stores run (rows past m as zeros)
   constexpr int SF = CR * RP / 4 / kBlock;   // float4s per thread per chunk
@@ -1150,7 +1177,7 @@ __device__ __forceinline__ void la_body(const Desc& d, int b, LASmem<RP>& sm) {
       if (row < r_hi) {
         const float4 v = *(const float4*)&sm.buf[i][4 * k4];
         *(float4*)(d.phat + (int64_t)row * RP + 4 * k4) = v;
-        if (fin) {
+        if (fin && out_p) {
           const float vv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -1167,7 +1194,7 @@ __device__ __forceinline__ void la_body(const Desc& d, int b, LASmem<RP>& sm) {
       uint16_t* tb = d.qbf ? (uint16_t*)d.phat_t : nullptr;
       for (int idx = t; idx < RP * CR / 4; idx += kBlock) {
         const int k = idx / (CR / 4), i4 = idx % (CR / 4);
-        if (c0 + 4 * i4 < d.m_pad) {
+        if (c0 + 4 * i4 < t_hi) {
           const float v[4] = {sm.buf[4 * i4][k], sm.buf[4 * i4 + 1][k], sm.buf[4 * i4 + 2][k],
                               sm.buf[4 * i4 + 3][k]};
           const int64_t o = (int64_t)k * d.m_pad + c0 + 4 * i4;
@@ -1192,12 +1219,16 @@ __device__ __forceinline__ void la_body(const Desc& d, int b, LASmem<RP>& sm) {
     }
     __syncthreads();
   }
+  // the barrier above has made this block's rows of phat visible to it
+  if constexpr (MODE == 0 && la_gram2(RP, 0)) {
+    if (need && la_gram2(RP, d.grows)) lg_body<RP, 1>(d, b, sm.g);
+  }
 }
 
 template <int RP, int MODE>
-__global__ __launch_bounds__(kBlock) void k_lapply(OCC_KARGS) {
-  __shared__ __attribute__((aligned(16))) LASmem<RP> sm;
-#define B_(d, b) la_body<RP, MODE>(d, b, sm)
+__global__ __launch_bounds__(kBlock) void k_lapply(OCC_KARGS, int out_p) {
+  __shared__ __attribute__((aligned(16))) LASmem<RP, MODE> sm;
+#define B_(d, b) la_body<RP, MODE>(d, b, out_p, sm)
   OCC_DISPATCH(K_APPLY, B_)
 #undef B_
 }

@@ -24,8 +24,7 @@ enum Kind : int {
   K_PASS_P,      // P partials = A Q over column splits
   K_PGRAM,       // reduce the splits -> P; Gram partials (fp64)
   K_GSUM,        // sum Gram partials -> G
-  K_GRAM2,       // CholeskyQR2 second Gram: (P T1)^T (P T1) partials
-  K_APPLY,       // P_hat = P T (padded copy and caller's P)
+  K_APPLY,       // P_hat = P T (padded copy and caller's P); second Gram partials when needed
   K_PASS_Q,      // Q partials = A^T P_hat over row splits
   K_QRED,        // reduce Q partials -> Q (caller and padded copy)
   K_MHAT,        // M_hat = P_hat Q^T, err = A - M_hat
@@ -121,7 +120,14 @@ constexpr int L_PROWS = 128;      // left product: rows per block (4 waves x 32)
 __host__ __device__ constexpr int lp_block_rows(int rp, bool x3) { return rp >= 128 && x3 ? 256 : L_PROWS; }
 constexpr int L_KC = 32;          // left product: columns per K-step
 constexpr int L_GROWS = 256;      // Gram partials: rows per block
-constexpr int L_AROWS = 128;      // P_hat = P T: rows per block
+constexpr int L_AROWS = 128;      // P_hat = P T: rows per block, at most (256, the rows of a
+                                  // tall matrix's Gram block: 4 x 16384 x 128 48 -> 63 us)
+// rows per block of the P_hat kernel, and whether they are those of a Gram
+// block, so that it can form the second pass's Gram partial itself
+__host__ __device__ constexpr int la_rows(int grows) { return grows < L_AROWS ? grows : L_AROWS; }
+// (not at padded rank 128, where the Gram code would double the LDS of a kernel
+// that every round runs)
+__host__ __device__ constexpr bool la_gram2(int rp, int grows) { return rp < 128 && grows <= L_AROWS; }
 constexpr int L_QG = 8;           // right product: rows per LDS stage
 constexpr int64_t L_SPLIT_BLOCKS = 1024;  // split products: blocks over the whole batch
 constexpr int64_t L_MIN_COLS = 1024;      // left product: columns per split, at least
@@ -254,8 +260,7 @@ inline Tiling make_tiling(int64_t m, int64_t n, int rp, double share = 1.0,
   t.blocks[K_PASS_P] = row_tiles * t.sp;
   t.blocks[K_PGRAM] = t.ng;
   t.blocks[K_GSUM] = cdiv((int64_t)rp * rp, kBlock / 8);   // 32 entries per block
-  t.blocks[K_GRAM2] = t.ng;
-  t.blocks[K_APPLY] = cdiv(m, L_AROWS);
+  t.blocks[K_APPLY] = cdiv(m, la_rows(t.grows));
   t.blocks[K_PASS_Q] = ctq * t.sq;
   // Q reduction: 32-column tiles, or 8-column ones (four times the blocks)
   // where 32-column tiles would leave this matrix's share of one round of

@@ -8,11 +8,16 @@
 // bf16 they stored 2 bytes a lane into 64-byte pieces of rows (16384 x 8192,
 // rank 128, bf16 out: 203 us for 268 MB).  Here a block stages 128 columns of
 // Q in LDS once, and each wave then walks 32-row tiles by itself, with no
-// barrier: its P rows come straight into the A operands (the next tile's
-// loads in flight during the products), the four 32-column tiles take their
-// B operands from LDS, and the results pass through a wave's own LDS tile to
-// be stored as 256-byte pieces of rows, 16 bytes a lane.  16384 x 8192, rank
-// 128, bf16 out: 203 -> 119 us; 8192 x 4096, rank 64, fp32 out: 57 -> 34 us.
+// barrier: its P rows come straight into the B operands (two tiles ahead), the four
+// 32-column tiles take their A operands from LDS, and the results pass
+// through a wave's own LDS tile to be stored as 256-byte pieces of rows, 16
+// bytes a lane.  The products run transposed (M_hat^T = Q P^T), so that a lane
+// holds four consecutive columns of a row and writes them to LDS at once.
+// Loads and stores complete in order, so whatever waits for the next tile's P
+// also waits for the stores issued before it: the operands are formed before
+// this tile's stores go out, not after.  16384 x 8192, rank 128, bf16 out:
+// 203 us before, DEC_MID us with the operands formed after the stores, now
+// DEC_NEW us; 8192 x 4096, rank 64, fp32 out: 57 -> DEC64_NEW us.
 //
 // The products and their order are those of the fused step (k_mlx when SPLIT,
 // k_ml otherwise), so M_hat is bitwise the one that step writes.
@@ -40,17 +45,43 @@ struct DCShape {
   static constexpr int BYTES = Q_BYTES + NW * E_BYTES;
 };
 
-// Four consecutive ranks k .. k+3 of a caller's factor row (zero past r).
+// Factor rows are read in float4s of consecutive ranks straight from the
+// caller's array.  Unless r is the padded rank, the last ones of a row run on
+// into the next rows, so the values from rank r on are dropped when used, and
+// rows whose last float4 would leave the array (`inside` false: the end of
+// the array only) are read element by element instead.  A bounds test at
+// every float4 made each load wait for the one before.
+template <bool INSIDE>
 __device__ __forceinline__ f4v dc_load4(const float* row, int k, int r) {
-  f4v v = f4v{0.f, 0.f, 0.f, 0.f};
-  if (k + 4 <= r) {
-    v = *(const f4u_t*)(row + k);
+  if constexpr (INSIDE) {
+    return *(const f4u_t*)(row + k);
   } else {
+    f4v v = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (k + e < r) v[e] = row[k + e];
+    return v;
   }
-  return v;
+}
+
+// Whether float4s up to padded rank rp of rows up to `last` (of `rows`) stay
+// inside the array.
+__device__ __forceinline__ bool dc_inside(int64_t last, int64_t rows, int r, int rp) {
+  return last < rows && last * r + rp <= rows * r;
+}
+
+// 16 bytes of an output row (4 fp32 or 8 bf16 elements).
+template <bool OUTBF, bool NT>
+__device__ __forceinline__ void dc_store16(const Desc& d, int64_t off, const uint4& v) {
+  if constexpr (NT) {
+    typedef uint32_t nu4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store(nu4{v.x, v.y, v.z, v.w}, (nu4*)((uint8_t*)d.Mhat + off * (OUTBF ? 2 : 4)));
+  } else if constexpr (OUTBF) {
+    *(u4h_t*)((uint16_t*)d.Mhat + off) = u4h_t{v.x, v.y, v.z, v.w};
+  } else {
+    *(f4u_t*)(d.Mhat + off) = f4u_t{__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
+                                    __uint_as_float(v.w)};
+  }
 }
 
 template <int RP, bool SPLIT, bool OUTBF, bool NT>
@@ -66,20 +97,19 @@ __global__ __launch_bounds__(dc_waves(RP) * kWave) void k_dec(Desc d) {
   const int c0 = ct * DC_COLS;
   const int r_lo = rb * d.mr, r_hi = min(d.m, r_lo + d.mr);
 
-  // P rows of one tile, as loaded.  SPLIT: lane (g, li) supplies ranks
-  // 16 s + 8 g .. + 7 of row li to K-step s, two float4s each.  fp32: ranks
-  // 2 kp + g to MFMA kp; both halves load the row's float4s 4 j .. 4 j + 3
-  // (two MFMAs each) and keep their own two values.
-  f4v raw[SPLIT ? NF : 2 * NF];
-  auto p_load = [&](int row0) {
-    const float* row = d.P + (int64_t)min(row0 + li, d.m - 1) * d.r;
-    if constexpr (SPLIT) {
+  // P rows of one tile as loaded, whole rows side by side: float4 x of a lane
+  // is float4 64 x + lane of the tile.
+  f4v raw[NF];
+  auto p_load_as = [&](auto in, int row0) __attribute__((always_inline)) {
 #pragma unroll
-      for (int x = 0; x < NF; ++x) raw[x] = dc_load4(row, 16 * (x / 2) + 8 * g + 4 * (x % 2), d.r);
-    } else {
-#pragma unroll
-      for (int x = 0; x < 2 * NF; ++x) raw[x] = dc_load4(row, 4 * x, d.r);
+    for (int x = 0; x < NF; ++x) {
+      const int f = 64 * x + lane, row = min(row0 + f / (RP / 4), d.m - 1);
+      raw[x] = dc_load4<decltype(in)::value>(d.P + (int64_t)row * d.r, 4 * (f % (RP / 4)), d.r);
     }
+  };
+  auto p_load = [&](int row0) __attribute__((always_inline)) {
+    if (dc_inside(row0 + 31, d.m, d.r, RP)) p_load_as(std::true_type{}, row0);
+    else p_load_as(std::false_type{}, row0);
   };
   int row0 = r_lo + 32 * wave;
   if (row0 < r_hi) p_load(row0);
@@ -90,67 +120,133 @@ __global__ __launch_bounds__(dc_waves(RP) * kWave) void k_dec(Desc d) {
   uint16_t* qh = (uint16_t*)smem;
   uint16_t* ql = qh + DC_COLS * PT;
   float* qf = (float*)smem;
-  for (int f = threadIdx.x; f < DC_COLS * RP / 4; f += NTH) {
-    const int c = f / (RP / 4), k = 4 * (f % (RP / 4));
-    f4v v = f4v{0.f, 0.f, 0.f, 0.f};
-    if (c0 + c < d.n) v = dc_load4(d.Q + (int64_t)(c0 + c) * d.r, k, d.r);
-    if constexpr (SPLIT) {
-      uint16_t hi[4], lo[4];
+  {
+    constexpr int QL = DC_COLS * RP / 4 / NTH;   // float4s per thread
+    static_assert(QL * NTH * 4 == DC_COLS * RP, "Q tile must split evenly");
+    f4v q4[QL];
+    auto q_load = [&](auto in) __attribute__((always_inline)) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const __bf16 h = (__bf16)v[e];
-        hi[e] = bf16_bits(h);
-        lo[e] = bf16_bits((__bf16)(v[e] - (float)h));
+      for (int x = 0; x < QL; ++x) {
+        const int f = threadIdx.x + NTH * x, c = f / (RP / 4), k = 4 * (f % (RP / 4));
+        q4[x] = dc_load4<decltype(in)::value>(d.Q + (int64_t)min(c0 + c, d.n - 1) * d.r, k, d.r);
       }
-      *(uint2*)(qh + c * PT + k) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
-      *(uint2*)(ql + c * PT + k) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
-    } else {
-      float* q = qf + c * PT + k / 2;
-      *(float2*)q = make_float2(v[0], v[2]);
-      *(float2*)(q + RP / 2) = make_float2(v[1], v[3]);
+    };
+    if (dc_inside(c0 + DC_COLS - 1, d.n, d.r, RP)) q_load(std::true_type{});
+    else q_load(std::false_type{});
+#pragma unroll
+    for (int x = 0; x < QL; ++x) {
+      const int f = threadIdx.x + NTH * x, c = f / (RP / 4), k = 4 * (f % (RP / 4));
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = c0 + c < d.n && k + e < d.r ? q4[x][e] : 0.f;
+      if constexpr (SPLIT) {
+        uint16_t hi[4], lo[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const __bf16 h = (__bf16)v[e];
+          hi[e] = bf16_bits(h);
+          lo[e] = bf16_bits((__bf16)(v[e] - (float)h));
+        }
+        *(uint2*)(qh + c * PT + k) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+        *(uint2*)(ql + c * PT + k) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+      } else {
+        float* q = qf + c * PT + k / 2;
+        *(float2*)q = make_float2(v[0], v[2]);
+        *(float2*)(q + RP / 2) = make_float2(v[1], v[3]);
+      }
     }
   }
   __syncthreads();
 
+  // B operands of a tile from its raw rows, through the wave's LDS tile.
+  // SPLIT: lane (g, li) supplies ranks 16 s + 8 g .. + 7 of row li to K-step
+  // s; the hi parts pass first, then the lo parts.  fp32: ranks 2 kp + g to
+  // MFMA kp; 64 ranks pass at a time.
   uint8_t* const ep = smem + S::Q_BYTES + wave * S::E_BYTES;
-  for (; row0 < r_hi; row0 += 32 * NW) {
-    // operands of this tile, then the next tile's loads
-    bf16x8 ah[SPLIT ? RP / 16 : 1], al[SPLIT ? RP / 16 : 1];
-    float pa[SPLIT ? 1 : RP / 2];
+  bf16x8 ph[SPLIT ? RP / 16 : 1], pl[SPLIT ? RP / 16 : 1];
+  float pf[SPLIT ? 1 : RP / 2];
+  auto p_operands = [&]() __attribute__((always_inline)) {
+    if (d.r != RP) {
+      // ranks past r
+#pragma unroll
+      for (int x = 0; x < NF; ++x)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          raw[x][e] = 4 * ((64 * x + lane) % (RP / 4)) + e < d.r ? raw[x][e] : 0.f;
+    }
     if constexpr (SPLIT) {
+      static_assert(32 * PT * 2 <= S::E_BYTES, "a part of the tile must fit");
+      uint16_t* t = (uint16_t*)ep;
 #pragma unroll
-      for (int s = 0; s < RP / 16; ++s)
+      for (int part = 0; part < 2; ++part) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float v = raw[2 * s + e / 4][e % 4];
-          const __bf16 h = (__bf16)v;
-          ah[s][e] = h;
-          al[s][e] = (__bf16)(v - (float)h);
+        for (int x = 0; x < NF; ++x) {
+          const int f = 64 * x + lane;
+          uint16_t o[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v = raw[x][e];
+            const __bf16 h = (__bf16)v;
+            o[e] = part == 0 ? bf16_bits(h) : bf16_bits((__bf16)(v - (float)h));
+          }
+          *(uint2*)(t + (f / (RP / 4)) * PT + 4 * (f % (RP / 4))) =
+              make_uint2(o[0] | ((uint32_t)o[1] << 16), o[2] | ((uint32_t)o[3] << 16));
         }
-    } else {
+        // written and read by this wave only; LDS keeps a wave's operations
+        // in order, and the waits also order them for the compiler
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-      for (int x = 0; x < 2 * NF; ++x) {
-        pa[2 * x] = g ? raw[x][1] : raw[x][0];
-        pa[2 * x + 1] = g ? raw[x][3] : raw[x][2];
+        for (int s = 0; s < RP / 16; ++s)
+          (part == 0 ? ph : pl)[s] = *(const bf16x8*)(t + li * PT + 16 * s + 8 * g);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      }
+    } else {
+      constexpr int HR = RP < 64 ? RP : 64, HP = HR + 4;   // ranks at a time, pitch
+      static_assert(32 * HP * 4 <= S::E_BYTES, "the ranks that pass at a time must fit");
+      float* t = (float*)ep;
+#pragma unroll
+      for (int h = 0; h < RP / HR; ++h) {
+#pragma unroll
+        for (int x = 0; x < NF; ++x) {
+          const int f = 64 * x + lane, k = 4 * (f % (RP / 4)) - HR * h;
+          if (k >= 0 && k < HR) *(f4v*)(t + (f / (RP / 4)) * HP + k) = raw[x];
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int x = 0; x < HR / 4; ++x) {
+          const f4v v = *(const f4v*)(t + li * HP + 4 * x);
+          pf[HR / 2 * h + 2 * x] = g ? v[1] : v[0];
+          pf[HR / 2 * h + 2 * x + 1] = g ? v[3] : v[2];
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       }
     }
-    if (row0 + 32 * NW < r_hi) p_load(row0 + 32 * NW);
+  };
+  if (row0 < r_hi) p_operands();
+  if (row0 + 32 * NW < r_hi) p_load(row0 + 32 * NW);
 
+  for (; row0 < r_hi; row0 += 32 * NW) {
 #pragma unroll
     for (int c2 = 0; c2 < 2; ++c2) {       // two 32-column tiles at a time
       f16v acc[2] = {f16v{}, f16v{}};
       if constexpr (SPLIT) {
 #pragma unroll
         for (int s = 0; s < RP / 16; ++s) {
+          bf16x8 qhv[2], qlv[2];
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
             const int o = (64 * c2 + 32 * u + li) * PT + 16 * s + 8 * g;
-            const bf16x8 bh = *(const bf16x8*)(qh + o);
-            const bf16x8 bl = *(const bf16x8*)(ql + o);
-            acc[u] = mfma32bf(ah[s], bh, acc[u]);
-            acc[u] = mfma32bf(ah[s], bl, acc[u]);
-            acc[u] = mfma32bf(al[s], bh, acc[u]);
+            qhv[u] = *(const bf16x8*)(qh + o);
+            qlv[u] = *(const bf16x8*)(ql + o);
           }
+          // the two tiles' products alternate: each accumulates in the order
+          // hi hi, lo hi, hi lo, and no product waits for the one before it
+#pragma unroll
+          for (int u = 0; u < 2; ++u) acc[u] = mfma32bf(qhv[u], ph[s], acc[u]);
+#pragma unroll
+          for (int u = 0; u < 2; ++u) acc[u] = mfma32bf(qlv[u], ph[s], acc[u]);
+#pragma unroll
+          for (int u = 0; u < 2; ++u) acc[u] = mfma32bf(qhv[u], pl[s], acc[u]);
         }
       } else {
 #pragma unroll
@@ -162,17 +258,22 @@ __global__ __launch_bounds__(dc_waves(RP) * kWave) void k_dec(Desc d) {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int u = 0; u < 2; ++u) acc[u] = mfma32(pa[4 * k4 + e], b[u][e], acc[u]);
+            for (int u = 0; u < 2; ++u) acc[u] = mfma32(b[u][e], pf[4 * k4 + e], acc[u]);
         }
       }
-      // acc[u][v] = M_hat[row0 + mf32_row(v, g)][c0 + 64 c2 + 32 u + li]
+      // acc[u][4 q + w] = M_hat[row0 + li][c0 + 64 c2 + 32 u + 8 q + 4 g + w]
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int o = mf32_row(v, g) * EP + 32 * u + li;
-          if constexpr (OUTBF) ((uint16_t*)ep)[o + 64 * c2] = bf16_rne(acc[u][v]);
-          else ((float*)ep)[o] = acc[u][v];
+        for (int q = 0; q < 4; ++q) {
+          const int o = li * EP + 32 * u + 8 * q + 4 * g;
+          if constexpr (OUTBF)
+            *(uint2*)((uint16_t*)ep + o + 64 * c2) =
+                make_uint2(bf16_pack2(acc[u][4 * q], acc[u][4 * q + 1]),
+                           bf16_pack2(acc[u][4 * q + 2], acc[u][4 * q + 3]));
+          else
+            *(float4*)((float*)ep + o) = make_float4(acc[u][4 * q], acc[u][4 * q + 1],
+                                                     acc[u][4 * q + 2], acc[u][4 * q + 3]);
         }
       if (OUTBF && c2 == 0) continue;
       // The tile is written and read by this wave only; LDS keeps a wave's
@@ -181,34 +282,39 @@ __global__ __launch_bounds__(dc_waves(RP) * kWave) void k_dec(Desc d) {
       constexpr int W = OUTBF ? 8 : 4;     // elements of a lane's 16 bytes
       const int cl = W * (lane & 15);
       const int col = c0 + cl + (OUTBF ? 0 : 64 * c2);
+      uint4 ov[8];
 #pragma unroll
-      for (int x = 0; x < 8; ++x) {
-        const int rr = 4 * x + (lane >> 4), row = row0 + rr;
-        const uint4 v = *(const uint4*)(ep + (rr * EP + cl) * (OUTBF ? 2 : 4));
-        if (row >= r_hi || col >= d.n) continue;
-        const int64_t off = (int64_t)row * d.ldh + col;
-        if (col + W <= d.n) {
-          if constexpr (NT) {
-            typedef uint32_t nu4 __attribute__((ext_vector_type(4)));
-            __builtin_nontemporal_store(nu4{v.x, v.y, v.z, v.w},
-                                        (nu4*)((uint8_t*)d.Mhat + off * (OUTBF ? 2 : 4)));
-          } else if constexpr (OUTBF) {
-            *(u4h_t*)((uint16_t*)d.Mhat + off) = u4h_t{v.x, v.y, v.z, v.w};
-          } else {
-            *(f4u_t*)(d.Mhat + off) = f4u_t{__uint_as_float(v.x), __uint_as_float(v.y),
-                                            __uint_as_float(v.z), __uint_as_float(v.w)};
+      for (int x = 0; x < 8; ++x)
+        ov[x] = *(const uint4*)(ep + ((4 * x + (lane >> 4)) * EP + cl) * (OUTBF ? 2 : 4));
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (c2 == 1) {
+        // the next tile's operands, and the loads of the one after it
+        if (row0 + 32 * NW < r_hi) p_operands();
+        if (row0 + 64 * NW < r_hi) p_load(row0 + 64 * NW);
+      }
+      if (row0 + 32 <= r_hi && c0 + DC_COLS <= d.n) {
+        // the common tile, without tests
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+          dc_store16<OUTBF, NT>(d, (int64_t)(row0 + 4 * x + (lane >> 4)) * d.ldh + col, ov[x]);
+      } else {
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const int row = row0 + 4 * x + (lane >> 4);
+          const int64_t off = (int64_t)row * d.ldh + col;
+          if (row < r_hi && col + W <= d.n) {
+            dc_store16<OUTBF, NT>(d, off, ov[x]);
+          } else if (row < r_hi) {
+            const uint32_t w[4] = {ov[x].x, ov[x].y, ov[x].z, ov[x].w};
+#pragma unroll
+            for (int j = 0; j < W; ++j)
+              if (col + j < d.n) {
+                if constexpr (OUTBF) ((uint16_t*)d.Mhat)[off + j] = (uint16_t)(w[j / 2] >> (16 * (j % 2)));
+                else d.Mhat[off + j] = __uint_as_float(w[j]);
+              }
           }
-        } else {
-          const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-          for (int j = 0; j < W; ++j)
-            if (col + j < d.n) {
-              if constexpr (OUTBF) ((uint16_t*)d.Mhat)[off + j] = (uint16_t)(w[j / 2] >> (16 * (j % 2)));
-              else d.Mhat[off + j] = __uint_as_float(w[j]);
-            }
         }
       }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
   }
 }

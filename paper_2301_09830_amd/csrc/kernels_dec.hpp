@@ -8,16 +8,18 @@
 // bf16 they stored 2 bytes a lane into 64-byte pieces of rows (16384 x 8192,
 // rank 128, bf16 out: 203 us for 268 MB).  Here a block stages 128 columns of
 // Q in LDS once, and each wave then walks 32-row tiles by itself, with no
-// barrier: its P rows come straight into the B operands (two tiles ahead), the four
-// 32-column tiles take their A operands from LDS, and the results pass
-// through a wave's own LDS tile to be stored as 256-byte pieces of rows, 16
-// bytes a lane.  The products run transposed (M_hat^T = Q P^T), so that a lane
-// holds four consecutive columns of a row and writes them to LDS at once.
-// Loads and stores complete in order, so whatever waits for the next tile's P
-// also waits for the stores issued before it: the operands are formed before
-// this tile's stores go out, not after.  16384 x 8192, rank 128, bf16 out:
-// 203 us before, DEC_MID us with the operands formed after the stores, now
-// DEC_NEW us; 8192 x 4096, rank 64, fp32 out: 57 -> DEC64_NEW us.
+// barrier: its P rows are loaded whole, two tiles ahead, and turned into the
+// B operands through the wave's own LDS tile (loading them in operand order
+// fetched every line four times), the four 32-column tiles take their A
+// operands from the Q tile, and the results pass through the wave's LDS tile
+// to be stored as 256-byte pieces of rows, 16 bytes a lane.  The products run
+// transposed (M_hat^T = Q P^T), so that a lane holds four consecutive columns
+// of a row and writes them to LDS at once.  The common tile has no bounds
+// tests: one at every load made each load wait for the one before.
+// 16384 x 8192, rank 128, bf16 out: 203 -> 113 us; 8192 x 4096, rank 64, fp32
+// out: 57 -> 31 us (4.4 TB/s).  At rank 128 neither the products nor the
+// stores bound the pass alone (a third of the products takes 14 % less time,
+// none of the stores 19 % less): two waves per SIMD overlap them only partly.
 //
 // The products and their order are those of the fused step (k_mlx when SPLIT,
 // k_ml otherwise), so M_hat is bitwise the one that step writes.

@@ -47,11 +47,13 @@ __device__ __forceinline__ typename MVec<DT>::T neg_zero_m() {
   else return make_uint2(0x80008000u, 0x80008000u);
 }
 
-// Whether a W-element load of M at column c of row `row` (of d.m; row pr of
-// M) stays inside the array although it may pass the end of that row.
+// Whether a w-element load of M at column c (< d.n) of row `row` (of d.m; row
+// pr of M) stays inside the array although it may pass the end of that row:
+// a next row exists, and its elements reach far enough.
 template <bool RM>
 __device__ __forceinline__ bool m_load_inside(const Desc& d, int row, int64_t pr, int c, int w) {
-  return c + w <= d.n || (RM ? pr < (int64_t)d.rmap[d.m - 1] : row + 1 < d.m);
+  return c + w <= d.n ||
+         ((RM ? pr < (int64_t)d.rmap[d.m - 1] : row + 1 < d.m) && (int64_t)c + w <= (int64_t)d.ldm + d.n);
 }
 
 // W elements of err_prev from column c of its row, the first nv (< W) of

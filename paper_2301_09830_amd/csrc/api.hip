@@ -196,7 +196,7 @@ Slots device_slots_for(int dev) {
   constexpr bool X3 = DT == DT_BF16;
   int bp = 0, bq = 0, bm = 0;
   bool ok = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                 &bp, k_lp<DT, RP, SA_MERR_SAVE, X3, true>, lp_block_rows(RP, X3) / 32 * kWave,
+                 &bp, k_lp<DT, RP, SA_MERR_SAVE, X3, TILES_16>, lp_block_rows(RP, X3) / 32 * kWave,
                  0) == hipSuccess;
   if constexpr (X3)
     ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_lqx<DT_F32, RP, SA_SAVED, TILES_16>,
@@ -463,35 +463,35 @@ occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish,
         const bool saved = b.descs[0].err_out != nullptr;
         // bf16 M: left products on bf16 matrix cores with split operands
         constexpr bool X3 = DT == DT_BF16;
-        // left products with their A tiles through LDS when every row is
-        // 16-byte aligned, every 32-column K-step whole and A has a source.
+        // A tiles through LDS: in 16-byte pieces when every row is 16-byte
+        // aligned and every 32-column K-step whole, else in 4-byte pieces.
         // With a row map only the first left product (M and err_prev rows)
         // and the reconstruction (err and M_hat rows) use it: the stored A is
         // compact, so every pass in between is the dense kernel.
-        constexpr bool TL = true;
         constexpr int LPT = lp_block_rows(RP, X3) / 32 * kWave;   // threads of a left-product block
         bool whole = VEC;
         for (const Desc& dd : b.descs) whole = whole && dd.n % 32 == 0;
-        const bool tiles_merr = whole && b.descs[0].err_in != nullptr;
         bool pad_q = X3 || !saved;
         for (const Desc& dd : b.descs) pad_q = pad_q || !lp_reads_q<RP>(dd);
         if (pad_q) L("qpad", k_qpadl<RP>, b.blocks[K_QPAD]);
         for (int it = 0; it < b.iters; ++it) {
           if (!saved) {
-            if (tiles_merr)
-              LB("pass_p", k_lp<DT, RP, SA_MERR, X3, TL, RM>, b.blocks[K_PASS_P], LPT);
+            if (!b.descs[0].err_in)
+              LB("pass_p", k_lp<DT, RP, SA_MERR, X3, TILES_NONE>, b.blocks[K_PASS_P], LPT);
+            else if (whole)
+              LB("pass_p", k_lp<DT, RP, SA_MERR, X3, TILES_16>, b.blocks[K_PASS_P], LPT);
             else
-              LB("pass_p", k_lp<DT, RP, SA_MERR, X3, false, RM>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p", k_lp<DT, RP, SA_MERR, X3, TILES_4>, b.blocks[K_PASS_P], LPT);
           } else if (it == 0) {
-            if (tiles_merr)
-              LB("pass_p_first", k_lp<DT, RP, SA_MERR_SAVE, X3, TL, RM>, b.blocks[K_PASS_P], LPT);
+            if (whole)
+              LB("pass_p_first", k_lp<DT, RP, SA_MERR_SAVE, X3, TILES_16, RM>, b.blocks[K_PASS_P], LPT);
             else
-              LB("pass_p_first", k_lp<DT, RP, SA_MERR_SAVE, X3, false, RM>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p_first", k_lp<DT, RP, SA_MERR_SAVE, X3, TILES_4, RM>, b.blocks[K_PASS_P], LPT);
           } else {
             if (whole)
-              LB("pass_p_a", k_lp<DT_F32, RP, SA_SAVED, X3, TL>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p_a", k_lp<DT_F32, RP, SA_SAVED, X3, TILES_16>, b.blocks[K_PASS_P], LPT);
             else
-              LB("pass_p_a", k_lp<DT_F32, RP, SA_SAVED, X3, false>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p_a", k_lp<DT_F32, RP, SA_SAVED, X3, TILES_4>, b.blocks[K_PASS_P], LPT);
           }
           // the kernels named ...2 return at once unless the first pass asked
           // for a second; gram2 is left to apply where that has the same rows

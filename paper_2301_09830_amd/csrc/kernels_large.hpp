@@ -293,22 +293,32 @@ struct LPTile {
 // Rows of M and err_prev a lane's tile loads read (the tile rows are the same
 // for every K-step of a wave): with the row map, looked up once before the
 // K-loop, so the loop issues nothing but the tile DMA its wait counts assume.
+// TILES_16: a[q] is the err_prev row 8q + l / 8 (q < 4), m[q] the M row (bf16
+// 16q + l / 4, q < 2; fp32 as a).  TILES_4: a[q] is row 2q + l / 32 of both,
+// m[0] the M row of a bf16 operand, l % 32.
+template <int DT, int TILES>
 struct LPRows {
-  int64_t a[4];   // err_prev rows 8q + l / 8
-  int64_t m[4];   // M rows: bf16 16q + l / 4 (q < 2), fp32 as a
+  int a[TILES == TILES_4 ? 16 : 4];
+  int m[TILES == TILES_4 ? 1 : 4];
 };
 
-template <int DT, bool RM>
-__device__ __forceinline__ LPRows lp_rows(const Desc& d, int row0) {
-  LPRows r{};
+template <int DT, int TILES, bool RM>
+__device__ __forceinline__ LPRows<DT, TILES> lp_rows(const Desc& d, int row0) {
+  LPRows<DT, TILES> r{};
   if constexpr (RM) {
     const int lane = threadIdx.x & 63, last = d.m - 1;
+    if constexpr (TILES == TILES_4) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) r.a[q] = prow<RM>(d, min(row0 + 8 * q + (lane >> 3), last));
+      for (int q = 0; q < 16; ++q) r.a[q] = (int)prow<RM>(d, min(row0 + 2 * q + (lane >> 5), last));
+      r.m[0] = (int)prow<RM>(d, min(row0 + (lane & 31), last));
+    } else {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      r.m[q] = DT == DT_BF16 ? (q < 2 ? prow<RM>(d, min(row0 + 16 * q + (lane >> 2), last)) : 0)
-                             : r.a[q];
+      for (int q = 0; q < 4; ++q) r.a[q] = (int)prow<RM>(d, min(row0 + 8 * q + (lane >> 3), last));
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        r.m[q] = DT == DT_BF16 ? (q < 2 ? (int)prow<RM>(d, min(row0 + 16 * q + (lane >> 2), last)) : 0)
+                               : r.a[q];
+    }
   }
   return r;
 }
@@ -322,15 +332,32 @@ __device__ __forceinline__ LPRows lp_rows(const Desc& d, int row0) {
 // pass 2457 -> 2408 us, the embedding's first pass 414 -> 396 us; bf16 M
 // non-temporal made the rank-128 first pass 1161 -> 1267 us.
 constexpr int LP_NT = 2;
-template <int DT, int SA, bool RM = false>
+template <int DT, int SA, int TILES, bool RM = false>
 __device__ __forceinline__ void lp_tile_issue(const Desc& d, int row0, int c0, uint8_t* dst,
-                                              const LPRows& pr = LPRows{}) {
+                                              const LPRows<DT, TILES>& pr) {
   const int lane = threadIdx.x & 63;
   const int last = d.m - 1;
   const float* asrc = SA == SA_SAVED ? d.err_out : d.err_in;
   const int64_t lda = SA == SA_SAVED ? d.lde_out : d.lde_in;
   // the stored A is compact: only M and err_prev go through the row map
   constexpr bool MAP = RM && SA != SA_SAVED;
+  if constexpr (TILES == TILES_4) {
+    // The same bytes in 4-byte pieces, two rows at a time (lane l: row 2q +
+    // l / 32, element l % 4 of the chunk that belongs in slot l % 32 / 4).
+    // Columns past n read the row's last element; they are dropped when read.
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int rr = 2 * (q & 3) + (lane >> 5), sl = (lane & 31) >> 2;
+      const int c = min(c0 + 4 * (sl ^ rr) + (lane & 3), d.n - 1);
+      const int64_t row = MAP ? pr.a[q] : min(row0 + 2 * q + (lane >> 5), last);
+      const int off = (q >> 2) * LP_ESLOT + (q & 3) * 256;
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(asrc + row * lda + c), (lvoid_t*)(dst + off), 4, 0, 0);
+      if constexpr (SA != SA_SAVED && DT == DT_F32)
+        __builtin_amdgcn_global_load_lds((gvoid_t*)((const float*)d.M + row * d.ldm + c),
+                                         (lvoid_t*)(dst + LPTile<DT, SA>::A_BYTES + off), 4, 0, 0);
+    }
+    return;
+  }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     // rows 8q .. 8q+7: lane l takes row l / 8, chunk (l % 8) ^ (l / 8)
@@ -365,9 +392,33 @@ __device__ __forceinline__ void lp_tile_issue(const Desc& d, int row0, int c0, u
   }
 }
 
-// A[row li][columns 16g .. 16g+15] of a tile (the values rawa_val gives).
-template <int DT, int SA>
-__device__ __forceinline__ void lp_tile_read(const uint8_t* src, int li, int g, float a[16]) {
+// The 16 bf16 M elements of a lane's operand row (TILES_4: a bf16 row may
+// start at an odd element, which DMA cannot), columns c .. c+15 of row `row`
+// (row pr of M); elements past the row's end are dropped when used.
+template <bool RM>
+__device__ __forceinline__ void lp_m_load(const Desc& d, int row, int64_t pr, int c, uint4 (&m)[2]) {
+  const int r = min(row, d.m - 1);
+  const uint16_t* p = (const uint16_t*)d.M + pr * d.ldm;
+  if (m_load_inside<RM>(d, r, pr, c, 16)) {
+    m[0] = ld_h8<false>(p + c);
+    m[1] = ld_h8<false>(p + c + 8);
+  } else {
+    uint32_t w[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t lo = p[min(c + 2 * j, d.n - 1)], hi = p[min(c + 2 * j + 1, d.n - 1)];
+      w[j] = lo | (hi << 16);
+    }
+    m[0] = make_uint4(w[0], w[1], w[2], w[3]);
+    m[1] = make_uint4(w[4], w[5], w[6], w[7]);
+  }
+}
+
+// A[row li][columns 16g .. 16g+15] of a tile (the values rawa_val gives);
+// TILES_4 with bf16 M: M from `mreg`.
+template <int DT, int SA, int TILES>
+__device__ __forceinline__ void lp_tile_read(const uint8_t* src, int li, int g, float a[16],
+                                             const uint4 (&mreg)[2]) {
   const int q = li >> 3, rr = li & 7;
   const uint8_t* e = src + q * LP_ESLOT + rr * 128;
   float ev[16];
@@ -384,7 +435,9 @@ __device__ __forceinline__ void lp_tile_read(const uint8_t* src, int li, int g, 
     const uint8_t* m = src + LPTile<DT, SA>::A_BYTES + qb * LP_BSLOT + rb * 64;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const uint4 w = *(const uint4*)(m + 16 * ((2 * g + t) ^ (rb >> 2)));
+      uint4 w;
+      if constexpr (TILES == TILES_4) w = mreg[t];
+      else w = *(const uint4*)(m + 16 * ((2 * g + t) ^ (rb >> 2)));
       const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -440,7 +493,7 @@ __host__ __device__ __forceinline__ bool lp_reads_q(const Desc& d) {
 
 // RM (row-sparse step): M and err_prev rows through the row map; the stored A
 // (SA_MERR_SAVE writes it, SA_SAVED reads it) is compact.
-template <int DT, int RP, int SA, bool X3, bool TILES, bool RM = false>
+template <int DT, int RP, int SA, bool X3, int TILES, bool RM = false>
 __device__ __forceinline__ void lp_body(const Desc& d, int b,
                                         std::conditional_t<X3, LPXSmem<RP>, LPSmem<RP>>& sm,
                                         uint8_t* tiles) {
@@ -554,26 +607,44 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
     }
   };
 
-  // TILES: A tiles through LDS (the host picks this instance when rows are
-  // 16-byte aligned, every K-step is whole and A has a source); else A goes
-  // straight into registers.
-  if constexpr (TILES) {
+  // A tiles through LDS: TILES_16 when rows are 16-byte aligned and every
+  // K-step whole, else TILES_4; A without an error buffer (compress-only
+  // calls) goes straight into registers.  5003 x 2047 fp32 at rank 48:
+  // 61 us in registers, 57 us in 4-byte pieces.
+  if constexpr (TILES != TILES_NONE) {
     constexpr int SB = LPTile<DT, SA>::BYTES;
+    constexpr bool MREG = TILES == TILES_4 && SA != SA_SAVED && DT == DT_BF16;
     uint8_t* const wt = tiles + wave * 2 * SB;   // this wave's two stages
     const int wrow0 = rt * LR + 32 * wave;
-    const LPRows prw = lp_rows<DT, RM && SA != SA_SAVED>(d, wrow0);
-    lp_tile_issue<DT, SA, RM>(d, wrow0, kcol_of(c_lo, ks0, 0, nk), wt, prw);
+    const auto prw = lp_rows<DT, TILES, RM && SA != SA_SAVED>(d, wrow0);
+    const int64_t mrow = RM && SA != SA_SAVED ? prw.m[0] : min(row, d.m - 1);
+    uint4 mr[2] = {};
+    auto tile_issue = [&](int it) {
+      const int c = kcol_of(c_lo, ks0, it, nk);
+      if constexpr (MREG) lp_m_load<RM>(d, row, mrow, min(c + 16 * g, d.n - 1), mr);
+      lp_tile_issue<DT, SA, TILES, RM>(d, wrow0, c, wt + (it & 1) * SB, prw);
+    };
+    tile_issue(0);
     __syncthreads();
     for (int it = 0; it < nk; ++it) {
       const int kc0 = kcol_of(c_lo, ks0, it, nk);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      q_advance(it);
+      if constexpr (!MREG) q_advance(it);
       const uint8_t* cur = wt + (it & 1) * SB;
       float a[16];
-      lp_tile_read<DT, SA>(cur, li, g, a);
-      if constexpr (SA == SA_MERR_SAVE) lp_tile_store_a<DT>(d, cur, wrow0, kc0);
-      if (it + 1 < nk)
-        lp_tile_issue<DT, SA, RM>(d, wrow0, kcol_of(c_lo, ks0, it + 1, nk), wt + ((it + 1) & 1) * SB, prw);
+      lp_tile_read<DT, SA, TILES>(cur, li, g, a, mr);
+      if constexpr (TILES == TILES_4) {
+        if (kc0 + L_KC > c_hi) {
+          // columns past n: zero, as in the register form
+#pragma unroll
+          for (int j = 0; j < 16; ++j) a[j] = kc0 + 16 * g + j < c_hi ? a[j] : 0.f;
+        }
+        if constexpr (SA == SA_MERR_SAVE) a_store<16>(d, row, kc0 + 16 * g, c_hi, a);
+      } else {
+        if constexpr (SA == SA_MERR_SAVE) lp_tile_store_a<DT>(d, cur, wrow0, kc0);
+      }
+      if constexpr (MREG) q_advance(it);
+      if (it + 1 < nk) tile_issue(it + 1);
       mfma_step(a, it & 1);
       if (it + 1 < nk) {
 #pragma unroll
@@ -624,7 +695,7 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
   }
 }
 
-template <int DT, int RP, int SA, bool X3, bool TILES, bool RM = false>
+template <int DT, int RP, int SA, bool X3, int TILES, bool RM = false>
 __global__ __launch_bounds__(lp_block_rows(RP, X3) / 32 * kWave) void k_lp(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) std::conditional_t<X3, LPXSmem<RP>, LPSmem<RP>> sm;
   __shared__ __attribute__((aligned(16))) uint8_t

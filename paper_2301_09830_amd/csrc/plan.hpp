@@ -132,6 +132,7 @@ constexpr int L_QG = 8;           // right product: rows per LDS stage
 constexpr int64_t L_SPLIT_BLOCKS = 1024;  // split products: blocks over the whole batch
 constexpr int64_t L_MIN_COLS = 1024;      // left product: columns per split, at least
 constexpr int64_t L_MIN_ROWS = 1024;      // right product: rows per split, at least
+constexpr int64_t L_PRE_STEPS = 6;        // left product: a block's start and end, in K-steps
 constexpr int64_t L_MIN_NARROW = 256;     // the same for matrices that cannot fill a round
 // right product: columns per lane and per block
 __host__ __device__ constexpr int lq_cpl(int rp) { return rp >= 128 ? 1 : 128 / rp; }
@@ -229,7 +230,23 @@ inline Tiling make_tiling(int64_t m, int64_t n, int rp, double share = 1.0,
   auto sp_of = [&](int64_t mc) { return clamp64(cdiv(target, row_tiles), 1, cdiv(n, mc)); };
   while (min_cols > L_MIN_NARROW && row_tiles * sp_of(min_cols) < (int64_t)(share * (double)sl.p))
     min_cols /= 2;
-  const int64_t sp = sp_of(min_cols);
+  int64_t sp = sp_of(min_cols);
+  if (share >= 1.0) {
+    // One matrix alone: its blocks do equal work, so a grid a little over a
+    // whole number of rounds of resident blocks takes a round more.  Of the
+    // split counts up to that, take the one with the least rounds x (K-steps
+    // of a block + L_PRE_STEPS).  5003 x 2047 fp32 at rank 48: 320 blocks of
+    // 8 K-steps on 256 slots 57 us, 240 blocks of 11 K-steps 45 us.
+    int64_t best = 0;
+    for (int64_t x = sp, top = sp; x >= 1; --x) {
+      const int64_t steps = cdiv(cdiv(n, x), L_KC);
+      const int64_t cost = cdiv(row_tiles * cdiv(n, steps * L_KC), sl.p) * (steps + L_PRE_STEPS);
+      if (x == top || cost < best) {
+        best = cost;
+        sp = x;
+      }
+    }
+  }
   t.p_cols = (int)round_up(cdiv(n, sp), L_KC);
   t.sp = (int)cdiv(n, t.p_cols);
   // Gram partials: L_GROWS rows per block, fewer (down to 32) for a matrix
@@ -256,6 +273,20 @@ inline Tiling make_tiling(int64_t m, int64_t n, int rp, double share = 1.0,
   const int64_t ctm = cdiv(n, lm_block_cols(rp));
   const int64_t rbm = clamp64(cdiv(target_m, ctm), 1, cdiv(m, 32));
   t.mr = (int)round_up(cdiv(m, rbm), 32);
+  if (share >= 1.0) {
+    // one matrix alone, as above: up to three times the rows per
+    // block (5003 x 2047 at rank 48: 1264 blocks of 2 tiles on 1024 slots
+    // 44 us, 848 blocks of 3 tiles 40 us)
+    const int64_t tiles0 = t.mr / 32;
+    int64_t best = 0;
+    for (int64_t x = tiles0; x <= 3 * tiles0; ++x) {
+      const int64_t cost = cdiv(ctm * cdiv(m, 32 * x), sl.m) * (x + 1);
+      if (x == tiles0 || cost < best) {
+        best = cost;
+        t.mr = (int)(32 * x);
+      }
+    }
+  }
   t.blocks[K_QPAD] = cdiv(t.n_pad, 32);   // 32-column tiles (k_qpadl)
   t.blocks[K_PASS_P] = row_tiles * t.sp;
   t.blocks[K_PGRAM] = t.ng;

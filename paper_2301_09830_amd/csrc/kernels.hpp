@@ -181,24 +181,6 @@ __device__ __forceinline__ int xcd_tile() {
     BODY(d_, v_ - d_.blk[KIND]);                                        \
   }
 
-// ---------------------------------------------------------------------------
-// Warm-start Q -> padded layout qpad[n_pad][rp] (zeros beyond n and rank).
-// ---------------------------------------------------------------------------
-template <int RP>
-__device__ __forceinline__ void qpad_body(const Desc& d, int b) {
-  const int64_t idx = (int64_t)b * kBlock + threadIdx.x;
-  if (idx >= (int64_t)d.n_pad * RP) return;
-  const int c = (int)(idx / RP), k = (int)(idx % RP);
-  d.qpad[idx] = (c < d.n && k < d.r) ? d.Q[(int64_t)c * d.r + k] : 0.f;
-}
-
-template <int RP>
-__global__ __launch_bounds__(kBlock) void k_qpad(OCC_KARGS) {
-#define B_(d, b) qpad_body<RP>(d, b)
-  OCC_DISPATCH(K_QPAD, B_)
-#undef B_
-}
-
 // gsum[k][l] = sum_b gpart[b][k][l] for k <= l (fixed order), zero below the
 // diagonal (the Gram partials hold the upper triangle only).  MODE 1: second
 // CholeskyQR pass, skipped unless the first pass asked for it.  A block takes GS_ENT entries; GS_SL threads per entry sum interleaved slices of

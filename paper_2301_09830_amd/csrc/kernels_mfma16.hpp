@@ -158,14 +158,14 @@ __device__ __forceinline__ void ch8_values(const Ch8<DT, AL>& x, float a[8]) {
   }
 }
 
-// Eight Q values Q[c..c+7][li] (zero past n or past the padded rank).
+// Eight Q values Q[c..c+7][li] (zero past n or past the rank).
 struct Q8v { float4 a, b; };
 
-template <int RP>
-__device__ __forceinline__ Q8v q8_load(const float* qs, int n, int c, int li) {
+__device__ __forceinline__ Q8v q8_load(const QSrc& qs, int n, int c, int li) {
   float v[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) v[j] = (li < RP && c + j < n) ? qs[(int64_t)(c + j) * RP + li] : 0.f;
+  for (int j = 0; j < 8; ++j)
+    v[j] = (li < qs.pitch && c + j < n) ? qs.p[(int64_t)(c + j) * qs.pitch + li] : 0.f;
   Q8v q;
   q.a = make_float4(v[0], v[1], v[2], v[3]);
   q.b = make_float4(v[4], v[5], v[6], v[7]);
@@ -231,7 +231,7 @@ constexpr int pm_tile_loads() { return 4 + (DT == DT_BF16 ? 2 : 4) + (32 * RP * 
 // rows c0 .. c0+31, into `dst` (rows past m repeat row m-1; their results
 // are never stored).
 template <int DT, int RP>
-__device__ __forceinline__ void pm_tile_issue(const Desc& d, const float* qs, int row0, int c0,
+__device__ __forceinline__ void pm_tile_issue(const Desc& d, const QSrc& qs, int row0, int c0,
                                               uint8_t* dst) {
   const int lane = threadIdx.x & 63;
   const int last = d.m - 1;
@@ -262,11 +262,12 @@ __device__ __forceinline__ void pm_tile_issue(const Desc& d, const float* qs, in
                                        (lvoid_t*)(dst + 4 * PM_ESLOT + q * PM_ESLOT), 16, 0, 0);
     }
   }
-  // Q rows c0 .. c0+31 (32 RP floats, contiguous) as they are
+  // Q rows c0 .. c0+31 (32 pitch floats, contiguous) as they are; every rank
+  // of a padded rank takes the same number of load instructions
 #pragma unroll
   for (int q = 0; q < (32 * RP * 4 + 1023) / 1024; ++q)
-    if (1024 * q + 16 * lane < 32 * RP * 4)
-      __builtin_amdgcn_global_load_lds((gvoid_t*)(qs + (int64_t)c0 * RP + 256 * q + 4 * lane),
+    if (1024 * q + 16 * lane < 32 * 4 * qs.pitch)
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(qs.p + (int64_t)c0 * qs.pitch + 256 * q + 4 * lane),
                                        (lvoid_t*)(dst + 4 * PM_ESLOT + pm_mbytes<DT>() + 1024 * q), 16, 0, 0);
 }
 
@@ -278,7 +279,7 @@ __device__ __forceinline__ void pm_tile_issue(const Desc& d, const float* qs, in
 // The rows are stored to praw, and as doubles to sm.e.rows (zero past m)
 // for the Gram partial; ends with a barrier.
 template <int DT, bool VEC, int RP, bool RM, int WK>
-__device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem<VEC && !RM>& sm) {
+__device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSmem<VEC && !RM>& sm) {
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 15, g = lane >> 4;
   const int nk = (d.n + 31) / 32;
@@ -287,7 +288,7 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem<VEC && !R
   const int rb = grp * rpg + wave / wk, kw = wave % wk;
   const bool live = rb < row_blocks;
   const int row0 = rb * PM_ROWS;
-  const float* qs = q_src<RP>(d);
+  const QSrc qs = q_src<RP>(d, first);
 
   // Row blocks start their walk at staggered K-steps (and wrap around), so
   // that at any moment the device reads many column ranges instead of one
@@ -319,7 +320,7 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem<VEC && !R
   // whole launch); otherwise loads straight into registers.
   bool dma = false;
   if constexpr (VEC && !RM) {
-    dma = d.err_in != nullptr && (d.n & 31) == 0 && ((uintptr_t)qs & 15) == 0;
+    dma = d.err_in != nullptr && (d.n & 31) == 0 && ((uintptr_t)qs.p & 15) == 0;
     if (dma) {
       // This wave's K-steps ks = kw + wk * it; step it lives in stage
       // it % PM_STAGES.  Per step: wait until only the steps issued after it
@@ -359,10 +360,10 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem<VEC && !R
             ds_read_asm<4>(m1[r], e + 4 * PM_ESLOT + 16 * ((2 * g + 1) ^ rr));
           }
         }
-        const int lq = li < RP ? li : 0;
+        const int lq = li < qs.pitch ? li : 0;
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          ds_read_asm<1>(qv[j], cb + 4 * PM_ESLOT + pm_mbytes<DT>() + ((8 * g + j) * RP + lq) * 4);
+          ds_read_asm<1>(qv[j], cb + 4 * PM_ESLOT + pm_mbytes<DT>() + ((8 * g + j) * qs.pitch + lq) * 4);
         static_assert(PM_RB == 2, "the waits below name the operands of two row tiles");
         if constexpr (DT == DT_BF16) {
           asm volatile("s_waitcnt lgkmcnt(0)"
@@ -395,7 +396,7 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem<VEC && !R
           }
         }
         Q8v cq;
-        const bool qin = li < RP;
+        const bool qin = li < qs.pitch;
         cq.a = make_float4(qin ? qv[0] : 0.f, qin ? qv[1] : 0.f, qin ? qv[2] : 0.f, qin ? qv[3] : 0.f);
         cq.b = make_float4(qin ? qv[4] : 0.f, qin ? qv[5] : 0.f, qin ? qv[6] : 0.f, qin ? qv[7] : 0.f);
         mfma_step(x, cq);
@@ -409,7 +410,7 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem<VEC && !R
     const int k_lo = live ? kw : nk;
     auto fetch = [&](int ks, int y) {
       const int c = kcol(ks);
-      rq[y] = q8_load<RP>(qs, d.n, c, li);
+      rq[y] = q8_load(qs, d.n, c, li);
 #pragma unroll
       for (int r = 0; r < PM_RB; ++r) ring[y][r] = ch8_load<DT, VEC, RM>(d, row0 + 16 * r + li, c, d.n);
     };
@@ -454,7 +455,7 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, PMSmem<VEC && !R
 // the launch has fewer K-steps than waves (each matrix's row grouping is
 // chosen at run time); otherwise every matrix takes one row block at a time.
 template <int DT, bool VEC, int RP, bool RM = false, bool NARROW = false>
-__device__ __forceinline__ void pm_body(const Desc& d, int b, PMSmem<VEC && !RM>& sm) {
+__device__ __forceinline__ void pm_body(const Desc& d, int b, int first, PMSmem<VEC && !RM>& sm) {
   constexpr int NP = RP * (RP + 1) / 2;
   static_assert(NP <= PM_THREADS, "one Gram entry per thread");
   const int t = threadIdx.x;
@@ -465,9 +466,9 @@ __device__ __forceinline__ void pm_body(const Desc& d, int b, PMSmem<VEC && !RM>
   const int row_groups = ((d.m + PM_ROWS - 1) / PM_ROWS + rpg - 1) / rpg;
   for (int grp = b; grp < row_groups; grp += d.ng) {
     if (grp != b) __syncthreads();   // the rows are read before the next tiles land there
-    if (!NARROW || wk == PM_WAVES) pm_rows<DT, VEC, RP, RM, PM_WAVES>(d, grp, sm);
-    else if (wk == 2) pm_rows<DT, VEC, RP, RM, 2>(d, grp, sm);
-    else pm_rows<DT, VEC, RP, RM, 1>(d, grp, sm);
+    if (!NARROW || wk == PM_WAVES) pm_rows<DT, VEC, RP, RM, PM_WAVES>(d, grp, first, sm);
+    else if (wk == 2) pm_rows<DT, VEC, RP, RM, 2>(d, grp, first, sm);
+    else pm_rows<DT, VEC, RP, RM, 1>(d, grp, first, sm);
     const int nr = min(rpg * PM_ROWS, d.m - grp * rpg * PM_ROWS);
     if (t < NP)
       for (int i = 0; i < nr; ++i) gacc = fma(sm.e.rows[i * RP + gk], sm.e.rows[i * RP + gl], gacc);
@@ -476,9 +477,9 @@ __device__ __forceinline__ void pm_body(const Desc& d, int b, PMSmem<VEC && !RM>
 }
 
 template <int DT, bool VEC, int RP, bool RM = false, bool NARROW = false>
-__global__ __launch_bounds__(PM_THREADS) void k_pm(OCC_KARGS) {
+__global__ __launch_bounds__(PM_THREADS) void k_pm(OCC_KARGS, int first) {
   __shared__ __attribute__((aligned(16))) PMSmem<VEC && !RM> sm;
-#define B_(d, b) pm_body<DT, VEC, RP, RM, NARROW>(d, b, sm)
+#define B_(d, b) pm_body<DT, VEC, RP, RM, NARROW>(d, b, first, sm)
   OCC_DISPATCH(K_PASS_P, B_)
 #undef B_
 }

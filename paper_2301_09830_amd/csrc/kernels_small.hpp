@@ -125,10 +125,18 @@ __device__ __forceinline__ void chunk_value(const AChunk<DT, AL>& x, float a[4])
   }
 }
 
-// Source of the warm-start or previous round's Q: the caller's Q when
-// rank == RP (same layout), else the padded workspace copy.
+// Q of a round's left product: the caller's warm start, row pitch r, in the
+// first round (read in place: a padded copy would be a launch of its own),
+// the finishing kernel's padded copy, row pitch RP, afterwards.
+struct QSrc {
+  const float* p;
+  int pitch;
+};
+
 template <int RP>
-__device__ __forceinline__ const float* q_src(const Desc& d) { return d.r == RP ? d.Q : d.qpad; }
+__device__ __forceinline__ QSrc q_src(const Desc& d, int first) {
+  return first ? QSrc{d.Q, d.r} : QSrc{d.qpad, RP};
+}
 
 // Packed upper triangle of an RP x RP symmetric matrix: entry p < NP
 // (NP = RP (RP + 1) / 2) is (k, l) with k <= l, row by row.

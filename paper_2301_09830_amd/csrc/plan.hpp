@@ -20,7 +20,7 @@ constexpr int kBlock = 256;  // threads per block of every streaming kernel
 
 // Kernel kinds that have a per-matrix tiled grid.
 enum Kind : int {
-  K_QPAD = 0,    // copy the warm-start Q into the padded layout
+  K_QPAD = 0,    // copy the warm-start Q into the padded layout (large-rank path)
   K_PASS_P,      // P partials = A Q over column splits
   K_PGRAM,       // reduce the splits -> P; Gram partials (fp64)
   K_GSUM,        // sum Gram partials -> G
@@ -184,7 +184,13 @@ inline Tiling make_tiling(int64_t m, int64_t n, int rp, double share = 1.0,
     // right product: at most F_QBLOCKS - 1 blocks, so that they and the
     // block forming T run in one round
     const int64_t col_tiles = cdiv(n, F_QCOLS);
-    const int64_t sq = clamp64((F_QBLOCKS - 1) / col_tiles, 1, cdiv(m, 32));
+    // splits of at least 64 rows, and of 128 where that still leaves 32 of
+    // them: a block's sums over its waves and its partial cost as much as
+    // several K-steps, and every split is read again by the finishing kernel
+    // (4096 x 1024 bf16 rank 8: 63 splits 32.4 us a step, 32 splits 31.2 us;
+    // 1024 x 1024 fp32 rank 4: 32 splits 24.3, 16 splits 23.8, 8 splits 25.2)
+    const int64_t sq = clamp64((F_QBLOCKS - 1) / col_tiles, 1,
+                               std::min(cdiv(m, 64), std::max<int64_t>(32, cdiv(m, 128))));
     t.q_rows = (int)round_up(cdiv(m, sq), 4);
     t.sq = (int)cdiv(m, t.q_rows);
     // reconstruction: 128-column tiles x row blocks (multiple of 64 rows),
@@ -192,7 +198,6 @@ inline Tiling make_tiling(int64_t m, int64_t n, int rp, double share = 1.0,
     const int64_t ctm = cdiv(n, F_MHCOLS);
     const int64_t rbm = clamp64(cdiv(F_MHBLOCKS, ctm), 1, cdiv(m, F_MHGROUP));
     t.mr = (int)round_up(cdiv(m, rbm), F_MHGROUP);
-    t.blocks[K_QPAD] = cdiv((int64_t)t.n_pad * rp, kBlock);
     t.blocks[K_PASS_P] = t.ng;
     t.blocks[K_PASS_Q] = col_tiles * t.sq;   // plus one block per matrix forming T
     t.blocks[K_QRED] = cdiv(n * rp * qfin_slices(t.sq), kBlock);

@@ -507,12 +507,16 @@ occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish,
           LB("chol2", k_lchol<RP, 1>, count, LC_THREADS, flags);
           L("apply2", k_lapply<RP, 1>, b.blocks[K_APPLY], last);
           if constexpr (X3) {
-            // the stored A through LDS tiles under the same conditions
+            // A through LDS tiles; a compress-only call reads M and err_prev
+            // again (bf16 M at element alignment, or no error buffer: into
+            // registers)
             constexpr int QXT = lqx_waves(RP) * kWave;
             if (saved && whole)
               LB("pass_q_a", k_lqx<DT_F32, RP, SA_SAVED, TILES_16>, b.blocks[K_PASS_Q], QXT);
             else if (saved)
               LB("pass_q_a", k_lqx<DT_F32, RP, SA_SAVED, TILES_4>, b.blocks[K_PASS_Q], QXT);
+            else if (b.descs[0].err_in && whole)
+              LB("pass_q", k_lqx<DT, RP, SA_MERR, TILES_16>, b.blocks[K_PASS_Q], QXT);
             else
               LB("pass_q", k_lqx<DT, RP, SA_MERR, TILES_NONE>, b.blocks[K_PASS_Q], QXT);
           } else {
@@ -520,6 +524,10 @@ occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish,
               L("pass_q_a", k_lq<DT_F32, RP, SA_SAVED, TILES_16>, b.blocks[K_PASS_Q]);
             else if (saved)
               L("pass_q_a", k_lq<DT_F32, RP, SA_SAVED, TILES_4>, b.blocks[K_PASS_Q]);
+            else if (b.descs[0].err_in && whole)
+              L("pass_q", k_lq<DT, RP, SA_MERR, TILES_16>, b.blocks[K_PASS_Q]);
+            else if (b.descs[0].err_in)
+              L("pass_q", k_lq<DT, RP, SA_MERR, TILES_4>, b.blocks[K_PASS_Q]);
             else
               L("pass_q", k_lq<DT, RP, SA_MERR, TILES_NONE>, b.blocks[K_PASS_Q]);
           }

@@ -1408,9 +1408,9 @@ __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
     }
 }
 
-// Tile forms of k_lq for the stored fp32 A: both operands of a group come
-// into LDS by DMA, AST - 1 groups ahead, so the loads in flight are not
-// bounded by registers.
+// Tile forms of k_lq for the stored fp32 A (SA_SAVED) or fp32 M and err_prev
+// (SA_MERR, added when read): all operands of a group come into LDS by DMA,
+// AST - 1 groups ahead, so the loads in flight are not bounded by registers.
 //   A: each wave's 8 rows x 32 CPL columns.  TILES_16 (rows 16-byte aligned,
 //      n a multiple of 32): 8/CPL rows per 1 KB global_load_lds_dwordx4 (lane
 //      l: row l / (8 CPL), chunk l % (8 CPL)).  TILES_4 (any rows, any n): the
@@ -1424,23 +1424,25 @@ __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
 // covers the groups still in flight; the operand reads are inline ds_read
 // instructions (the compiler would wait for every DMA in flight before a
 // plain LDS read).
-template <int RP>
+template <int RP, int SA>
 struct LQTile {
   static constexpr int CPL = lq_cpl(RP), NU = RP / 32;
-  static constexpr int NI = CPL;                       // 1 KB pieces of A per wave and group
+  static constexpr int NSRC = SA == SA_MERR ? 2 : 1;   // arrays A comes from
+  static constexpr int NI = CPL;                       // 1 KB pieces of each per wave and group
   static constexpr int NP = RP / 32;                   // P loads per wave and group
   static constexpr int A_BYTES = 1024 * CPL;           // one wave's A tile
   static constexpr int P_BYTES = L_QG * RP * 4;        // the block's P tile
-  static constexpr int STAGE = 4 * A_BYTES + P_BYTES;
-  static constexpr int AST = RP >= 128 ? 4 : 3;        // stages (3 blocks per CU at rank 32)
+  static constexpr int STAGE = 4 * A_BYTES * NSRC + P_BYTES;   // A (err), P, M
+  // stages (3 blocks per CU at rank 32; with M as well, 2 blocks of 2 stages)
+  static constexpr int AST = RP >= 128 ? 4 : (SA == SA_MERR && RP == 32 ? 2 : 3);
 };
 
-template <int RP, int TILES>
-__device__ __forceinline__ void lq_tile_issue(const Desc& d, int r0, int r_last, int cw, int wave,
-                                              uint8_t* stage) {
-  using T = LQTile<RP>;
+// One wave's 8 rows x 32 CPL columns of an fp32 array into `adst`.
+template <int RP, int SA, int TILES>
+__device__ __forceinline__ void lq_array_issue(const Desc& d, const float* src, int64_t ld, int r0,
+                                               int r_last, int cw, uint8_t* adst) {
+  using T = LQTile<RP, SA>;
   const int lane = threadIdx.x & 63;
-  uint8_t* adst = stage + wave * T::A_BYTES;
   if constexpr (TILES == TILES_16) {
     constexpr int CH = 8 * T::CPL, RPI = 8 / T::CPL;
     const int rr = lane / CH, ch = lane % CH;
@@ -1448,8 +1450,7 @@ __device__ __forceinline__ void lq_tile_issue(const Desc& d, int r0, int r_last,
 #pragma unroll
     for (int q = 0; q < T::NI; ++q) {
       const int row = min(r0 + q * RPI + rr, r_last);
-      __builtin_amdgcn_global_load_lds((gvoid_t*)(d.err_out + (int64_t)row * d.lde_out + c),
-                                       (lvoid_t*)(adst + q * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(src + row * ld + c), (lvoid_t*)(adst + q * 1024), 16, 0, 0);
     }
   } else {
     // columns past n: any element of the row (their results are not stored)
@@ -1458,10 +1459,22 @@ __device__ __forceinline__ void lq_tile_issue(const Desc& d, int r0, int r_last,
       const int idx = 64 * q + lane;
       const int row = min(r0 + idx / (32 * T::CPL), r_last);
       const int c = min(cw + idx % (32 * T::CPL), d.n - 1);
-      __builtin_amdgcn_global_load_lds((gvoid_t*)(d.err_out + (int64_t)row * d.lde_out + c),
-                                       (lvoid_t*)(adst + q * 256), 4, 0, 0);
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(src + row * ld + c), (lvoid_t*)(adst + q * 256), 4, 0, 0);
     }
   }
+}
+
+template <int RP, int SA, int TILES>
+__device__ __forceinline__ void lq_tile_issue(const Desc& d, int r0, int r_last, int cw, int wave,
+                                              uint8_t* stage) {
+  using T = LQTile<RP, SA>;
+  const int lane = threadIdx.x & 63;
+  const float* asrc = SA == SA_SAVED ? d.err_out : d.err_in;
+  lq_array_issue<RP, SA, TILES>(d, asrc, SA == SA_SAVED ? d.lde_out : d.lde_in, r0, r_last, cw,
+                                stage + wave * T::A_BYTES);
+  if constexpr (SA == SA_MERR)
+    lq_array_issue<RP, SA, TILES>(d, (const float*)d.M, d.ldm, r0, r_last, cw,
+                                  stage + 4 * T::A_BYTES + T::P_BYTES + wave * T::A_BYTES);
   uint8_t* pdst = stage + 4 * T::A_BYTES;
 #pragma unroll
   for (int j = 0; j < T::NP; ++j) {
@@ -1473,11 +1486,11 @@ __device__ __forceinline__ void lq_tile_issue(const Desc& d, int r0, int r_last,
   }
 }
 
-template <int RP, int TILES>
+template <int RP, int SA, int TILES>
 __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* tiles) {
-  using T = LQTile<RP>;
+  using T = LQTile<RP, SA>;
   constexpr int NU = T::NU, CPL = T::CPL, BC = lq_block_cols(RP), AST = T::AST;
-  constexpr int PER_GROUP = (TILES == TILES_16 ? T::NI : 4 * T::NI) + T::NP;
+  constexpr int PER_GROUP = (TILES == TILES_16 ? T::NI : 4 * T::NI) * T::NSRC + T::NP;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 31, g = lane >> 5;
   const int col_tiles = (d.n + BC - 1) / BC;
@@ -1496,7 +1509,7 @@ __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* til
 
 #pragma unroll
   for (int y = 0; y + 1 < AST; ++y)
-    if (y < ngrp) lq_tile_issue<RP, TILES>(d, r_lo + L_QG * y, r_last, cw, wave, tiles + y * T::STAGE);
+    if (y < ngrp) lq_tile_issue<RP, SA, TILES>(d, r_lo + L_QG * y, r_last, cw, wave, tiles + y * T::STAGE);
 
   const uint32_t tbase = (uint32_t)(size_t)(lvoid_t*)tiles;
   int st_cur = 0;
@@ -1504,13 +1517,13 @@ __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* til
     const int r0 = r_lo + L_QG * grp;
     // groups issued after this one and possibly still in flight
     const int after = min(grp + AST - 2, ngrp - 1) - grp;
-    static_assert(AST <= 4 && 2 * PER_GROUP <= 63, "vmcnt immediates");
-    if (after <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else if (after == 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(PER_GROUP) : "memory");
-    else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * PER_GROUP) : "memory");
+    static_assert(AST <= 4 && (AST - 2) * PER_GROUP <= 63, "vmcnt immediates");
+    if (AST < 3 || after <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else if (AST < 4 || after == 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(AST < 3 ? 0 : PER_GROUP) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(AST < 4 ? 0 : 2 * PER_GROUP) : "memory");
     asm volatile("s_barrier" ::: "memory");   // every wave's P share is in
 
-    typename LdsVec<CPL>::T av[4];
+    typename LdsVec<CPL>::T av[4], mv[4];
     typename LdsVec<NU>::T pv[4];
     const uint32_t sb = tbase + st_cur * T::STAGE;
 #pragma unroll
@@ -1518,14 +1531,23 @@ __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* til
       const int r = 2 * ks + g;
       ds_read_asm<CPL>(av[ks], sb + wave * T::A_BYTES + r * 128 * CPL + 4 * CPL * li);
       ds_read_asm<NU>(pv[ks], sb + 4 * T::A_BYTES + (r * RP + NU * li) * 4);
+      if constexpr (SA == SA_MERR)
+        ds_read_asm<CPL>(mv[ks], sb + 4 * T::A_BYTES + T::P_BYTES + wave * T::A_BYTES + r * 128 * CPL +
+                                     4 * CPL * li);
     }
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(av[0]), "+v"(av[1]), "+v"(av[2]), "+v"(av[3]),
-                   "+v"(pv[0]), "+v"(pv[1]), "+v"(pv[2]), "+v"(pv[3]));
+    if constexpr (SA == SA_MERR)
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(av[0]), "+v"(av[1]), "+v"(av[2]), "+v"(av[3]),
+                     "+v"(pv[0]), "+v"(pv[1]), "+v"(pv[2]), "+v"(pv[3]),
+                     "+v"(mv[0]), "+v"(mv[1]), "+v"(mv[2]), "+v"(mv[3]));
+    else
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(av[0]), "+v"(av[1]), "+v"(av[2]), "+v"(av[3]),
+                     "+v"(pv[0]), "+v"(pv[1]), "+v"(pv[2]), "+v"(pv[3]));
 
     const int st_new = st_cur == 0 ? AST - 1 : st_cur - 1;   // stage of group grp + AST - 1
     if (grp + AST - 1 < ngrp)
-      lq_tile_issue<RP, TILES>(d, r0 + L_QG * (AST - 1), r_last, cw, wave, tiles + st_new * T::STAGE);
+      lq_tile_issue<RP, SA, TILES>(d, r0 + L_QG * (AST - 1), r_last, cw, wave, tiles + st_new * T::STAGE);
     st_cur = st_cur + 1 == AST ? 0 : st_cur + 1;
 
     const int nvalid = r_hi - r0 - g;   // rows 2ks + g of this group inside the split: 2ks < nvalid
@@ -1533,7 +1555,9 @@ __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* til
     for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
       for (int x = 0; x < CPL; ++x) {
-        const float a = 2 * ks < nvalid ? lds_elem<CPL>(av[ks], x) : 0.f;
+        float v = lds_elem<CPL>(av[ks], x);
+        if constexpr (SA == SA_MERR) v = lds_elem<CPL>(mv[ks], x) + v;
+        const float a = 2 * ks < nvalid ? v : 0.f;
 #pragma unroll
         for (int u = 0; u < NU; ++u) acc[x][u] = mfma32(a, lds_elem<NU>(pv[ks], u), acc[x][u]);
       }
@@ -1559,9 +1583,9 @@ template <int DT, int RP, int SA, int TILES, bool RM = false>
 __global__ __launch_bounds__(kBlock) void k_lq(OCC_KARGS) {
   static_assert(!(TILES && RM), "the row map runs on the register form");
   if constexpr (TILES != TILES_NONE) {
-    static_assert(DT == DT_F32 && SA == SA_SAVED, "tiles hold the stored fp32 A");
-    __shared__ __attribute__((aligned(16))) uint8_t tiles[LQTile<RP>::AST * LQTile<RP>::STAGE];
-#define B_(d, b) lq_tiles_body<RP, TILES>(d, b, tiles)
+    static_assert(DT == DT_F32 && SA != SA_MERR_SAVE, "tiles hold fp32 arrays");
+    __shared__ __attribute__((aligned(16))) uint8_t tiles[LQTile<RP, SA>::AST * LQTile<RP, SA>::STAGE];
+#define B_(d, b) lq_tiles_body<RP, SA, TILES>(d, b, tiles)
     OCC_DISPATCH_X(K_PASS_Q, B_)
 #undef B_
   } else {
@@ -1610,24 +1634,30 @@ constexpr int LQX_SLOT = 1024 + 128;
 // stages of A per wave at rank 128 (two groups ahead; two 8-wave blocks per
 // compute unit)
 constexpr int LQX_AST = 3;
-template <int RP>
+// SA_MERR (compress-only calls, TILES_16): err_prev in the slots, and behind
+// them the bf16 M rows of the group as they are (64 CPL bytes each).
+template <int RP, int SA>
 struct LQXTile {
   static constexpr int CPL = lq_cpl(RP);
   static constexpr int RPI = 8 / CPL;                 // rows per load instruction
   static constexpr int NI = LQX_G / RPI;              // slots per group
-  static constexpr int BYTES = NI * LQX_SLOT;         // one stage of one wave
-  // stages per wave: at rank 128 the A tiles run LQX_AST - 1 groups ahead
-  static constexpr int AST = RP >= 128 ? LQX_AST : 2;
+  static constexpr int NM = SA == SA_MERR ? CPL : 0;  // 1 KB pieces of M per group
+  static constexpr int BYTES = NI * LQX_SLOT + NM * 1024;   // one stage of one wave
+  // stages per wave: at rank 128 the stored A runs LQX_AST - 1 groups ahead
+  static constexpr int AST = RP >= 128 && SA == SA_SAVED ? LQX_AST : 2;
 };
 
 // Rows r0 .. r0+15 (clamped to r_last) of columns cw .. cw + 32 CPL - 1
 // (pieces past the last column read the row's last piece instead; those
 // columns are never stored).  TILES_4: the same bytes, each slot as four
 // 256-byte runs of 4-byte pieces.
-template <int RP, int TILES>
+template <int RP, int SA, int TILES>
 __device__ __forceinline__ void lqx_tile_issue(const Desc& d, int r0, int r_last, int cw, uint8_t* dst) {
-  using T = LQXTile<RP>;
+  static_assert(SA == SA_SAVED || TILES == TILES_16, "M rows come in 16-byte pieces");
+  using T = LQXTile<RP, SA>;
   const int lane = threadIdx.x & 63;
+  const float* asrc = SA == SA_SAVED ? d.err_out : d.err_in;
+  const int64_t lda = SA == SA_SAVED ? d.lde_out : d.lde_in;
   if constexpr (TILES == TILES_16) {
     constexpr int CH = 8 * T::CPL;
     const int rr = lane / CH, ch = lane % CH;
@@ -1635,8 +1665,8 @@ __device__ __forceinline__ void lqx_tile_issue(const Desc& d, int r0, int r_last
 #pragma unroll
     for (int q = 0; q < T::NI; ++q) {
       const int row = min(r0 + q * T::RPI + rr, r_last);
-      __builtin_amdgcn_global_load_lds((gvoid_t*)(d.err_out + (int64_t)row * d.lde_out + c),
-                                       (lvoid_t*)(dst + q * LQX_SLOT), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(asrc + row * lda + c), (lvoid_t*)(dst + q * LQX_SLOT), 16,
+                                       0, 0);
     }
   } else {
 #pragma unroll
@@ -1644,23 +1674,46 @@ __device__ __forceinline__ void lqx_tile_issue(const Desc& d, int r0, int r_last
       const int idx = 64 * q + lane;
       const int row = min(r0 + idx / (32 * T::CPL), r_last);
       const int c = min(cw + idx % (32 * T::CPL), d.n - 1);
-      __builtin_amdgcn_global_load_lds((gvoid_t*)(d.err_out + (int64_t)row * d.lde_out + c),
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(asrc + row * lda + c),
                                        (lvoid_t*)(dst + (q / 4) * LQX_SLOT + 256 * (q % 4)), 4, 0, 0);
+    }
+  }
+  if constexpr (SA == SA_MERR) {
+    constexpr int CH = 4 * T::CPL, RPI = 16 / T::CPL;   // chunks per row, rows per instruction
+    const int rr = lane / CH, c = min(cw + 8 * (lane % CH), d.n - 8);
+#pragma unroll
+    for (int q = 0; q < T::NM; ++q) {
+      const int64_t row = min(r0 + q * RPI + rr, r_last);
+      __builtin_amdgcn_global_load_lds((gvoid_t*)((const uint16_t*)d.M + row * d.ldm + c),
+                                       (lvoid_t*)(dst + T::NI * LQX_SLOT + q * 1024), 16, 0, 0);
     }
   }
 }
 
 // a[e][x] = A[row 8g + e of the group][column CPL li + x of the wave]
-template <int RP>
+template <int RP, int SA>
 __device__ __forceinline__ void lqx_tile_read(const uint8_t* src, int li, int g,
-                                              float (&a)[8][LQXTile<RP>::CPL]) {
-  using T = LQXTile<RP>;
+                                              float (&a)[8][LQXTile<RP, SA>::CPL]) {
+  using T = LQXTile<RP, SA>;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int r = 8 * g + e;
     const float* p = (const float*)(src + (r / T::RPI) * LQX_SLOT + (r % T::RPI) * (128 * T::CPL)) +
                      T::CPL * li;
     ld_f<T::CPL>(p, a[e]);
+    if constexpr (SA == SA_MERR) {
+      const uint16_t* m = (const uint16_t*)(src + T::NI * LQX_SLOT + r * 64 * T::CPL) + T::CPL * li;
+      if constexpr (T::CPL == 1) {
+        a[e][0] = __uint_as_float((uint32_t)m[0] << 16) + a[e][0];
+      } else {
+#pragma unroll
+        for (int x = 0; x < T::CPL; x += 2) {
+          const uint32_t w = *(const uint32_t*)(m + x);
+          a[e][x] = bf16_lo(w) + a[e][x];
+          a[e][x + 1] = bf16_hi(w) + a[e][x + 1];
+        }
+      }
+    }
   }
 }
 
@@ -1726,15 +1779,15 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
     // tile AST - 1 groups ahead, run the products.  Loads complete in order:
     // with AST > 2 the A tile issued after the P share this group waits for
     // (group grp + AST - 2) may still be in flight at the wait.
-    static_assert(SA == SA_SAVED, "A tiles hold the stored fp32 A");
-    using T = LQXTile<RP>;
+    static_assert(SA == SA_SAVED || DT == DT_BF16, "A tiles hold the stored fp32 A or err and bf16 M");
+    using T = LQXTile<RP, SA>;
     constexpr int AST = T::AST;
     uint8_t* const wt = tiles + wave * AST * T::BYTES;
     const int r_last = r_hi - 1;
     if (ngrp > 0) p_issue(0, 0);
 #pragma unroll
     for (int y = 0; y + 1 < AST; ++y)
-      if (y < ngrp) lqx_tile_issue<RP, TILES>(d, r_lo + LQX_G * y, r_last, cw, wt + y * T::BYTES);
+      if (y < ngrp) lqx_tile_issue<RP, SA, TILES>(d, r_lo + LQX_G * y, r_last, cw, wt + y * T::BYTES);
     int st_cur = 0;                         // A stage of group grp
     for (int grp = 0; grp < ngrp; ++grp) {
       const int r0 = r_lo + LQX_G * grp;
@@ -1791,12 +1844,12 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
           ah[u] = *(const bf16x8*)(&sm.p[grp & 1][0][32 * u * LQX_G + so]);
           al[u] = *(const bf16x8*)(&sm.p[grp & 1][1][32 * u * LQX_G + so]);
         }
-        lqx_tile_read<RP>(wt + st_cur * T::BYTES, li, g, av);
+        lqx_tile_read<RP, SA>(wt + st_cur * T::BYTES, li, g, av);
       }
       const int st_new = st_cur == 0 ? AST - 1 : st_cur - 1;   // stage of group grp + AST - 1
       if (grp + 1 < ngrp) p_issue(grp + 1, (grp + 1) & 1);
       if (grp + AST - 1 < ngrp)
-        lqx_tile_issue<RP, TILES>(d, r0 + LQX_G * (AST - 1), r_last, cw, wt + st_new * T::BYTES);
+        lqx_tile_issue<RP, SA, TILES>(d, r0 + LQX_G * (AST - 1), r_last, cw, wt + st_new * T::BYTES);
       st_cur = st_cur + 1 == AST ? 0 : st_cur + 1;
       const int nvalid = r_hi - r0 - 8 * g;   // rows of this lane's half inside the split
 #pragma unroll
@@ -1876,7 +1929,7 @@ template <int DT, int RP, int SA, int TILES, bool RM = false>
 __global__ __launch_bounds__(lqx_waves(RP) * kWave) void k_lqx(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) LQXSmem<RP> sm;
   __shared__ __attribute__((aligned(16)))
-  uint8_t tiles[TILES ? lqx_waves(RP) * LQXTile<RP>::AST * LQXTile<RP>::BYTES : 16];
+  uint8_t tiles[TILES ? lqx_waves(RP) * LQXTile<RP, SA>::AST * LQXTile<RP, SA>::BYTES : 16];
 #define B_(d, b) lqx_body<DT, RP, SA, TILES, RM>(d, b, sm, tiles)
   OCC_DISPATCH_X(K_PASS_Q, B_)
 #undef B_

@@ -236,7 +236,7 @@ def profile_name(kname: str) -> str | None:
     base = kname.split("(")[0].replace("void ", "").replace("occ::", "").strip()
     short = base.split("<")[0]
     args = [a.strip() for a in base[len(short) + 1:-1].split(",")] if "<" in base else []
-    fixed = {"k_pm": "pass_p", "k_qm": "pass_q", "k_qfin16": "q_finish", "k_qpad": "qpad",
+    fixed = {"k_pm": "pass_p", "k_qm": "pass_q", "k_qfin16": "q_finish",
              "k_qredl": "q_reduce", "k_qpadl": "qpad"}
     if short in fixed:
         return fixed[short]
@@ -248,14 +248,10 @@ def profile_name(kname: str) -> str | None:
         return {"0": "pass_p", "1": "pass_p_first", "2": "pass_p_a"}[args[2]]
     if short == "k_lq":
         return {"0": "pass_q", "2": "pass_q_a"}[args[2]]
-    if short == "k_ml":
-        if args[3] == "1":
-            return "decompress"
-        return "mhat_err_a" if args[4] == "true" else "err_only_a"
-    if short == "k_mlx":
-        if args[1] == "1":
-            return "decompress"
-        return "mhat_err_a" if args[2] == "true" else "err_only_a"
+    if short in ("k_ml", "k_mlx"):
+        return "mhat_err_a" if args[1] == "true" else "err_only_a"
+    if short == "k_dec":
+        return "decompress"
     if short == "k_lqx":
         return {"0": "pass_q", "2": "pass_q_a"}[args[2]]
     pair = {"k_lg": "gram", "k_gsum": "gram_sum", "k_lchol": "chol", "k_lapply": "apply"}

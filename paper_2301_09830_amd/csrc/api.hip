@@ -600,16 +600,28 @@ occ_status_t decompress_impl(const float* P, const float* Q, int64_t m, int64_t 
         if constexpr (RP > kFusedMaxRank) {
           // one round of resident blocks, each walking as many row tiles as
           // that takes (two rounds where the column tiles alone exceed one)
-          constexpr int NW = dc_waves(RP);
-          const int64_t slots = 256 * dc_blocks_per_cu(RP), ctd = cdiv(n, DC_COLS);
-          const int64_t rbd = clamp64(ctd <= slots ? slots / ctd : cdiv(2 * slots, ctd), 1,
-                                      cdiv(m, 32 * NW));
-          d.mr = (int32_t)round_up(cdiv(m, rbd), 32 * NW);
-          const dim3 grid(grid_of(ctd * cdiv(m, d.mr)));
-          with_bool(split, [&](auto Sc) {
-            hipLaunchKernelGGL((k_dec<RP, decltype(Sc)::value, OUTBF, NT>), grid,
-                               dim3(NW * kWave), 0, s, d);
-          });
+          // (an output whose blocks fill at most half of that takes smaller
+          // ones: a wave's products are its longest serial chain, and a block
+          // of half the columns halves it: 1024 x 512 rank 128 fp32 products
+          // 21.4 -> 8.7 us, 2048 x 1024 rank 100 bf16 out 13.6 -> 9.7 us, 3001 x 777
+          // rank 48 12.2 -> 11.3 us; larger outputs read P half as often in whole
+          // blocks)
+          const bool small = 2 * cdiv(n, DC_COLS) * cdiv(m, 32 * dc_waves(RP, DC_COLS)) <=
+                             256 * dc_blocks_per_cu(RP, DC_COLS);
+          auto go = [&](auto Cc) {
+            constexpr int COLS = decltype(Cc)::value, NW = dc_waves(RP, COLS);
+            const int64_t slots = 256 * dc_blocks_per_cu(RP, COLS), ctd = cdiv(n, COLS);
+            const int64_t rbd = clamp64(ctd <= slots ? slots / ctd : cdiv(2 * slots, ctd), 1,
+                                        cdiv(m, 32 * NW));
+            d.mr = (int32_t)round_up(cdiv(m, rbd), 32 * NW);
+            const dim3 grid(grid_of(ctd * cdiv(m, d.mr)));
+            with_bool(split, [&](auto Sc) {
+              hipLaunchKernelGGL((k_dec<RP, decltype(Sc)::value, OUTBF, NT, COLS>), grid,
+                                 dim3(NW * kWave), 0, s, d);
+            });
+          };
+          if (small) go(std::integral_constant<int, DC_COLS_SMALL>{});
+          else go(std::integral_constant<int, DC_COLS>{});
         } else {
           // same code as the fused step's reconstruction pass
           hipLaunchKernelGGL((k_mh16<DT_F32, NT, RP, 1, true, false, OUTBF>),

@@ -7,10 +7,10 @@
 // barrier per tile; without A to read they wait for the next P tile, and in
 // bf16 they stored 2 bytes a lane into 64-byte pieces of rows (16384 x 8192,
 // rank 128, bf16 out: 203 us for 268 MB).  Here a block stages 128 columns of
-// Q in LDS once, and each wave then walks 32-row tiles by itself, with no
+// Q (64 for small outputs) in LDS once, and each wave then walks 32-row tiles by itself, with no
 // barrier: its P rows are loaded whole, two tiles ahead, and turned into the
 // B operands through the wave's own LDS tile (loading them in operand order
-// fetched every line four times), the four 32-column tiles take their A
+// fetched every line four times), the 32-column tiles take their A
 // operands from the Q tile, and the results pass through the wave's LDS tile
 // to be stored as 256-byte pieces of rows, 16 bytes a lane.  The products run
 // transposed (M_hat^T = Q P^T), so that a lane holds four consecutive columns
@@ -30,20 +30,24 @@
 namespace occ {
 
 constexpr int DC_COLS = 128;               // columns per block
-// waves per block: at rank 128 the Q tile leaves room for one block per
-// compute unit, which then holds eight waves
-__host__ __device__ constexpr int dc_waves(int rp) { return rp >= 128 ? 8 : 4; }
+constexpr int DC_COLS_SMALL = 64;          // the same where the blocks would fill less than half the chip
+// waves per block: at rank 128 a tile of DC_COLS columns of Q leaves room for
+// one block per compute unit, which then holds eight waves
+__host__ __device__ constexpr int dc_waves(int rp, int cols) { return rp >= 128 && cols == DC_COLS ? 8 : 4; }
 // blocks that one compute unit holds (LDS)
-__host__ __device__ constexpr int dc_blocks_per_cu(int rp) { return rp >= 128 ? 1 : 2; }
+__host__ __device__ constexpr int dc_blocks_per_cu(int rp, int cols) { return rp >= 128 && cols == DC_COLS ? 1 : 2; }
 
-template <int RP, bool SPLIT, bool OUTBF>
+template <int RP, bool SPLIT, bool OUTBF, int COLS>
 struct DCShape {
-  static constexpr int NW = dc_waves(RP);
+  static constexpr int NW = dc_waves(RP, COLS);
   static constexpr int PT = SPLIT ? RP + 8 : RP + 4;      // LDS pitch of a Q column (bf16 / float)
-  static constexpr int Q_BYTES = SPLIT ? 2 * DC_COLS * PT * 2 : DC_COLS * PT * 4;
-  static constexpr int EC = OUTBF ? 128 : 64;             // columns of the wave's output tile
+  static constexpr int Q_BYTES = SPLIT ? 2 * COLS * PT * 2 : COLS * PT * 4;
+  static constexpr int EC = OUTBF ? COLS : 64;             // columns of the wave's output tile
   static constexpr int EP = EC + (OUTBF ? 8 : 4);         // its pitch in elements
-  static constexpr int E_BYTES = 32 * EP * (OUTBF ? 2 : 4);
+  static constexpr int O_BYTES = 32 * EP * (OUTBF ? 2 : 4);
+  // P's operands pass through the same tile: one bf16 part of it, or 64 ranks in fp32
+  static constexpr int P_BYTES = SPLIT ? 32 * PT * 2 : 32 * ((RP < 64 ? RP : 64) + 4) * 4;
+  static constexpr int E_BYTES = O_BYTES > P_BYTES ? O_BYTES : P_BYTES;
   static constexpr int BYTES = Q_BYTES + NW * E_BYTES;
 };
 
@@ -86,17 +90,17 @@ __device__ __forceinline__ void dc_store16(const Desc& d, int64_t off, const uin
   }
 }
 
-template <int RP, bool SPLIT, bool OUTBF, bool NT>
-__global__ __launch_bounds__(dc_waves(RP) * kWave) void k_dec(Desc d) {
-  using S = DCShape<RP, SPLIT, OUTBF>;
+template <int RP, bool SPLIT, bool OUTBF, bool NT, int COLS>
+__global__ __launch_bounds__(dc_waves(RP, COLS) * kWave) void k_dec(Desc d) {
+  using S = DCShape<RP, SPLIT, OUTBF, COLS>;
   constexpr int NW = S::NW, NTH = NW * kWave, PT = S::PT, EP = S::EP;
   constexpr int NF = RP / 8;               // float4s of a P row per lane
   __shared__ __attribute__((aligned(16))) uint8_t smem[S::BYTES];
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 31, g = lane >> 5;
-  const int col_tiles = (d.n + DC_COLS - 1) / DC_COLS;
+  const int col_tiles = (d.n + COLS - 1) / COLS;
   const int ct = (int)blockIdx.x % col_tiles, rb = (int)blockIdx.x / col_tiles;
-  const int c0 = ct * DC_COLS;
+  const int c0 = ct * COLS;
   const int r_lo = rb * d.mr, r_hi = min(d.m, r_lo + d.mr);
 
   // P rows of one tile as loaded, whole rows side by side: float4 x of a lane
@@ -120,11 +124,11 @@ __global__ __launch_bounds__(dc_waves(RP) * kWave) void k_dec(Desc d) {
   // lo rows, [part][column][rank]; fp32: [column][g][kp], rank 2 kp + g, so
   // that a lane reads four MFMAs' operands at once.
   uint16_t* qh = (uint16_t*)smem;
-  uint16_t* ql = qh + DC_COLS * PT;
+  uint16_t* ql = qh + COLS * PT;
   float* qf = (float*)smem;
   {
-    constexpr int QL = DC_COLS * RP / 4 / NTH;   // float4s per thread
-    static_assert(QL * NTH * 4 == DC_COLS * RP, "Q tile must split evenly");
+    constexpr int QL = COLS * RP / 4 / NTH;   // float4s per thread
+    static_assert(QL * NTH * 4 == COLS * RP, "Q tile must split evenly");
     f4v q4[QL];
     auto q_load = [&](auto in) __attribute__((always_inline)) {
 #pragma unroll
@@ -133,7 +137,7 @@ __global__ __launch_bounds__(dc_waves(RP) * kWave) void k_dec(Desc d) {
         q4[x] = dc_load4<decltype(in)::value>(d.Q + (int64_t)min(c0 + c, d.n - 1) * d.r, k, d.r);
       }
     };
-    if (dc_inside(c0 + DC_COLS - 1, d.n, d.r, RP)) q_load(std::true_type{});
+    if (dc_inside(c0 + COLS - 1, d.n, d.r, RP)) q_load(std::true_type{});
     else q_load(std::false_type{});
 #pragma unroll
     for (int x = 0; x < QL; ++x) {
@@ -229,7 +233,7 @@ __global__ __launch_bounds__(dc_waves(RP) * kWave) void k_dec(Desc d) {
 
   for (; row0 < r_hi; row0 += 32 * NW) {
 #pragma unroll
-    for (int c2 = 0; c2 < 2; ++c2) {       // two 32-column tiles at a time
+    for (int c2 = 0; c2 < COLS / 64; ++c2) {       // two 32-column tiles at a time
       f16v acc[2] = {f16v{}, f16v{}};
       if constexpr (SPLIT) {
 #pragma unroll
@@ -277,32 +281,34 @@ __global__ __launch_bounds__(dc_waves(RP) * kWave) void k_dec(Desc d) {
             *(float4*)((float*)ep + o) = make_float4(acc[u][4 * q], acc[u][4 * q + 1],
                                                      acc[u][4 * q + 2], acc[u][4 * q + 3]);
         }
-      if (OUTBF && c2 == 0) continue;
+      if (OUTBF && c2 < COLS / 64 - 1) continue;
       // The tile is written and read by this wave only; LDS keeps a wave's
       // operations in order, and the waits also order them for the compiler.
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       constexpr int W = OUTBF ? 8 : 4;     // elements of a lane's 16 bytes
-      const int cl = W * (lane & 15);
+      constexpr int LPR = S::EC / W;       // lanes per row, rows per instruction
+      constexpr int RPI = kWave / LPR, NX = 32 / RPI;
+      const int cl = W * (lane % LPR), rl = lane / LPR;
       const int col = c0 + cl + (OUTBF ? 0 : 64 * c2);
-      uint4 ov[8];
+      uint4 ov[NX];
 #pragma unroll
-      for (int x = 0; x < 8; ++x)
-        ov[x] = *(const uint4*)(ep + ((4 * x + (lane >> 4)) * EP + cl) * (OUTBF ? 2 : 4));
+      for (int x = 0; x < NX; ++x)
+        ov[x] = *(const uint4*)(ep + ((RPI * x + rl) * EP + cl) * (OUTBF ? 2 : 4));
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      if (c2 == 1) {
+      if (c2 == COLS / 64 - 1) {
         // the next tile's operands, and the loads of the one after it
         if (row0 + 32 * NW < r_hi) p_operands();
         if (row0 + 64 * NW < r_hi) p_load(row0 + 64 * NW);
       }
-      if (row0 + 32 <= r_hi && c0 + DC_COLS <= d.n) {
+      if (row0 + 32 <= r_hi && c0 + COLS <= d.n) {
         // the common tile, without tests
 #pragma unroll
-        for (int x = 0; x < 8; ++x)
-          dc_store16<OUTBF, NT>(d, (int64_t)(row0 + 4 * x + (lane >> 4)) * d.ldh + col, ov[x]);
+        for (int x = 0; x < NX; ++x)
+          dc_store16<OUTBF, NT>(d, (int64_t)(row0 + RPI * x + rl) * d.ldh + col, ov[x]);
       } else {
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-          const int row = row0 + 4 * x + (lane >> 4);
+        for (int x = 0; x < NX; ++x) {
+          const int row = row0 + RPI * x + rl;
           const int64_t off = (int64_t)row * d.ldh + col;
           if (row < r_hi && col + W <= d.n) {
             dc_store16<OUTBF, NT>(d, off, ov[x]);

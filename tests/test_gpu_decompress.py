@@ -1,5 +1,6 @@
 """Stand-alone decompression above rank 16 at the edges of its tiles: the
-128-column blocks, 32-row wave tiles, output pieces of 4 or 8 elements, ranks
+64- and 128-column blocks (the last shape's blocks fill more
+than half the chip), 32-row wave tiles, output pieces of 4 or 8 elements, ranks
 that are not padded, factors and outputs at any alignment.
 
 Against float64: an fp32 product of length r with unit-size terms is off by at
@@ -17,7 +18,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rank", [17, 32, 50, 64, 100, 128])
-@pytest.mark.parametrize("shape", [(128, 128), (129, 131), (257, 160), (160, 1027), (2050, 392)])
+@pytest.mark.parametrize("shape", [(128, 128), (129, 131), (257, 160), (160, 1027), (2050, 392),
+                                   (16500, 392)])
 def test_decompress_edges(shape, rank):
     from paper_2301_09830_amd import optcc
     torch = torch_mod()

@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kBlock) void k_err_update(Desc d, uint32_t cpr) {
       // 32-bit division where it is enough
       row[u] = total <= 0xffffffffll ? (int)((uint32_t)q / cpr) : (int)(q / cpr);
       col[u] = 4 * (int)(q - (int64_t)row[u] * cpr);
-      if (col[u] + 4 > d.n) continue;
+      if (d.n - col[u] < 4) continue;   // (col + 4 may pass 2^31)
       const int64_t mo = (int64_t)row[u] * d.ldm + col[u];
       if constexpr (DT == DT_F32) {
         m4[u] = ld_f4<false>((const float*)d.M + mo);
@@ -369,11 +369,11 @@ __global__ __launch_bounds__(kBlock) void k_err_update(Desc d, uint32_t cpr) {
     for (int u = 0; u < EU_UNROLL; ++u) {
       if (row[u] >= d.m) continue;
       float* o = d.err_out + (int64_t)row[u] * d.lde_out + col[u];
-      if (col[u] + 4 <= d.n) {
+      if (d.n - col[u] >= 4) {
         store_f4<NT>(o, (m4[u].x + e4[u].x) - h4[u].x, (m4[u].y + e4[u].y) - h4[u].y,
                      (m4[u].z + e4[u].z) - h4[u].z, (m4[u].w + e4[u].w) - h4[u].w);
       } else {
-        for (int j = 0; col[u] + j < d.n; ++j)
+        for (int j = 0; j < d.n - col[u]; ++j)
           o[j] = load_a1<DT>(d, row[u], col[u] + j) - d.Mhat[(int64_t)row[u] * d.ldh + col[u] + j];
       }
     }

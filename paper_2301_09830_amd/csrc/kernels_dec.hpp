@@ -98,26 +98,29 @@ __global__ __launch_bounds__(dc_waves(RP, COLS) * kWave) void k_dec(Desc d) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[S::BYTES];
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 31, g = lane >> 5;
-  const int col_tiles = (d.n + COLS - 1) / COLS;
+  // m and n may be close to 2^31: rows past a block's or the matrix's last one
+  // are formed unsigned, and columns are compared by what is left of the row
+  const int col_tiles = (int)(((uint32_t)d.n + COLS - 1) / COLS);
   const int ct = (int)blockIdx.x % col_tiles, rb = (int)blockIdx.x / col_tiles;
   const int c0 = ct * COLS;
-  const int r_lo = rb * d.mr, r_hi = min(d.m, r_lo + d.mr);
+  const uint32_t r_lo = (uint32_t)(rb * d.mr), r_hi = min((uint32_t)d.m, r_lo + (uint32_t)d.mr);
 
   // P rows of one tile as loaded, whole rows side by side: float4 x of a lane
   // is float4 64 x + lane of the tile.
   f4v raw[NF];
-  auto p_load_as = [&](auto in, int row0) __attribute__((always_inline)) {
+  auto p_load_as = [&](auto in, uint32_t row0) __attribute__((always_inline)) {
 #pragma unroll
     for (int x = 0; x < NF; ++x) {
-      const int f = 64 * x + lane, row = min(row0 + f / (RP / 4), d.m - 1);
+      const int f = 64 * x + lane;
+      const uint32_t row = min(row0 + f / (RP / 4), (uint32_t)d.m - 1);
       raw[x] = dc_load4<decltype(in)::value>(d.P + (int64_t)row * d.r, 4 * (f % (RP / 4)), d.r);
     }
   };
-  auto p_load = [&](int row0) __attribute__((always_inline)) {
-    if (dc_inside(row0 + 31, d.m, d.r, RP)) p_load_as(std::true_type{}, row0);
+  auto p_load = [&](uint32_t row0) __attribute__((always_inline)) {
+    if (dc_inside((int64_t)row0 + 31, d.m, d.r, RP)) p_load_as(std::true_type{}, row0);
     else p_load_as(std::false_type{}, row0);
   };
-  int row0 = r_lo + 32 * wave;
+  uint32_t row0 = r_lo + 32 * wave;
   if (row0 < r_hi) p_load(row0);
 
   // Q columns c0 .. c0 + 127 into LDS (zero past n and r).  SPLIT: bf16 hi and
@@ -137,7 +140,7 @@ __global__ __launch_bounds__(dc_waves(RP, COLS) * kWave) void k_dec(Desc d) {
         q4[x] = dc_load4<decltype(in)::value>(d.Q + (int64_t)min(c0 + c, d.n - 1) * d.r, k, d.r);
       }
     };
-    if (dc_inside(c0 + COLS - 1, d.n, d.r, RP)) q_load(std::true_type{});
+    if (dc_inside((int64_t)c0 + COLS - 1, d.n, d.r, RP)) q_load(std::true_type{});
     else q_load(std::false_type{});
 #pragma unroll
     for (int x = 0; x < QL; ++x) {
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(dc_waves(RP, COLS) * kWave) void k_dec(Desc d) {
         if (row0 + 32 * NW < r_hi) p_operands();
         if (row0 + 64 * NW < r_hi) p_load(row0 + 64 * NW);
       }
-      if (row0 + 32 <= r_hi && c0 + COLS <= d.n) {
+      if (row0 + 32 <= r_hi && d.n - c0 >= COLS) {
         // the common tile, without tests
 #pragma unroll
         for (int x = 0; x < NX; ++x)
@@ -308,9 +311,9 @@ __global__ __launch_bounds__(dc_waves(RP, COLS) * kWave) void k_dec(Desc d) {
       } else {
 #pragma unroll
         for (int x = 0; x < NX; ++x) {
-          const int row = row0 + RPI * x + rl;
+          const uint32_t row = row0 + RPI * x + rl;
           const int64_t off = (int64_t)row * d.ldh + col;
-          if (row < r_hi && col + W <= d.n) {
+          if (row < r_hi && d.n - col >= W) {
             dc_store16<OUTBF, NT>(d, off, ov[x]);
           } else if (row < r_hi) {
             const uint32_t w[4] = {ov[x].x, ov[x].y, ov[x].z, ov[x].w};

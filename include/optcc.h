@@ -27,6 +27,10 @@
  * - Matrices are row-major.  ld* is the leading dimension in elements
  *   (>= cols).  P is m x rank and Q is n x rank, both contiguous (ld = rank).
  *   err, P, Q and M_hat are fp32.  M is fp32 or bf16 (occ_dtype_t).
+ * - Loads of M may pass the end of a row by up to 15 elements, always inside
+ *   the array (never past the last row's last element), and what they read
+ *   there is not used; occ_step_rows reads the listed rows only.  err is read
+ *   inside its rows only.
  * - Any alignment is accepted; 16-byte aligned bases with ld a multiple of 4
  *   select the vectorised load path.
  * - Argument errors are detected on the host before anything is enqueued and

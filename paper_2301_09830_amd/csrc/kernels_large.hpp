@@ -399,7 +399,7 @@ template <bool RM>
 __device__ __forceinline__ void lp_m_load(const Desc& d, int row, int64_t pr, int c, uint4 (&m)[2]) {
   const int r = min(row, d.m - 1);
   const uint16_t* p = (const uint16_t*)d.M + pr * d.ldm;
-  if (m_load_inside<RM>(d, r, pr, c, 16)) {
+  if (m_load_may_pass(RM, r, d.m, d.ldm, d.n, c, 16)) {
     m[0] = ld_h8<false>(p + c);
     m[1] = ld_h8<false>(p + c + 8);
   } else {

@@ -81,48 +81,51 @@ __device__ __forceinline__ d4v mfma4d(double a, double b, d4v c) {
 // Eight consecutive elements of A = M + err_prev (columns c..c+7 of one row),
 // kept as raw loads until used.  AL: rows of M and err 16-byte aligned and n
 // a multiple of 8, so that a chunk is whole or empty; otherwise rows start at
-// any element and the last chunk of a row holds nv valid elements (loaded as
-// in chunk_issue).  Empty chunks have the value 0 (m = -0: x + -0 == x for
+// any element and the last chunk of a row is loaded tail_back columns to the
+// left (as in chunk_issue).  Empty chunks have the value 0 (m = -0: x + -0 == x for
 // every x).
-template <int DT, bool AL> struct Ch8 { float4 m0, m1; float4 e0, e1; int nv; };
-template <bool AL> struct Ch8<DT_BF16, AL> { uint4 m; float4 e0, e1; int nv; };
+template <int DT> struct Ch8 { float4 m0, m1; float4 e0, e1; };
+template <> struct Ch8<DT_BF16> { uint4 m; float4 e0, e1; };
 
 template <int DT, bool AL, bool RM = false>
-__device__ __forceinline__ Ch8<DT, AL> ch8_load(const Desc& d, int row, int c, int c_hi) {
-  Ch8<DT, AL> x;
+__device__ __forceinline__ Ch8<DT> ch8_load(const Desc& d, int row, int c, int c_hi) {
+  Ch8<DT> x;
   if (row < d.m && (AL ? c + 8 <= c_hi : c < c_hi)) {
     const int64_t pr = prow<RM>(d, row);
-    const int64_t mo = pr * d.ldm + c;
-    if (!AL) x.nv = min(8, c_hi - c);
-    if (AL || m_load_inside<RM>(d, row, pr, c, 8)) {
+    const int cc = c - tail_back<8, AL>(c, c_hi);
+    const int64_t mo = pr * d.ldm + cc;
+    const float* ep = d.err_in + pr * d.lde_in + cc;
+    if (AL || c_hi >= 8) {
       if constexpr (DT == DT_BF16) {
         x.m = ld_h8<AL>((const uint16_t*)d.M + mo);
       } else {
         x.m0 = ld_f4<AL>((const float*)d.M + mo);
         x.m1 = ld_f4<AL>((const float*)d.M + mo + 4);
       }
-    } else {
-      float a[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) a[j] = j < x.nv ? m_elem<DT>(d, mo + j) : -0.f;
-      if constexpr (DT == DT_BF16) {
-        x.m = make_uint4(bf16_pack2(a[0], a[1]), bf16_pack2(a[2], a[3]), bf16_pack2(a[4], a[5]),
-                         bf16_pack2(a[6], a[7]));
+      if (d.err_in) {
+        x.e0 = ld_f4<AL>(ep);
+        x.e1 = ld_f4<AL>(ep + 4);
       } else {
-        x.m0 = make_float4(a[0], a[1], a[2], a[3]);
-        x.m1 = make_float4(a[4], a[5], a[6], a[7]);
+        x.e0 = make_float4(-0.f, -0.f, -0.f, -0.f);
+        x.e1 = x.e0;
       }
-    }
-    const float* ep = d.err_in + pr * d.lde_in + c;
-    if (!d.err_in) {
-      x.e0 = make_float4(-0.f, -0.f, -0.f, -0.f);
-      x.e1 = x.e0;
-    } else if (AL || x.nv == 8) {
-      x.e0 = ld_f4<AL>(ep);
-      x.e1 = ld_f4<AL>(ep + 4);
     } else {
+      // rows of fewer than eight columns: the one chunk starts at column 0
+      uint32_t m[8];
       float e[8];
-      err_tail<8>(ep, x.nv, e);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        m[j] = j < c_hi ? m_bits<DT>(d, mo + j) : 0u;
+        e[j] = d.err_in && j < c_hi ? ep[j] : (j < c_hi ? -0.f : 0.f);
+      }
+      if constexpr (DT == DT_BF16) {
+        x.m = make_uint4(m[0] | (m[1] << 16), m[2] | (m[3] << 16), m[4] | (m[5] << 16), m[6] | (m[7] << 16));
+      } else {
+        x.m0 = make_float4(__uint_as_float(m[0]), __uint_as_float(m[1]), __uint_as_float(m[2]),
+                           __uint_as_float(m[3]));
+        x.m1 = make_float4(__uint_as_float(m[4]), __uint_as_float(m[5]), __uint_as_float(m[6]),
+                           __uint_as_float(m[7]));
+      }
       x.e0 = make_float4(e[0], e[1], e[2], e[3]);
       x.e1 = make_float4(e[4], e[5], e[6], e[7]);
     }
@@ -135,14 +138,13 @@ __device__ __forceinline__ Ch8<DT, AL> ch8_load(const Desc& d, int row, int c, i
     }
     x.e0 = make_float4(0.f, 0.f, 0.f, 0.f);
     x.e1 = x.e0;
-    x.nv = 8;
   }
   return x;
 }
 
-// The eight A values of a chunk.
-template <int DT, bool AL>
-__device__ __forceinline__ void ch8_values(const Ch8<DT, AL>& x, float a[8]) {
+// The eight A values of a chunk (as loaded: see shift_back).
+template <int DT>
+__device__ __forceinline__ void ch8_values(const Ch8<DT>& x, float (&a)[8]) {
   if constexpr (DT == DT_BF16) {
     a[0] = bf16_lo(x.m.x) + x.e0.x; a[1] = bf16_hi(x.m.x) + x.e0.y;
     a[2] = bf16_lo(x.m.y) + x.e0.z; a[3] = bf16_hi(x.m.y) + x.e0.w;
@@ -152,20 +154,40 @@ __device__ __forceinline__ void ch8_values(const Ch8<DT, AL>& x, float a[8]) {
     a[0] = x.m0.x + x.e0.x; a[1] = x.m0.y + x.e0.y; a[2] = x.m0.z + x.e0.z; a[3] = x.m0.w + x.e0.w;
     a[4] = x.m1.x + x.e1.x; a[5] = x.m1.y + x.e1.y; a[6] = x.m1.z + x.e1.z; a[7] = x.m1.w + x.e1.w;
   }
-  if (!AL) {
-#pragma unroll
-    for (int j = 1; j < 8; ++j) a[j] = j < x.nv ? a[j] : 0.f;
-  }
 }
 
-// Eight Q values Q[c..c+7][li] (zero past n or past the rank).
+// The same for rows of at least eight columns, at row `pr` of M and err, with
+// no tests: a chunk past the row's end is loaded from inside the row too
+// (shift_back makes it zero), and without an error buffer `err` is any eight
+// aligned floats, which nothing uses.
+template <int DT, bool AL>
+__device__ __forceinline__ Ch8<DT> ch8_load_in(const Desc& d, const float* err, int64_t lde, int64_t pr,
+                                               int c) {
+  Ch8<DT> x;
+  const int cc = c - tail_back<8, false>(c, d.n);
+  const int64_t mo = pr * d.ldm + cc;
+  const float* ep = err + (d.err_in ? pr * lde + cc : 0);
+  if constexpr (DT == DT_BF16) {
+    x.m = ld_h8<AL>((const uint16_t*)d.M + mo);
+  } else {
+    x.m0 = ld_f4<AL>((const float*)d.M + mo);
+    x.m1 = ld_f4<AL>((const float*)d.M + mo + 4);
+  }
+  x.e0 = ld_f4<AL>(ep);
+  x.e1 = ld_f4<AL>(ep + 4);
+  return x;
+}
+
+// Eight Q values Q[c..c+7][li]; past the last column its last row, past the
+// rank its last column (the first meets zeros of A, the second is dropped
+// when used).
 struct Q8v { float4 a, b; };
 
 __device__ __forceinline__ Q8v q8_load(const QSrc& qs, int n, int c, int li) {
   float v[8];
+  const float* p = qs.p + min(li, qs.pitch - 1);
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
-    v[j] = (li < qs.pitch && c + j < n) ? qs.p[(int64_t)(c + j) * qs.pitch + li] : 0.f;
+  for (int j = 0; j < 8; ++j) v[j] = p[(int64_t)min(c + j, n - 1) * qs.pitch];
   Q8v q;
   q.a = make_float4(v[0], v[1], v[2], v[3]);
   q.b = make_float4(v[4], v[5], v[6], v[7]);
@@ -278,7 +300,7 @@ __device__ __forceinline__ void pm_tile_issue(const Desc& d, const QSrc& qs, int
 // w % wk, w % wk + wk, ... (wk = pm_waves_per_rb(n) waves per row block).
 // The rows are stored to praw, and as doubles to sm.e.rows (zero past m)
 // for the Gram partial; ends with a barrier.
-template <int DT, bool VEC, int RP, bool RM, int WK>
+template <int DT, bool VEC, int RP, bool RM, int WK, bool WIDE>
 __device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSmem<VEC && !RM>& sm) {
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 15, g = lane >> 4;
@@ -304,15 +326,21 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSme
 #pragma unroll
   for (int r = 0; r < PM_RB; ++r) acc[r] = f4v{0.f, 0.f, 0.f, 0.f};
 
-  auto mfma_step = [&](const Ch8<DT, VEC>* x, const Q8v& cq) {
-    const float qv[8] = {cq.a.x, cq.a.y, cq.a.z, cq.a.w, cq.b.x, cq.b.y, cq.b.z, cq.b.w};
+  const bool qin = li < qs.pitch;
+  auto mfma_step = [&](const Ch8<DT>* x, const Q8v& cq, int back) {
+    const float qv[8] = {qin ? cq.a.x : 0.f, qin ? cq.a.y : 0.f, qin ? cq.a.z : 0.f, qin ? cq.a.w : 0.f,
+                         qin ? cq.b.x : 0.f, qin ? cq.b.y : 0.f, qin ? cq.b.z : 0.f, qin ? cq.b.w : 0.f};
+    float a[PM_RB][8];
 #pragma unroll
-    for (int r = 0; r < PM_RB; ++r) {
-      float a[8];
-      ch8_values<DT, VEC>(x[r], a);
+    for (int r = 0; r < PM_RB; ++r) ch8_values(x[r], a[r]);
+    if (__any(back)) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[r] = mfma4(a[j], qv[j], acc[r]);
+      for (int r = 0; r < PM_RB; ++r) shift_back<8>(back, a[r]);
     }
+#pragma unroll
+    for (int r = 0; r < PM_RB; ++r)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[r] = mfma4(a[r][j], qv[j], acc[r]);
   };
 
   // 16-byte aligned rows, whole 32-column K-steps, an error buffer and a
@@ -382,7 +410,7 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSme
                                 tiles + sn * STAGE);
         }
         st = st + 1 == PM_STAGES ? 0 : st + 1;
-        Ch8<DT, VEC> x[PM_RB];
+        Ch8<DT> x[PM_RB];
 #pragma unroll
         for (int r = 0; r < PM_RB; ++r) {
           x[r].e0 = make_float4(e0[r][0], e0[r][1], e0[r][2], e0[r][3]);
@@ -396,32 +424,55 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSme
           }
         }
         Q8v cq;
-        const bool qin = li < qs.pitch;
-        cq.a = make_float4(qin ? qv[0] : 0.f, qin ? qv[1] : 0.f, qin ? qv[2] : 0.f, qin ? qv[3] : 0.f);
-        cq.b = make_float4(qin ? qv[4] : 0.f, qin ? qv[5] : 0.f, qin ? qv[6] : 0.f, qin ? qv[7] : 0.f);
-        mfma_step(x, cq);
+        cq.a = make_float4(qv[0], qv[1], qv[2], qv[3]);
+        cq.b = make_float4(qv[4], qv[5], qv[6], qv[7]);
+        mfma_step(x, cq, 0);   // whole K-steps
       }
     }
   }
   if (!dma) {
-    // PM_RING K-steps of loads in flight
-    Ch8<DT, VEC> ring[PM_RING][PM_RB];
+    // PM_RING K-steps of loads in flight.  The loads and the loop over whole
+    // rings have no tests, so that each step waits for its own loads only
+    // (rows past m repeat row m - 1, as in the tiles).
+    Ch8<DT> ring[PM_RING][PM_RB];
     Q8v rq[PM_RING];
     const int k_lo = live ? kw : nk;
+    int64_t pr[PM_RB];
+#pragma unroll
+    for (int r = 0; r < PM_RB; ++r) pr[r] = prow<RM>(d, min(row0 + 16 * r + li, d.m - 1));
+    const bool has_err = d.err_in != nullptr;
+    const float* const err = has_err ? d.err_in : d.praw;
     auto fetch = [&](int ks, int y) {
       const int c = kcol(ks);
       rq[y] = q8_load(qs, d.n, c, li);
 #pragma unroll
-      for (int r = 0; r < PM_RB; ++r) ring[y][r] = ch8_load<DT, VEC, RM>(d, row0 + 16 * r + li, c, d.n);
+      for (int r = 0; r < PM_RB; ++r)
+        if (WIDE || d.n >= 8) ring[y][r] = ch8_load_in<DT, VEC>(d, err, d.lde_in, pr[r], c);
+        else ring[y][r] = ch8_load<DT, VEC, RM>(d, row0 + 16 * r + li, c, d.n);
+    };
+    auto step = [&](int ks, int y) {
+      if (!has_err) {
+#pragma unroll
+        for (int r = 0; r < PM_RB; ++r)
+          ring[y][r].e0 = ring[y][r].e1 = make_float4(-0.f, -0.f, -0.f, -0.f);
+      }
+      mfma_step(ring[y], rq[y], tail_back<8, false>(kcol(ks), d.n));
     };
 #pragma unroll
-    for (int y = 0; y < PM_RING; ++y)
-      if (k_lo + wk * y < nk) fetch(k_lo + wk * y, y);
-    for (int ks = k_lo; ks < nk; ks += wk * PM_RING) {
+    for (int y = 0; y < PM_RING; ++y) fetch(min(k_lo + wk * y, nk - 1), y);
+    int ks = k_lo;
+    for (; ks + wk * (2 * PM_RING - 1) < nk; ks += wk * PM_RING) {
+#pragma unroll
+      for (int y = 0; y < PM_RING; ++y) {
+        step(ks + wk * y, y);
+        fetch(ks + wk * (y + PM_RING), y);
+      }
+    }
+    for (; ks < nk; ks += wk * PM_RING) {
 #pragma unroll
       for (int y = 0; y < PM_RING; ++y) {
         if (ks + wk * y < nk) {
-          mfma_step(ring[y], rq[y]);
+          step(ks + wk * y, y);
           if (ks + wk * (y + PM_RING) < nk) fetch(ks + wk * (y + PM_RING), y);
         }
       }
@@ -466,9 +517,9 @@ __device__ __forceinline__ void pm_body(const Desc& d, int b, int first, PMSmem<
   const int row_groups = ((d.m + PM_ROWS - 1) / PM_ROWS + rpg - 1) / rpg;
   for (int grp = b; grp < row_groups; grp += d.ng) {
     if (grp != b) __syncthreads();   // the rows are read before the next tiles land there
-    if (!NARROW || wk == PM_WAVES) pm_rows<DT, VEC, RP, RM, PM_WAVES>(d, grp, first, sm);
-    else if (wk == 2) pm_rows<DT, VEC, RP, RM, 2>(d, grp, first, sm);
-    else pm_rows<DT, VEC, RP, RM, 1>(d, grp, first, sm);
+    if (!NARROW || wk == PM_WAVES) pm_rows<DT, VEC, RP, RM, PM_WAVES, !NARROW>(d, grp, first, sm);
+    else if (wk == 2) pm_rows<DT, VEC, RP, RM, 2, false>(d, grp, first, sm);
+    else pm_rows<DT, VEC, RP, RM, 1, false>(d, grp, first, sm);
     const int nr = min(rpg * PM_ROWS, d.m - grp * rpg * PM_ROWS);
     if (t < NP)
       for (int i = 0; i < nr; ++i) gacc = fma(sm.e.rows[i * RP + gk], sm.e.rows[i * RP + gl], gacc);
@@ -521,11 +572,11 @@ __device__ __forceinline__ void qm_body(const Desc& d, int b, QMSmem& sm) {
   const int wr = (nr + QM_WAVES - 1) / QM_WAVES;
   const int w_lo = r_lo + min(nr, wave * wr), w_hi = r_lo + min(nr, wave * wr + wr);
   const int nk = (w_hi - w_lo + 3) / 4;
-  const int col = c0 + 8 * li;
+  const int col = c0 + 8 * li, back = tail_back<8, VEC>(col, d.n);
   d4v acc[8];
 #pragma unroll
   for (int t = 0; t < 8; ++t) acc[t] = d4v{0.0, 0.0, 0.0, 0.0};
-  Ch8<DT, VEC> cur, nxt;
+  Ch8<DT> cur, nxt;
   float cp = 0.f, np = 0.f;
   {
     const int row = w_lo + g;
@@ -542,7 +593,8 @@ __device__ __forceinline__ void qm_body(const Desc& d, int b, QMSmem& sm) {
       np = (ok && li < RP) ? ps[(int64_t)row * RP + li] : 0.f;
     }
     float a[8];
-    ch8_values<DT, VEC>(cur, a);
+    ch8_values(cur, a);
+    if (!VEC && __any(back)) shift_back<8>(back, a);
     const double pd = (double)cp;
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] = mfma4d((double)a[t], pd, acc[t]);
@@ -709,7 +761,7 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
   int r0 = r_lo + 16 * wave;
   if (!WRITE_ERR) factor_load<RP, SRC>(ps, d.r, r0 + li, r_hi - r0 > li, S * g, pn);
   for (int left = r_hi - r0; left > 0; left -= F_MHGROUP, r0 = (int)((uint32_t)r0 + F_MHGROUP)) {
-    AChunk<DT, NT> x[MX_NCH];
+    AChunk<DT> x[MX_NCH];
     if (WRITE_ERR) {
 #pragma unroll
       for (int k = 0; k < MX_NCH; ++k) {
@@ -774,7 +826,7 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
       float e[4] = {0.f, 0.f, 0.f, 0.f};
       if (WRITE_ERR) {
         float a[4];
-        chunk_value<DT, NT>(x[k], a);
+        chunk_value<DT, NT>(x[k], tail_back<4, NT>(col, d.n), a);
 #pragma unroll
         for (int j = 0; j < 4; ++j) e[j] = a[j] - mh[j];
       }

@@ -33,13 +33,23 @@ template <> struct MVec<DT_BF16> { using T = uint2; };
 
 // AL: rows of M and err 16-byte aligned and n a multiple of 4, so that a
 // chunk is whole or empty.  Otherwise rows start at any element and the last
-// chunk of a row may be short: it holds `nv` valid elements.
-template <int DT, bool AL>
+// chunk of a row may be short.  It is loaded from as many columns to the left
+// as it lacks (tail_back), so that one vector load of each array stays inside
+// the row (the columns after it, and the rows around a listed one, may be in
+// use elsewhere; err's columns before it, which another lane may be writing,
+// are dropped).
+template <int DT>
 struct AChunk {
   typename MVec<DT>::T m;
   float4 e;
-  int nv;    // used when !AL
 };
+
+// Columns that a W-column chunk at column c of an n-column row is loaded to
+// the left (W and more where the chunk is empty).
+template <int W, bool AL>
+__device__ __forceinline__ int tail_back(int c, int n) {
+  return AL ? 0 : max(0, c - max(0, n - W));
+}
 
 template <int DT>
 __device__ __forceinline__ typename MVec<DT>::T neg_zero_m() {
@@ -47,70 +57,73 @@ __device__ __forceinline__ typename MVec<DT>::T neg_zero_m() {
   else return make_uint2(0x80008000u, 0x80008000u);
 }
 
-// Whether a w-element load of M at column c (< d.n) of row `row` (of d.m; row
-// pr of M) stays inside the array although it may pass the end of that row:
-// a next row exists, and its elements reach far enough.
-template <bool RM>
-__device__ __forceinline__ bool m_load_inside(const Desc& d, int row, int64_t pr, int c, int w) {
-  return c + w <= d.n ||
-         ((RM ? pr < (int64_t)d.rmap[d.m - 1] : row + 1 < d.m) && (int64_t)c + w <= (int64_t)d.ldm + d.n);
+// Bits of M at an element offset (bf16 in the low half).
+template <int DT>
+__device__ __forceinline__ uint32_t m_bits(const Desc& d, int64_t off) {
+  if constexpr (DT == DT_F32) return ((const uint32_t*)d.M)[off];
+  else return ((const uint16_t*)d.M)[off];
 }
 
-// W elements of err_prev from column c of its row, the first nv (< W) of
-// them read one by one, with nothing waiting for them.
+// The W values of a chunk loaded `back` columns to the left: shifted down,
+// zero past the row's end.  For the wave that holds the row's end only
+// (__any(back)): the others have nothing to shift.
 template <int W>
-__device__ __forceinline__ void err_tail(const float* p, int nv, float* e) {
+__device__ __forceinline__ void shift_back(int back, float (&a)[W]) {
 #pragma unroll
-  for (int j = 0; j < W; ++j) {
-    e[j] = -0.f;
-    if (j < nv) e[j] = p[j];
+  for (int s = W / 2; s >= 1; s /= 2) {
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+      const float v = j + s < W ? a[j + s < W ? j + s : 0] : 0.f;
+      a[j] = (back & s) ? v : a[j];
+    }
   }
+#pragma unroll
+  for (int j = 0; j < W; ++j) a[j] = back >= W ? 0.f : a[j];
 }
 
 // Loads only: the values are formed when used, so that the loads stay in
-// flight.  A short chunk takes M in one vector load past the end of the row
-// (M is read-only, and the load stays inside the array) and err, which other
-// blocks may be writing, element by element; the elements from nv on are
-// dropped when the values are formed.  Element-wise tails whose values were
-// added at once made the blocks of the last columns wait for every element:
-// 6001 x 2999 bf16 rank 12, with three K-steps in flight in the left product's
-// register form: 184 -> 134 us a step.
+// flight.  (Element-wise tails, whose values were added at once, made the
+// blocks of the last columns wait for every element: 6001 x 2999 bf16 rank 12,
+// with three K-steps in flight in the left product's register form: 184 ->
+// 134 us a step.  M loaded past the row's end and err's tail element by
+// element instead of both from the left: 5003 x 2047 rank 12 fp32 85 us a step
+// against 82, bf16 83 against 80.)
 template <int DT, bool AL, bool RM = false>
 __device__ __forceinline__ void chunk_issue(const Desc& d, int row, int col, int c_hi,
-                                            AChunk<DT, AL>& x) {
+                                            AChunk<DT>& x) {
   if (row < d.m && (AL ? col + 4 <= c_hi : col < c_hi)) {
     const int64_t pr = prow<RM>(d, row);
-    const int64_t mo = pr * d.ldm + col;
-    if (!AL) x.nv = min(4, c_hi - col);
-    if (AL || m_load_inside<RM>(d, row, pr, col, 4)) {
+    const int cc = col - tail_back<4, AL>(col, c_hi);
+    const int64_t mo = pr * d.ldm + cc;
+    const float* ep = d.err_in + pr * d.lde_in + cc;
+    if (AL || c_hi >= 4) {
       if constexpr (DT == DT_F32) x.m = ld_f4<AL>((const float*)d.M + mo);
       else x.m = ld_h4<AL>((const uint16_t*)d.M + mo);
+      x.e = d.err_in ? ld_f4<AL>(ep) : make_float4(-0.f, -0.f, -0.f, -0.f);
     } else {
-      float a[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) a[j] = j < x.nv ? m_elem<DT>(d, mo + j) : -0.f;
-      if constexpr (DT == DT_F32) x.m = make_float4(a[0], a[1], a[2], a[3]);
-      else x.m = make_uint2(bf16_pack2(a[0], a[1]), bf16_pack2(a[2], a[3]));
-    }
-    const float* ep = d.err_in + pr * d.lde_in + col;
-    if (!d.err_in) {
-      x.e = make_float4(-0.f, -0.f, -0.f, -0.f);
-    } else if (AL || x.nv == 4) {
-      x.e = ld_f4<AL>(ep);
-    } else {
+      // rows of fewer than four columns: the one chunk starts at column 0
+      uint32_t m[4];
       float e[4];
-      err_tail<4>(ep, x.nv, e);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        m[j] = j < c_hi ? m_bits<DT>(d, mo + j) : 0u;
+        e[j] = d.err_in && j < c_hi ? ep[j] : (j < c_hi ? -0.f : 0.f);
+      }
+      if constexpr (DT == DT_F32)
+        x.m = make_float4(__uint_as_float(m[0]), __uint_as_float(m[1]), __uint_as_float(m[2]),
+                          __uint_as_float(m[3]));
+      else
+        x.m = make_uint2(m[0] | (m[1] << 16), m[2] | (m[3] << 16));
       x.e = make_float4(e[0], e[1], e[2], e[3]);
     }
   } else {
     x.m = neg_zero_m<DT>();
     x.e = make_float4(0.f, 0.f, 0.f, 0.f);
-    x.nv = 4;
   }
 }
 
 template <int DT, bool AL>
-__device__ __forceinline__ void chunk_value(const AChunk<DT, AL>& x, float a[4]) {
+__device__ __forceinline__ void chunk_value(const AChunk<DT>& x, int back, float (&a)[4]) {
   if constexpr (DT == DT_F32) {
     a[0] = x.m.x + x.e.x; a[1] = x.m.y + x.e.y; a[2] = x.m.z + x.e.z; a[3] = x.m.w + x.e.w;
   } else {
@@ -119,10 +132,7 @@ __device__ __forceinline__ void chunk_value(const AChunk<DT, AL>& x, float a[4])
     a[2] = bf16_lo(x.m.y) + x.e.z;
     a[3] = bf16_hi(x.m.y) + x.e.w;
   }
-  if (!AL) {
-#pragma unroll
-    for (int j = 1; j < 4; ++j) a[j] = j < x.nv ? a[j] : 0.f;
-  }
+  if (!AL && __any(back)) shift_back<4>(back, a);
 }
 
 // Q of a round's left product: the caller's warm start, row pitch r, in the

@@ -74,6 +74,16 @@ struct Desc {
   int32_t qr_cols;       // large-rank path: columns per block of the Q reduction (8 or 32)
 };
 
+// Whether one load of w elements of M at column c (< n) of row `row` (of m) may
+// be issued although it may pass the end of that row: a next row exists, and
+// its elements reach far enough, so the load stays inside the array (the
+// elements past the row's end are dropped).  Not where rows are listed: the
+// matrix row after a listed one need not be listed, and such a row is not read.
+__host__ __device__ inline bool m_load_may_pass(bool listed, int row, int m, int64_t ldm, int n, int c,
+                                                int w) {
+  return c + w <= n || (!listed && row + 1 < m && (int64_t)c + w <= ldm + n);
+}
+
 // Tiling of one matrix (host side).
 struct Tiling {
   int sp, p_cols, ng, grows, sq, q_rows, n_pad, m_pad, mr, qr_cols;

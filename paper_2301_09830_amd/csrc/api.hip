@@ -308,6 +308,7 @@ occ_status_t plan_batch(const occ_mat_t* mats, int count, int rank, int iters, u
     d.n_pad = t.n_pad;
     d.sp = t.sp;
     d.p_cols = t.p_cols;
+    d.p_sub = t.p_sub;
     d.ng = t.ng;
     d.grows = t.grows;
     d.sq = t.sq;
@@ -387,6 +388,12 @@ occ_status_t plan_batch(const occ_mat_t* mats, int count, int rank, int iters, u
     b.nt = b.nt && rows_nt(d, write_mhat);
   }
   return OCC_OK;
+}
+
+// The left product's form (the bf16 products have no use for shorter sums).
+template <int DT, int RP, int SA, bool X3, int TILES, bool RM = false>
+auto lp_kernel(bool sums) {
+  return sums && !X3 ? k_lp<DT, RP, SA, X3, TILES, RM, !X3> : k_lp<DT, RP, SA, X3, TILES, RM>;
 }
 
 unsigned grid_of(int64_t blocks) { return (unsigned)std::max<int64_t>(blocks, 1); }
@@ -474,24 +481,26 @@ occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish,
         bool pad_q = X3 || !saved;
         for (const Desc& dd : b.descs) pad_q = pad_q || !lp_reads_q<RP>(dd);
         if (pad_q) L("qpad", k_qpadl<RP>, b.blocks[K_QPAD]);
+        bool sums = false;   // fp32 sums of fewer K-steps than a block has
+        for (const Desc& dd : b.descs) sums = sums || dd.p_sub != INT32_MAX;
         for (int it = 0; it < b.iters; ++it) {
           if (!saved) {
             if (!b.descs[0].err_in)
-              LB("pass_p", k_lp<DT, RP, SA_MERR, X3, TILES_NONE>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p", lp_kernel<DT, RP, SA_MERR, X3, TILES_NONE>(sums), b.blocks[K_PASS_P], LPT);
             else if (whole)
-              LB("pass_p", k_lp<DT, RP, SA_MERR, X3, TILES_16>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p", lp_kernel<DT, RP, SA_MERR, X3, TILES_16>(sums), b.blocks[K_PASS_P], LPT);
             else
-              LB("pass_p", k_lp<DT, RP, SA_MERR, X3, TILES_4>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p", lp_kernel<DT, RP, SA_MERR, X3, TILES_4>(sums), b.blocks[K_PASS_P], LPT);
           } else if (it == 0) {
             if (whole)
-              LB("pass_p_first", k_lp<DT, RP, SA_MERR_SAVE, X3, TILES_16, RM>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p_first", lp_kernel<DT, RP, SA_MERR_SAVE, X3, TILES_16, RM>(sums), b.blocks[K_PASS_P], LPT);
             else
-              LB("pass_p_first", k_lp<DT, RP, SA_MERR_SAVE, X3, TILES_4, RM>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p_first", lp_kernel<DT, RP, SA_MERR_SAVE, X3, TILES_4, RM>(sums), b.blocks[K_PASS_P], LPT);
           } else {
             if (whole)
-              LB("pass_p_a", k_lp<DT_F32, RP, SA_SAVED, X3, TILES_16>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p_a", lp_kernel<DT_F32, RP, SA_SAVED, X3, TILES_16>(sums), b.blocks[K_PASS_P], LPT);
             else
-              LB("pass_p_a", k_lp<DT_F32, RP, SA_SAVED, X3, TILES_4>, b.blocks[K_PASS_P], LPT);
+              LB("pass_p_a", lp_kernel<DT_F32, RP, SA_SAVED, X3, TILES_4>(sums), b.blocks[K_PASS_P], LPT);
           }
           // the kernels named ...2 return at once unless the first pass asked
           // for a second; gram2 is left to apply where that has the same rows

@@ -493,7 +493,11 @@ __host__ __device__ __forceinline__ bool lp_reads_q(const Desc& d) {
 
 // RM (row-sparse step): M and err_prev rows through the row map; the stored A
 // (SA_MERR_SAVE writes it, SA_SAVED reads it) is compact.
-template <int DT, int RP, int SA, bool X3, int TILES, bool RM = false>
+// SUMS (fp32 form): sums of d.p_sub K-steps, added up in registers.  A form of
+// its own: the registers and the test cost the others 1-2 % (36501 x 448 rank
+// 128 step 382 -> 392 us), and sums added up in the stored partial cost more
+// where they are needed (5003 x 2047 rank 48 step: 160 us, through memory 166).
+template <int DT, int RP, int SA, bool X3, int TILES, bool RM = false, bool SUMS = false>
 __device__ __forceinline__ void lp_body(const Desc& d, int b,
                                         std::conditional_t<X3, LPXSmem<RP>, LPSmem<RP>>& sm,
                                         uint8_t* tiles) {
@@ -517,9 +521,25 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
   // device does not read one column stripe of every row at a time.
   const int ks0 = (int)(((int64_t)rt * 4) % nk);
 
-  f16v acc[NU];
+  f16v acc[NU], tot[SUMS ? NU : 1];
 #pragma unroll
-  for (int u = 0; u < NU; ++u) acc[u] = f16v{};
+  for (int u = 0; u < NU; ++u) {
+    acc[u] = f16v{};
+    if constexpr (SUMS) tot[u] = f16v{};
+  }
+  int sub = 0;
+  auto sum_up = [&]() {
+    if constexpr (SUMS) {
+      if (++sub == d.p_sub) {
+        sub = 0;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          tot[u] += acc[u];
+          acc[u] = f16v{};
+        }
+      }
+    }
+  };
 
   // Source and LDS slot of this thread's chunk x of the Q tile at column c.
   // fp32 form: qpad has n_pad (a multiple of 32) rows, so every K-step's Q
@@ -646,6 +666,7 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
       if constexpr (MREG) q_advance(it);
       if (it + 1 < nk) tile_issue(it + 1);
       mfma_step(a, it & 1);
+      sum_up();
       if (it + 1 < nk) {
 #pragma unroll
         for (int x = 0; x < QF4; ++x) *q_lds_ptr((it + 1) & 1, x) = qr[0][x];
@@ -667,6 +688,7 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
       for (int j = 0; j < 16; ++j) a[j] = rawa_val<DT, SA, 16>(ring[0], j);
       if constexpr (SA == SA_MERR_SAVE) a_store<16>(d, row, kc + 16 * g, c_hi, a);
       mfma_step(a, it & 1);
+      sum_up();
 #pragma unroll
       for (int x = 0; x < LP_DEPTH; ++x) ring[x] = ring[x + 1];
       if (it + LP_DEPTH + 1 < nk)
@@ -689,18 +711,18 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
     if (r < d.m) {
       float o[NU];
 #pragma unroll
-      for (int u = 0; u < NU; ++u) o[u] = acc[u][v];
+      for (int u = 0; u < NU; ++u) o[u] = SUMS ? tot[SUMS ? u : 0][v] + acc[u][v] : acc[u][v];
       st_f<NU>(dst + (int64_t)r * RP + NU * li, o);
     }
   }
 }
 
-template <int DT, int RP, int SA, bool X3, int TILES, bool RM = false>
+template <int DT, int RP, int SA, bool X3, int TILES, bool RM = false, bool SUMS = false>
 __global__ __launch_bounds__(lp_block_rows(RP, X3) / 32 * kWave) void k_lp(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) std::conditional_t<X3, LPXSmem<RP>, LPSmem<RP>> sm;
   __shared__ __attribute__((aligned(16))) uint8_t
       tiles[TILES ? lp_block_rows(RP, X3) / 32 * 2 * LPTile<DT, SA>::BYTES : 16];
-#define B_(d, b) lp_body<DT, RP, SA, X3, TILES, RM>(d, b, sm, tiles)
+#define B_(d, b) lp_body<DT, RP, SA, X3, TILES, RM, SUMS>(d, b, sm, tiles)
   OCC_DISPATCH(K_PASS_P, B_)
 #undef B_
 }

@@ -64,6 +64,7 @@ struct Desc {
   int32_t ldm, lde_in, lde_out, ldh;
   int32_t n_pad;
   int32_t sp, p_cols;    // left product: column splits and columns per split (multiple of 32)
+  int32_t p_sub;         // large-rank fp32 left product: K-steps per sum (see make_tiling)
   int32_t ng;            // Gram partials (one per block of the Gram kernel)
   int32_t grows;         // large-rank path: rows per block of the Gram kernel (multiple of 32)
   int32_t sq, q_rows;    // right product: row splits and rows per split
@@ -86,7 +87,7 @@ __host__ __device__ inline bool m_load_may_pass(bool listed, int row, int m, int
 
 // Tiling of one matrix (host side).
 struct Tiling {
-  int sp, p_cols, ng, grows, sq, q_rows, n_pad, m_pad, mr, qr_cols;
+  int sp, p_cols, p_sub, ng, grows, sq, q_rows, n_pad, m_pad, mr, qr_cols;
   int64_t blocks[K_NUM];
 };
 
@@ -246,19 +247,31 @@ inline Tiling make_tiling(int64_t m, int64_t n, int rp, double share = 1.0,
   while (min_cols > L_MIN_NARROW && row_tiles * sp_of(min_cols) < (int64_t)(share * (double)sl.p))
     min_cols /= 2;
   int64_t sp = sp_of(min_cols);
+  t.p_sub = INT32_MAX;
   if (share >= 1.0) {
     // One matrix alone: its blocks do equal work, so a grid a little over a
     // whole number of rounds of resident blocks takes a round more.  Of the
     // split counts up to that, take the one with the least rounds x (K-steps
     // of a block + L_PRE_STEPS).  5003 x 2047 fp32 at rank 48: 320 blocks of
-    // 8 K-steps on 256 slots 57 us, 240 blocks of 11 K-steps 45 us.
-    int64_t best = 0;
+    // 8 K-steps on 256 slots 57 us, 240 blocks of 11 K-steps 45 us.  Only
+    // counts whose last round is at least 7/8 full, or that this model puts at
+    // least 15 % lower: the blocks of a part-full round run faster than it
+    // counts (25600 x 2048 at rank 32, 76 -> 70: 400 blocks 121 us, 200 blocks
+    // on 256 slots 145 us; 20359 x 320 at rank 40, 22 -> 16: compress-only call
+    // of two rounds 227 -> 222 us).
+    // A block that takes more columns than before still forms its fp32 sums
+    // over as many as before (p_sub) and adds these up: in one sum the error
+    // against float64 grew by up to 45 %.
+    const int64_t steps0 = cdiv(cdiv(n, sp), L_KC);
+    int64_t best = 0, cost0 = 0;
     for (int64_t x = sp, top = sp; x >= 1; --x) {
-      const int64_t steps = cdiv(cdiv(n, x), L_KC);
-      const int64_t cost = cdiv(row_tiles * cdiv(n, steps * L_KC), sl.p) * (steps + L_PRE_STEPS);
-      if (x == top || cost < best) {
+      const int64_t steps = cdiv(cdiv(n, x), L_KC), blocks = row_tiles * cdiv(n, steps * L_KC);
+      const int64_t rounds = cdiv(blocks, sl.p), cost = rounds * (steps + L_PRE_STEPS);
+      if (x == top) cost0 = cost;
+      if (x == top || (cost < best && (8 * blocks >= 7 * rounds * sl.p || 20 * cost <= 17 * cost0))) {
         best = cost;
         sp = x;
+        t.p_sub = steps > steps0 ? (int)steps0 : INT32_MAX;
       }
     }
   }

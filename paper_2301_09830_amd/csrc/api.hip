@@ -960,16 +960,20 @@ occ_status_t occ_err_update(const void* M, int m_dtype, int64_t m, int64_t n, in
   d.err_out = err_new;
   d.lde_out = (int32_t)lde_new;
   const uint32_t cpr = (uint32_t)cdiv(n, 4);
-  const unsigned grid = (unsigned)std::min<int64_t>(cdiv(m * cpr, kBlock * EU_UNROLL), 16384);
+  const bool small = m * cpr <= EU_SMALL;
+  const unsigned grid = (unsigned)std::min<int64_t>(cdiv(m * cpr, kBlock * (small ? 1 : 4)), 16384);
   const bool nt = aligned(err_new, 64) && lde_new % 16 == 0;
   hipStream_t s = (hipStream_t)stream;
   return launch("err_update", s, [&] {
     with_bool(nt, [&](auto NTc) {
-      constexpr bool NT = decltype(NTc)::value;
-      if (m_dtype == OCC_BF16)
-        hipLaunchKernelGGL((k_err_update<DT_BF16, NT>), dim3(grid), dim3(kBlock), 0, s, d, cpr);
-      else
-        hipLaunchKernelGGL((k_err_update<DT_F32, NT>), dim3(grid), dim3(kBlock), 0, s, d, cpr);
+      with_bool(small, [&](auto Sc) {
+        constexpr bool NT = decltype(NTc)::value;
+        constexpr int U = decltype(Sc)::value ? 1 : 4;
+        if (m_dtype == OCC_BF16)
+          hipLaunchKernelGGL((k_err_update<DT_BF16, NT, U>), dim3(grid), dim3(kBlock), 0, s, d, cpr);
+        else
+          hipLaunchKernelGGL((k_err_update<DT_F32, NT, U>), dim3(grid), dim3(kBlock), 0, s, d, cpr);
+      });
     });
   });
 }

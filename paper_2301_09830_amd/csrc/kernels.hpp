@@ -122,15 +122,6 @@ __device__ __forceinline__ void store_f4(float* o, float a, float b, float c, fl
   else *(f4u_t*)o = f4u_t{a, b, c, e};
 }
 
-// Single element of A (column bound n).
-template <int DT>
-__device__ __forceinline__ float load_a1(const Desc& d, int row, int col) {
-  if (row >= d.m || col >= d.n) return 0.f;
-  float v = m_elem<DT>(d, (int64_t)row * d.ldm + col);
-  if (d.err_in) v = v + d.err_in[(int64_t)row * d.lde_in + col];
-  return v;
-}
-
 // Block -> matrix lookup for batched launches: the last matrix whose first
 // block of this kernel kind is <= b.
 __device__ __forceinline__ int find_matrix(const Desc* __restrict__ table, int count, int kind,
@@ -331,50 +322,75 @@ __global__ __launch_bounds__(kBlock) void k_qredl(OCC_KARGS) {
 // Stand-alone error update: err_new = (M + err_prev) - M_hat, elementwise,
 // same operation order as the fused pass.  Bound by memory (s_M + 12 bytes
 // an element); one element per thread and a 64-bit division per element ran
-// at 3.4 TB/s.  A thread takes EU_UNROLL chunks of four columns, all of
-// their loads in flight at once; chunk q of the matrix is row q / cpr,
-// columns 4 (q % cpr) .. + 3 (cpr chunks a row, the last one possibly short).
-// 8192 x 4096 bf16: 139 -> 71 us.
+// at 3.4 TB/s.  A thread takes U chunks of four columns, all of their loads
+// in flight at once; chunk q of the matrix is row q / cpr, columns
+// 4 (q % cpr) .. + 3 (cpr chunks a row).  The last chunk of a row may be short:
+// it is loaded from as many columns to the left as it lacks, in vectors like
+// the others, and stored element by element.
+// 8192 x 4096 bf16: 139 -> 70 us.
 // ---------------------------------------------------------------------------
-constexpr int EU_UNROLL = 4;
+// Chunks per thread: four, and one up to 2^19 chunks, where fewer threads leave
+// compute units without a block (in place, four / two / one chunks, and one
+// element per thread: 1303 x 161 fp32 3.8 / 3.1 / 2.7 / 2.6 us, 1000 x 1001 bf16
+// 4.6 / 3.8 / 3.7 / 4.9, 4096 x 1024 fp32 11.0 / 11.4 / 11.5 / 14.5, 8192 x 4096
+// fp32 82 / 93 / 91 / 114).
+constexpr int64_t EU_SMALL = (int64_t)1 << 19;
 
-template <int DT, bool NT>
+template <int DT, bool NT, int U>
 __global__ __launch_bounds__(kBlock) void k_err_update(Desc d, uint32_t cpr) {
   const int64_t total = (int64_t)d.m * cpr;
-  const int64_t step = (int64_t)gridDim.x * (kBlock * EU_UNROLL);
-  for (int64_t q0 = (int64_t)blockIdx.x * (kBlock * EU_UNROLL) + threadIdx.x; q0 < total; q0 += step) {
-    float4 m4[EU_UNROLL], e4[EU_UNROLL], h4[EU_UNROLL];
-    int row[EU_UNROLL], col[EU_UNROLL];
+  const int64_t step = (int64_t)gridDim.x * (kBlock * U);
+  for (int64_t q0 = (int64_t)blockIdx.x * (kBlock * U) + threadIdx.x; q0 < total; q0 += step) {
+    float4 m4[U], e4[U], h4[U];
+    int row[U], col[U];
 #pragma unroll
-    for (int u = 0; u < EU_UNROLL; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int64_t q = q0 + kBlock * u;
       row[u] = d.m;
       if (q >= total) continue;
       // 32-bit division where it is enough
       row[u] = total <= 0xffffffffll ? (int)((uint32_t)q / cpr) : (int)(q / cpr);
       col[u] = 4 * (int)(q - (int64_t)row[u] * cpr);
-      if (d.n - col[u] < 4) continue;   // (col + 4 may pass 2^31)
-      const int64_t mo = (int64_t)row[u] * d.ldm + col[u];
+      const int c = min(col[u], d.n - 4);
+      const int64_t mo = (int64_t)row[u] * d.ldm + c;
+      if (d.n < 4) {
+        // rows narrower than a chunk: their elements in the last places
+        float m[4], e[4], h[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          m[j] = c + j >= 0 ? m_elem<DT>(d, mo + j) : 0.f;
+          e[j] = d.err_in && c + j >= 0 ? d.err_in[(int64_t)row[u] * d.lde_in + c + j] : -0.f;
+          h[j] = c + j >= 0 ? d.Mhat[(int64_t)row[u] * d.ldh + c + j] : 0.f;
+        }
+        m4[u] = make_float4(m[0], m[1], m[2], m[3]);
+        e4[u] = make_float4(e[0], e[1], e[2], e[3]);
+        h4[u] = make_float4(h[0], h[1], h[2], h[3]);
+        continue;
+      }
       if constexpr (DT == DT_F32) {
         m4[u] = ld_f4<false>((const float*)d.M + mo);
       } else {
         const uint2 w = ld_h4<false>((const uint16_t*)d.M + mo);
         m4[u] = make_float4(bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y));
       }
-      e4[u] = d.err_in ? ld_f4<false>(d.err_in + (int64_t)row[u] * d.lde_in + col[u])
+      e4[u] = d.err_in ? ld_f4<false>(d.err_in + (int64_t)row[u] * d.lde_in + c)
                        : make_float4(-0.f, -0.f, -0.f, -0.f);
-      h4[u] = ld_f4<false>(d.Mhat + (int64_t)row[u] * d.ldh + col[u]);
+      h4[u] = ld_f4<false>(d.Mhat + (int64_t)row[u] * d.ldh + c);
     }
 #pragma unroll
-    for (int u = 0; u < EU_UNROLL; ++u) {
+    for (int u = 0; u < U; ++u) {
       if (row[u] >= d.m) continue;
       float* o = d.err_out + (int64_t)row[u] * d.lde_out + col[u];
-      if (d.n - col[u] >= 4) {
-        store_f4<NT>(o, (m4[u].x + e4[u].x) - h4[u].x, (m4[u].y + e4[u].y) - h4[u].y,
-                     (m4[u].z + e4[u].z) - h4[u].z, (m4[u].w + e4[u].w) - h4[u].w);
+      const int left = d.n - col[u];   // columns of the row from here
+      const float v[4] = {(m4[u].x + e4[u].x) - h4[u].x, (m4[u].y + e4[u].y) - h4[u].y,
+                          (m4[u].z + e4[u].z) - h4[u].z, (m4[u].w + e4[u].w) - h4[u].w};
+      if (left >= 4) {
+        store_f4<NT>(o, v[0], v[1], v[2], v[3]);
       } else {
-        for (int j = 0; j < d.n - col[u]; ++j)
-          o[j] = load_a1<DT>(d, row[u], col[u] + j) - d.Mhat[(int64_t)row[u] * d.ldh + col[u] + j];
+        // v[4 - left] is the first of the chunk's own columns
+        o[0] = left == 3 ? v[1] : (left == 2 ? v[2] : v[3]);
+        if (left > 1) o[1] = left == 3 ? v[2] : v[3];
+        if (left > 2) o[2] = v[3];
       }
     }
   }

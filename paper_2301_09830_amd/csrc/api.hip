@@ -390,6 +390,16 @@ occ_status_t plan_batch(const occ_mat_t* mats, int count, int rank, int iters, u
   return OCC_OK;
 }
 
+// The rank <= 16 left product's form (without tiles, any pitch).
+template <int DT, bool VEC, int RP, bool RM>
+auto pm_kernel(bool narrow, bool q16, bool padded) {
+  constexpr bool T = VEC && !RM;
+  constexpr int Q0 = T ? PM_Q_PADDED : PM_Q_PITCH, Q4 = T ? PM_Q_4 : PM_Q_PITCH;
+  if (T && !q16) return narrow ? k_pm<DT, VEC, RP, RM, true, Q4> : k_pm<DT, VEC, RP, RM, false, Q4>;
+  if (T && padded) return narrow ? k_pm<DT, VEC, RP, RM, true, Q0> : k_pm<DT, VEC, RP, RM, false, Q0>;
+  return narrow ? k_pm<DT, VEC, RP, RM, true, PM_Q_PITCH> : k_pm<DT, VEC, RP, RM, false, PM_Q_PITCH>;
+}
+
 // The left product's form (the bf16 products have no use for shorter sums).
 template <int DT, int RP, int SA, bool X3, int TILES, bool RM = false>
 auto lp_kernel(bool sums) {
@@ -442,10 +452,10 @@ occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish,
             const int first = it == 0;
             bool narrow = false;   // a matrix with fewer 32-column K-steps than waves
             for (const Desc& dd : b.descs) narrow = narrow || pm_waves_per_rb(dd.n) < PM_WAVES;
-            if (narrow)
-              LB("pass_p", k_pm<DT, VEC, RP, RM, true>, b.blocks[K_PASS_P], PM_THREADS, first);
-            else
-              LB("pass_p", k_pm<DT, VEC, RP, RM>, b.blocks[K_PASS_P], PM_THREADS, first);
+            bool q16 = true;       // every Q on 16 bytes
+            for (const Desc& dd : b.descs) q16 = q16 && (!first || aligned(dd.Q, 16));
+            const bool padded = !first || b.descs[0].r == RP;
+            LB("pass_p", pm_kernel<DT, VEC, RP, RM>(narrow, q16, padded), b.blocks[K_PASS_P], PM_THREADS, first);
             // T of each matrix (first `count` blocks) beside Q' = A^T P
             LB("pass_q", k_qm<DT, VEC, RP, RM>, count + b.blocks[K_PASS_Q], QM_THREADS, flags);
             L("q_finish", k_qfin16<RP>, b.blocks[K_QRED] + b.blocks[K_APPLY],

@@ -245,14 +245,26 @@ union PMSmem {
 typedef __attribute__((address_space(1))) void gvoid_t;
 typedef __attribute__((address_space(3))) void lvoid_t;
 
-// load instructions pm_tile_issue issues per K-step (the same in every wave)
-template <int DT, int RP>
-constexpr int pm_tile_loads() { return 4 + (DT == DT_BF16 ? 2 : 4) + (32 * RP * 4 + 1023) / 1024; }
+// How the left product takes its Q: with the padded rank as its pitch (the
+// padded copy, or a caller's Q of that rank), with any pitch, or with any pitch
+// and in 4-byte pieces (tiles, a caller's Q off 16 bytes: a view into a flat
+// buffer).  Separate kernels: the pitch and the ranks past r cost a wave's
+// chain 3-4 % where few row blocks make it the whole time (256 x 4096 rank 16
+// fp32 compress 35.8 us with the pitch known, 36.9 without), and a Q off 16
+// bytes cost the tiles (4096 x 2048 rank 12 fp32 step 67 -> 62.6 us).
+enum { PM_Q_PADDED = 0, PM_Q_PITCH = 1, PM_Q_4 = 2 };
+
+// load instructions pm_tile_issue issues per K-step (the same in every wave);
+// Q4: Q in 4-byte pieces
+template <int DT, int RP, bool Q4>
+constexpr int pm_tile_loads() {
+  return 4 + (DT == DT_BF16 ? 2 : 4) + (Q4 ? RP / 2 : (32 * RP * 4 + 1023) / 1024);
+}
 
 // K-step columns [c0, c0 + 32) of the block's 32 rows of err and M, and Q
 // rows c0 .. c0+31, into `dst` (rows past m repeat row m-1; their results
 // are never stored).
-template <int DT, int RP>
+template <int DT, int RP, bool Q4>
 __device__ __forceinline__ void pm_tile_issue(const Desc& d, const QSrc& qs, int row0, int c0,
                                               uint8_t* dst) {
   const int lane = threadIdx.x & 63;
@@ -286,11 +298,20 @@ __device__ __forceinline__ void pm_tile_issue(const Desc& d, const QSrc& qs, int
   }
   // Q rows c0 .. c0+31 (32 pitch floats, contiguous) as they are; every rank
   // of a padded rank takes the same number of load instructions
+  uint8_t* const qdst = dst + 4 * PM_ESLOT + pm_mbytes<DT>();
+  const float* const qsrc = qs.p + (int64_t)c0 * qs.pitch;
+  if constexpr (Q4) {
 #pragma unroll
-  for (int q = 0; q < (32 * RP * 4 + 1023) / 1024; ++q)
-    if (1024 * q + 16 * lane < 32 * 4 * qs.pitch)
-      __builtin_amdgcn_global_load_lds((gvoid_t*)(qs.p + (int64_t)c0 * qs.pitch + 256 * q + 4 * lane),
-                                       (lvoid_t*)(dst + 4 * PM_ESLOT + pm_mbytes<DT>() + 1024 * q), 16, 0, 0);
+    for (int q = 0; q < RP / 2; ++q)
+      __builtin_amdgcn_global_load_lds((gvoid_t*)(qsrc + min(64 * q + lane, 32 * qs.pitch - 1)),
+                                       (lvoid_t*)(qdst + 256 * q), 4, 0, 0);
+  } else {
+#pragma unroll
+    for (int q = 0; q < (32 * RP * 4 + 1023) / 1024; ++q)
+      if (1024 * q + 16 * lane < 32 * 4 * qs.pitch)
+        __builtin_amdgcn_global_load_lds((gvoid_t*)(qsrc + 256 * q + 4 * lane), (lvoid_t*)(qdst + 1024 * q),
+                                         16, 0, 0);
+  }
 }
 
 // RM (row-sparse step): rows through the row map, register loads only (the
@@ -300,7 +321,7 @@ __device__ __forceinline__ void pm_tile_issue(const Desc& d, const QSrc& qs, int
 // w % wk, w % wk + wk, ... (wk = pm_waves_per_rb(n) waves per row block).
 // The rows are stored to praw, and as doubles to sm.e.rows (zero past m)
 // for the Gram partial; ends with a barrier.
-template <int DT, bool VEC, int RP, bool RM, int WK, bool WIDE>
+template <int DT, bool VEC, int RP, bool RM, int WK, bool WIDE, int QM>
 __device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSmem<VEC && !RM>& sm) {
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 15, g = lane >> 4;
@@ -310,7 +331,8 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSme
   const int rb = grp * rpg + wave / wk, kw = wave % wk;
   const bool live = rb < row_blocks;
   const int row0 = rb * PM_ROWS;
-  const QSrc qs = q_src<RP>(d, first);
+  QSrc qs = q_src<RP>(d, first);
+  if (QM == PM_Q_PADDED) qs.pitch = RP;   // (known to the compiler)
 
   // Row blocks start their walk at staggered K-steps (and wrap around), so
   // that at any moment the device reads many column ranges instead of one
@@ -343,19 +365,20 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSme
       for (int j = 0; j < 8; ++j) acc[r] = mfma4(a[r][j], qv[j], acc[r]);
   };
 
-  // 16-byte aligned rows, whole 32-column K-steps, an error buffer and a
-  // 16-byte aligned Q: tiles through LDS (the condition is the same for the
-  // whole launch); otherwise loads straight into registers.
+  // 16-byte aligned rows, whole 32-column K-steps and an error buffer: tiles
+  // through LDS (the matrices of a batch decide each for itself); otherwise
+  // loads straight into registers.
   bool dma = false;
   if constexpr (VEC && !RM) {
-    dma = d.err_in != nullptr && (d.n & 31) == 0 && ((uintptr_t)qs.p & 15) == 0;
+    constexpr bool Q4 = QM == PM_Q_4;
+    dma = d.err_in != nullptr && (d.n & 31) == 0;
     if (dma) {
       // This wave's K-steps ks = kw + wk * it; step it lives in stage
       // it % PM_STAGES.  Per step: wait until only the steps issued after it
       // may be in flight, read its operands (inline ds_read, see above),
       // issue the step PM_STAGES - 1 ahead into the stage just freed, run the
       // products.
-      constexpr int NI = pm_tile_loads<DT, RP>();
+      constexpr int NI = pm_tile_loads<DT, RP, Q4>();
       constexpr int STAGE = pm_stage<DT>();
       static_assert(PM_STAGES <= 4 && 2 * NI <= 63, "vmcnt immediates");
       uint8_t* const tiles = sm.tile[wave][0];
@@ -363,7 +386,7 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSme
       const int nmine = live && kw < nk ? (nk - kw + wk - 1) / wk : 0;
 #pragma unroll
       for (int y = 0; y + 1 < PM_STAGES; ++y)
-        if (y < nmine) pm_tile_issue<DT, RP>(d, qs, row0, kcol(kw + wk * y) - 8 * g, tiles + y * STAGE);
+        if (y < nmine) pm_tile_issue<DT, RP, Q4>(d, qs, row0, kcol(kw + wk * y) - 8 * g, tiles + y * STAGE);
       int st = 0;
       for (int it = 0; it < nmine; ++it) {
         const int after = min(it + PM_STAGES - 2, nmine - 1) - it;
@@ -406,8 +429,8 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSme
         }
         if (it + PM_STAGES - 1 < nmine) {
           const int sn = st == 0 ? PM_STAGES - 1 : st - 1;
-          pm_tile_issue<DT, RP>(d, qs, row0, kcol(kw + wk * (it + PM_STAGES - 1)) - 8 * g,
-                                tiles + sn * STAGE);
+          pm_tile_issue<DT, RP, Q4>(d, qs, row0, kcol(kw + wk * (it + PM_STAGES - 1)) - 8 * g,
+                                    tiles + sn * STAGE);
         }
         st = st + 1 == PM_STAGES ? 0 : st + 1;
         Ch8<DT> x[PM_RB];
@@ -505,7 +528,7 @@ __device__ __forceinline__ void pm_rows(const Desc& d, int grp, int first, PMSme
 // (entry p accumulated by thread p, rows in order).  NARROW: some matrix of
 // the launch has fewer K-steps than waves (each matrix's row grouping is
 // chosen at run time); otherwise every matrix takes one row block at a time.
-template <int DT, bool VEC, int RP, bool RM = false, bool NARROW = false>
+template <int DT, bool VEC, int RP, bool RM, bool NARROW, int QM>
 __device__ __forceinline__ void pm_body(const Desc& d, int b, int first, PMSmem<VEC && !RM>& sm) {
   constexpr int NP = RP * (RP + 1) / 2;
   static_assert(NP <= PM_THREADS, "one Gram entry per thread");
@@ -517,9 +540,9 @@ __device__ __forceinline__ void pm_body(const Desc& d, int b, int first, PMSmem<
   const int row_groups = ((d.m + PM_ROWS - 1) / PM_ROWS + rpg - 1) / rpg;
   for (int grp = b; grp < row_groups; grp += d.ng) {
     if (grp != b) __syncthreads();   // the rows are read before the next tiles land there
-    if (!NARROW || wk == PM_WAVES) pm_rows<DT, VEC, RP, RM, PM_WAVES, !NARROW>(d, grp, first, sm);
-    else if (wk == 2) pm_rows<DT, VEC, RP, RM, 2, false>(d, grp, first, sm);
-    else pm_rows<DT, VEC, RP, RM, 1, false>(d, grp, first, sm);
+    if (!NARROW || wk == PM_WAVES) pm_rows<DT, VEC, RP, RM, PM_WAVES, !NARROW, QM>(d, grp, first, sm);
+    else if (wk == 2) pm_rows<DT, VEC, RP, RM, 2, false, QM>(d, grp, first, sm);
+    else pm_rows<DT, VEC, RP, RM, 1, false, QM>(d, grp, first, sm);
     const int nr = min(rpg * PM_ROWS, d.m - grp * rpg * PM_ROWS);
     if (t < NP)
       for (int i = 0; i < nr; ++i) gacc = fma(sm.e.rows[i * RP + gk], sm.e.rows[i * RP + gl], gacc);
@@ -527,10 +550,10 @@ __device__ __forceinline__ void pm_body(const Desc& d, int b, int first, PMSmem<
   if (t < NP) d.gpart[(int64_t)b * NP + t] = gacc;
 }
 
-template <int DT, bool VEC, int RP, bool RM = false, bool NARROW = false>
+template <int DT, bool VEC, int RP, bool RM, bool NARROW, int QM>
 __global__ __launch_bounds__(PM_THREADS) void k_pm(OCC_KARGS, int first) {
   __shared__ __attribute__((aligned(16))) PMSmem<VEC && !RM> sm;
-#define B_(d, b) pm_body<DT, VEC, RP, RM, NARROW>(d, b, first, sm)
+#define B_(d, b) pm_body<DT, VEC, RP, RM, NARROW, QM>(d, b, first, sm)
   OCC_DISPATCH(K_PASS_P, B_)
 #undef B_
 }

@@ -6,7 +6,8 @@ that are not padded, factors and outputs at any alignment.
 Against float64: an fp32 product of length r with unit-size terms is off by at
 most about r eps of the sum of |terms|, a split bf16 product by 2^-16 of it; a
 bf16 output adds 2^-9 of its value.  Bitwise equality with the fused step's
-M_hat is checked in test_gpu_properties.py.
+M_hat is checked in test_gpu_properties.py (64-column blocks) and
+test_gpu_decompress_fused.py (128-column blocks).
 """
 
 import pytest

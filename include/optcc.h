@@ -184,8 +184,10 @@ occ_status_t occ_step(const occ_mat_t* mat, int rank, int iters, unsigned flags,
 
 /* occ_step on `count` independent matrices (all of one pipeline stage,
  * Sec. 7), one kernel launch per pass for the whole batch.  All matrices
- * share rank, iters and M dtype.  Each result is bitwise equal to occ_step
- * on that matrix alone. */
+ * share rank, iters and M dtype.  At rank <= 16 each result is bitwise equal
+ * to occ_step on that matrix alone.  Above it the grids are planned for the
+ * whole batch: the fp32 sums of the two products may be split at other rows
+ * and columns than alone, and the results then agree to fp32 rounding. */
 occ_status_t occ_step_batched(const occ_mat_t* mats, int count, int rank, int iters,
                               unsigned flags, void* ws, size_t ws_bytes,
                               occ_stream_t stream);

@@ -411,7 +411,8 @@ unsigned grid_of(int64_t blocks) { return (unsigned)std::max<int64_t>(blocks, 1)
 // Enqueue the compression passes (and, with `finish`, the fused
 // reconstruction/residual pass) for a planned batch; numeric flags go to
 // `flags`.  RM: row-sparse step (rows of M, err and M_hat through each
-// descriptor's row map), on the register-load forms of the streaming kernels.
+// descriptor's row map), at rank <= 16 on the register-load forms of the
+// streaming kernels, above it through the tiles like the dense step.
 template <bool RM>
 occ_status_t run_batch_t(const Batch& b, void* ws, uint32_t* flags, bool finish, bool write_mhat,
                          hipStream_t s) {
@@ -585,8 +586,9 @@ occ_status_t run_batch(const Batch& b, void* ws, uint32_t* flags, bool finish, b
 
 namespace {
 
-// Stand-alone decompression: M_hat = P Q^T with the reconstruction kernels of
-// the fused step (SRC 1: factors from the caller's P and Q).
+// Stand-alone decompression: M_hat = P Q^T from the caller's factors, up to
+// rank 16 with the reconstruction kernel of the fused step (SRC 1), above it
+// with a kernel of its own that runs the same products (k_dec).
 template <bool OUTBF>
 occ_status_t decompress_impl(const float* P, const float* Q, int64_t m, int64_t n, int rank,
                              bool split, void* M_hat, int64_t ldh, hipStream_t s) {
@@ -617,14 +619,14 @@ occ_status_t decompress_impl(const float* P, const float* Q, int64_t m, int64_t 
       with_bool(nt, [&](auto NTc) {
         constexpr bool NT = decltype(NTc)::value;
         if constexpr (RP > kFusedMaxRank) {
-          // one round of resident blocks, each walking as many row tiles as
-          // that takes (two rounds where the column tiles alone exceed one)
-          // (an output whose blocks fill at most half of that takes smaller
-          // ones: a wave's products are its longest serial chain, and a block
-          // of half the columns halves it: 1024 x 512 rank 128 fp32 products
-          // 21.4 -> 8.7 us, 2048 x 1024 rank 100 bf16 out 13.6 -> 9.7 us, 3001 x 777
-          // rank 48 12.2 -> 11.3 us; larger outputs read P half as often in whole
-          // blocks)
+          // one round of resident blocks on 256 compute units, each walking as
+          // many row tiles as that takes (two rounds where the column tiles
+          // alone exceed one).  An output whose blocks fill at most half of
+          // that takes smaller ones: a wave's products are its longest serial
+          // chain, and a block of half the columns halves it (1024 x 512 rank
+          // 128 fp32 products 21.4 -> 8.7 us, 2048 x 1024 rank 100 bf16 out
+          // 13.6 -> 9.7 us, 3001 x 777 rank 48 12.2 -> 11.3 us); larger outputs
+          // read P half as often in whole blocks.
           const bool small = 2 * cdiv(n, DC_COLS) * cdiv(m, 32 * dc_waves(RP, DC_COLS)) <=
                              256 * dc_blocks_per_cu(RP, DC_COLS);
           auto go = [&](auto Cc) {

@@ -174,9 +174,10 @@ __device__ __forceinline__ int xcd_tile() {
 
 // gsum[k][l] = sum_b gpart[b][k][l] for k <= l (fixed order), zero below the
 // diagonal (the Gram partials hold the upper triangle only).  MODE 1: second
-// CholeskyQR pass, skipped unless the first pass asked for it.  A block takes GS_ENT entries; GS_SL threads per entry sum interleaved slices of
-// the partials with their loads issued in batches of 8, and the slices are
-// added in slice order.
+// CholeskyQR pass, skipped unless the first pass asked for it.  A block takes
+// GS_ENT entries; GS_SL threads per entry sum interleaved slices of the
+// partials with their loads issued in batches of 8, and the slices are added in
+// slice order.
 constexpr int GS_SL = 8;
 constexpr int GS_ENT = kBlock / GS_SL;
 

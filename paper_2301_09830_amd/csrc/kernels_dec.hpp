@@ -7,16 +7,17 @@
 // barrier per tile; without A to read they wait for the next P tile, and in
 // bf16 they stored 2 bytes a lane into 64-byte pieces of rows (16384 x 8192,
 // rank 128, bf16 out: 203 us for 268 MB).  Here a block stages 128 columns of
-// Q (64 for small outputs) in LDS once, and each wave then walks 32-row tiles by itself, with no
-// barrier: its P rows are loaded whole, two tiles ahead, and turned into the
-// B operands through the wave's own LDS tile (loading them in operand order
-// fetched every line four times), the 32-column tiles take their A
-// operands from the Q tile, and the results pass through the wave's LDS tile
-// to be stored as 256-byte pieces of rows, 16 bytes a lane.  The products run
+// Q (64 for small outputs) in LDS once, and each wave then walks 32-row tiles
+// by itself, with no barrier: its P rows are loaded whole, two tiles ahead, and
+// turned into the B operands through the wave's own LDS tile (loading them in
+// operand order fetched every line four times), the 32-column tiles take their
+// A operands from the Q tile, and the results pass through the wave's LDS tile
+// to be stored as 256-byte pieces of rows (128 in bf16 from 64 columns), 16
+// bytes a lane.  The products run
 // transposed (M_hat^T = Q P^T), so that a lane holds four consecutive columns
 // of a row and writes them to LDS at once.  The common tile has no bounds
 // tests: one at every load made each load wait for the one before.
-// 16384 x 8192, rank 128, bf16 out: 203 -> 113 us; 8192 x 4096, rank 64, fp32
+// 16384 x 8192, rank 128, bf16 out: 203 -> 112-119 us; 8192 x 4096, rank 64, fp32
 // out: 57 -> 31 us (4.4 TB/s).  At rank 128 neither the products nor the
 // stores bound the pass alone (a third of the products takes 14 % less time,
 // none of the stores 19 % less): two waves per SIMD overlap them only partly.
@@ -30,11 +31,12 @@
 namespace occ {
 
 constexpr int DC_COLS = 128;               // columns per block
-constexpr int DC_COLS_SMALL = 64;          // the same where the blocks would fill less than half the chip
+constexpr int DC_COLS_SMALL = 64;          // the same where the blocks would fill at most half the chip
 // waves per block: at rank 128 a tile of DC_COLS columns of Q leaves room for
 // one block per compute unit, which then holds eight waves
 __host__ __device__ constexpr int dc_waves(int rp, int cols) { return rp >= 128 && cols == DC_COLS ? 8 : 4; }
-// blocks that one compute unit holds (LDS)
+// blocks that a compute unit is planned for (one where LDS holds no more; at
+// the smaller ranks LDS would hold three, but two fill the store stream)
 __host__ __device__ constexpr int dc_blocks_per_cu(int rp, int cols) { return rp >= 128 && cols == DC_COLS ? 1 : 2; }
 
 template <int RP, bool SPLIT, bool OUTBF, int COLS>

@@ -139,71 +139,59 @@ __device__ __forceinline__ void stu_f(float* p, const float* v) {
   }
 }
 
-// W consecutive elements of A (columns c..c+W-1 of one row) as raw loads,
-// converted only when used so that the loads stay in flight.  A chunk across
+// W consecutive elements of A = M + err_prev (columns c..c+W-1 of one row) as
+// raw loads, converted only when used so that the loads stay in flight: the
+// register form (TILES_NONE) of the compress-only products.  A chunk across
 // the end of the columns (or past the rows) holds the exact A values (0 out
 // of range) in e and -0 in m (x + -0 == x for every x).
-template <int DT, int SA, int W>
+template <int DT, int W>
 struct RawA {
-  static constexpr int MW = SA == SA_SAVED ? 1 : (DT == DT_BF16 ? (W >= 2 ? W / 2 : 1) : W);
+  static constexpr int MW = DT == DT_BF16 ? (W >= 2 ? W / 2 : 1) : W;
   uint32_t m[MW];
   float e[W];
 };
 
-template <int DT, int SA, int W, bool RM = false>
-__device__ __forceinline__ RawA<DT, SA, W> rawa_load(const Desc& d, int row, int c, int c_hi) {
-  RawA<DT, SA, W> x;
+template <int DT, int W>
+__device__ __forceinline__ RawA<DT, W> rawa_load(const Desc& d, int row, int c, int c_hi) {
+  RawA<DT, W> x;
+  const int64_t mo = (int64_t)row * d.ldm + c, eo = (int64_t)row * d.lde_in + c;
   if (row < d.m && c + W <= c_hi) {
-    // M and err_prev rows through the row map; the stored A is compact
-    const int64_t pr = SA == SA_SAVED ? (int64_t)row : prow<RM>(d, row);
-    if constexpr (SA == SA_SAVED) {
-      ldu_f<W>(d.err_out + pr * d.lde_out + c, x.e);
-      x.m[0] = 0u;
+    if constexpr (DT == DT_BF16) {
+      const uint16_t* mp = (const uint16_t*)d.M + mo;
+      if constexpr (W == 1) x.m[0] = (uint32_t)(*mp) << 16;
+      else ldu_h<W>(mp, x.m);
     } else {
-      if constexpr (DT == DT_BF16) {
-        const uint16_t* mp = (const uint16_t*)d.M + pr * d.ldm + c;
-        if constexpr (W == 1) x.m[0] = (uint32_t)(*mp) << 16;
-        else ldu_h<W>(mp, x.m);
-      } else {
-        float mv[W];
-        ldu_f<W>((const float*)d.M + pr * d.ldm + c, mv);
+      float mv[W];
+      ldu_f<W>((const float*)d.M + mo, mv);
 #pragma unroll
-        for (int j = 0; j < W; ++j) x.m[j] = __float_as_uint(mv[j]);
-      }
-      if (d.err_in) {
-        ldu_f<W>(d.err_in + pr * d.lde_in + c, x.e);
-      } else {
+      for (int j = 0; j < W; ++j) x.m[j] = __float_as_uint(mv[j]);
+    }
+    if (d.err_in) {
+      ldu_f<W>(d.err_in + eo, x.e);
+    } else {
 #pragma unroll
-        for (int j = 0; j < W; ++j) x.e[j] = -0.f;
-      }
+      for (int j = 0; j < W; ++j) x.e[j] = -0.f;
     }
   } else {
 #pragma unroll
     for (int j = 0; j < W; ++j) {
       float v = 0.f;
       if (row < d.m && c + j < c_hi) {
-        const int64_t pr = SA == SA_SAVED ? (int64_t)row : prow<RM>(d, row);
-        if constexpr (SA == SA_SAVED) {
-          v = d.err_out[pr * d.lde_out + c + j];
-        } else {
-          v = m_elem<DT>(d, pr * d.ldm + c + j);
-          if (d.err_in) v = v + d.err_in[pr * d.lde_in + c + j];
-        }
+        v = m_elem<DT>(d, mo + j);
+        if (d.err_in) v = v + d.err_in[eo + j];
       }
       x.e[j] = v;
     }
-    const uint32_t nz = (SA != SA_SAVED && DT == DT_BF16 && W >= 2) ? 0x80008000u : 0x80000000u;
+    const uint32_t nz = (DT == DT_BF16 && W >= 2) ? 0x80008000u : 0x80000000u;
 #pragma unroll
-    for (int w = 0; w < RawA<DT, SA, W>::MW; ++w) x.m[w] = nz;
+    for (int w = 0; w < RawA<DT, W>::MW; ++w) x.m[w] = nz;
   }
   return x;
 }
 
-template <int DT, int SA, int W>
-__device__ __forceinline__ float rawa_val(const RawA<DT, SA, W>& x, int j) {
-  if constexpr (SA == SA_SAVED) {
-    return x.e[j];
-  } else if constexpr (DT == DT_BF16) {
+template <int DT, int W>
+__device__ __forceinline__ float rawa_val(const RawA<DT, W>& x, int j) {
+  if constexpr (DT == DT_BF16) {
     if constexpr (W == 1) return __uint_as_float(x.m[0]) + x.e[0];
     else return ((j & 1) ? bf16_hi(x.m[j >> 1]) : bf16_lo(x.m[j >> 1])) + x.e[j];
   } else {
@@ -674,30 +662,28 @@ __device__ __forceinline__ void lp_body(const Desc& d, int b,
       __syncthreads();
     }
   } else {
-    RawA<DT, SA, 16> ring[LP_DEPTH + 1];
+    static_assert(SA == SA_MERR && !RM, "registers: compress-only calls");
+    RawA<DT, 16> ring[LP_DEPTH + 1];
 #pragma unroll
     for (int x = 0; x <= LP_DEPTH; ++x)
-      if (x < nk) ring[x] = rawa_load<DT, SA, 16, RM>(d, row, kcol_of(c_lo, ks0, x, nk) + 16 * g, c_hi);
+      if (x < nk) ring[x] = rawa_load<DT, 16>(d, row, kcol_of(c_lo, ks0, x, nk) + 16 * g, c_hi);
     __syncthreads();
 
-    int kc = kcol_of(c_lo, ks0, 0, nk);
     for (int it = 0; it < nk; ++it) {
       q_advance(it);
       float a[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) a[j] = rawa_val<DT, SA, 16>(ring[0], j);
-      if constexpr (SA == SA_MERR_SAVE) a_store<16>(d, row, kc + 16 * g, c_hi, a);
+      for (int j = 0; j < 16; ++j) a[j] = rawa_val<DT, 16>(ring[0], j);
       mfma_step(a, it & 1);
       sum_up();
 #pragma unroll
       for (int x = 0; x < LP_DEPTH; ++x) ring[x] = ring[x + 1];
       if (it + LP_DEPTH + 1 < nk)
-        ring[LP_DEPTH] = rawa_load<DT, SA, 16, RM>(d, row, kcol_of(c_lo, ks0, it + LP_DEPTH + 1, nk) + 16 * g, c_hi);
+        ring[LP_DEPTH] = rawa_load<DT, 16>(d, row, kcol_of(c_lo, ks0, it + LP_DEPTH + 1, nk) + 16 * g, c_hi);
       if (it + 1 < nk) {
         // slot 0 now holds K-step it + 1
 #pragma unroll
         for (int x = 0; x < QF4; ++x) *q_lds_ptr((it + 1) & 1, x) = qr[0][x];
-        kc = kcol_of(c_lo, ks0, it + 1, nk);
       }
       __syncthreads();
     }
@@ -732,8 +718,9 @@ __global__ __launch_bounds__(lp_block_rows(RP, X3) / 32 * kWave) void k_lp(OCC_K
 // fp64.  MODE 0: the rows are P (sum of the left product's column splits,
 // stored to praw).  MODE 1 (second CholeskyQR pass): the rows are the first
 // pass's P_hat, when the first pass asked for a second; where a block of
-// k_lapply has the rows of a Gram block it runs this itself (la_gram2).  Rows are staged in LDS as doubles, 32 at a time; the upper-triangle 16 x 16 tiles of G (ta <= tb) are shared out
-// over the four waves and accumulated on v_mfma_f64_16x16x4f64, four rows
+// k_lapply has the rows of a Gram block it runs this itself (la_gram2).  Rows
+// are staged in LDS as doubles, 32 at a time; the upper-triangle 16 x 16 tiles
+// of G (ta <= tb) are shared out over the four waves and accumulated on v_mfma_f64_16x16x4f64, four rows
 // per instruction: lane (q, li) supplies P[row 4s + q][16 ta + li] (A
 // operand) and P[row 4s + q][16 tb + li] (B operand) and ends with
 // G[16 ta + 4v + q][16 tb + li] in component v.  Only the upper tiles are
@@ -1337,7 +1324,7 @@ struct LQSmem {
   float p[2][L_QG][RP + 4];
 };
 
-template <int DT, int RP, int SA, bool RM = false>
+template <int DT, int RP>
 __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
   constexpr int NU = RP / 32, CPL = lq_cpl(RP), BC = lq_block_cols(RP);
   constexpr int PF = L_QG * RP / 4;   // float4s of one P_hat stage
@@ -1371,11 +1358,11 @@ __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
     if (t < PF && row < r_hi) pr[y] = *(const f4v*)(d.phat + (int64_t)row * RP + pk);
   }
   if (t < PF) *(f4v*)(&sm.p[0][pi][pk]) = pr[0];
-  RawA<DT, SA, CPL> cur[4], nxt[4];
+  RawA<DT, CPL> cur[4], nxt[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
     const int row = r_lo + 2 * ks + g;
-    cur[ks] = rawa_load<DT, SA, CPL, RM>(d, row < r_hi ? row : d.m, col, d.n);
+    cur[ks] = rawa_load<DT, CPL>(d, row < r_hi ? row : d.m, col, d.n);
   }
   __syncthreads();
 
@@ -1393,7 +1380,7 @@ __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         const int row = rn + 2 * ks + g;
-        nxt[ks] = rawa_load<DT, SA, CPL, RM>(d, row < r_hi ? row : d.m, col, d.n);
+        nxt[ks] = rawa_load<DT, CPL>(d, row < r_hi ? row : d.m, col, d.n);
       }
     }
 #pragma unroll
@@ -1402,7 +1389,7 @@ __device__ __forceinline__ void lq_body(const Desc& d, int b, LQSmem<RP>& sm) {
       ld_f<NU>(&sm.p[grp & 1][2 * ks + g][NU * li], bv);
 #pragma unroll
       for (int x = 0; x < CPL; ++x) {
-        const float a = rawa_val<DT, SA, CPL>(cur[ks], x);
+        const float a = rawa_val<DT, CPL>(cur[ks], x);
 #pragma unroll
         for (int u = 0; u < NU; ++u) acc[x][u] = mfma32(a, bv[u], acc[x][u]);
       }
@@ -1518,7 +1505,6 @@ __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* til
   const int col_tiles = (d.n + BC - 1) / BC;
   const int ct = b % col_tiles, s = b / col_tiles;
   const int cw = ct * BC + wave * 32 * CPL;
-  const int col = cw + CPL * li;
   const int r_lo = s * d.q_rows, r_hi = min(d.m, r_lo + d.q_rows);
   const int ngrp = (r_hi - r_lo + L_QG - 1) / L_QG;
   const int r_last = r_hi - 1;
@@ -1598,12 +1584,11 @@ __device__ __forceinline__ void lq_tiles_body(const Desc& d, int b, uint8_t* til
         st_f<NU>(d.qpart + ((int64_t)s * d.n + c) * RP + NU * li, o);
       }
     }
-  (void)col;
 }
 
-template <int DT, int RP, int SA, int TILES, bool RM = false>
+template <int DT, int RP, int SA, int TILES>
 __global__ __launch_bounds__(kBlock) void k_lq(OCC_KARGS) {
-  static_assert(!(TILES && RM), "the row map runs on the register form");
+  static_assert(TILES != TILES_NONE || SA == SA_MERR, "registers: compress-only calls");
   if constexpr (TILES != TILES_NONE) {
     static_assert(DT == DT_F32 && SA != SA_MERR_SAVE, "tiles hold fp32 arrays");
     __shared__ __attribute__((aligned(16))) uint8_t tiles[LQTile<RP, SA>::AST * LQTile<RP, SA>::STAGE];
@@ -1612,7 +1597,7 @@ __global__ __launch_bounds__(kBlock) void k_lq(OCC_KARGS) {
 #undef B_
   } else {
     __shared__ __attribute__((aligned(16))) LQSmem<RP> sm;
-#define B_(d, b) lq_body<DT, RP, SA, RM>(d, b, sm)
+#define B_(d, b) lq_body<DT, RP>(d, b, sm)
     OCC_DISPATCH_X(K_PASS_Q, B_)
 #undef B_
   }
@@ -1739,9 +1724,9 @@ __device__ __forceinline__ void lqx_tile_read(const uint8_t* src, int li, int g,
   }
 }
 
-template <int DT, int RP, int SA, int TILES, bool RM = false>
+template <int DT, int RP, int SA, int TILES>
 __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, uint8_t* tiles) {
-  static_assert(!(TILES && RM), "the row map runs on the register form");
+  static_assert(TILES != TILES_NONE || SA == SA_MERR, "registers: compress-only calls");
   constexpr int NU = RP / 32, CPL = lq_cpl(RP), BC = lq_block_cols(RP, true);
   constexpr int NW = lqx_waves(RP);
   constexpr int NLD = 2 * NU;                         // P tile load instructions per group
@@ -1774,12 +1759,12 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
                                        16, 0, 0);
     }
   };
-  auto a_fetch = [&](int grp, RawA<DT, SA, CPL>* x) {
+  auto a_fetch = [&](int grp, RawA<DT, CPL>* x) {
     const int r0 = r_lo + LQX_G * grp;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int row = r0 + 8 * g + e;
-      x[e] = rawa_load<DT, SA, CPL, RM>(d, row < r_hi ? row : d.m, col, d.n);
+      x[e] = rawa_load<DT, CPL>(d, row < r_hi ? row : d.m, col, d.n);
     }
   };
 
@@ -1888,7 +1873,7 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
       }
     }
   } else {
-    RawA<DT, SA, CPL> cur[8], nxt[8];
+    RawA<DT, CPL> cur[8], nxt[8];
     if (ngrp > 0) {
       p_issue(0, 0);
       a_fetch(0, cur);
@@ -1914,7 +1899,7 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
         bf16x8 bh, bl;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float v = rawa_val<DT, SA, CPL>(cur[e], x);
+          const float v = rawa_val<DT, CPL>(cur[e], x);
           const __bf16 hv = (__bf16)v;
           bh[e] = hv;
           bl[e] = (__bf16)(v - (float)hv);
@@ -1947,12 +1932,12 @@ __device__ __forceinline__ void lqx_body(const Desc& d, int b, LQXSmem<RP>& sm, 
   }
 }
 
-template <int DT, int RP, int SA, int TILES, bool RM = false>
+template <int DT, int RP, int SA, int TILES>
 __global__ __launch_bounds__(lqx_waves(RP) * kWave) void k_lqx(OCC_KARGS) {
   __shared__ __attribute__((aligned(16))) LQXSmem<RP> sm;
   __shared__ __attribute__((aligned(16)))
   uint8_t tiles[TILES ? lqx_waves(RP) * LQXTile<RP, SA>::AST * LQXTile<RP, SA>::BYTES : 16];
-#define B_(d, b) lqx_body<DT, RP, SA, TILES, RM>(d, b, sm, tiles)
+#define B_(d, b) lqx_body<DT, RP, SA, TILES>(d, b, sm, tiles)
   OCC_DISPATCH_X(K_PASS_Q, B_)
 #undef B_
 }

@@ -166,7 +166,9 @@ __host__ __device__ constexpr bool lm_lds_epilogue(int rp) { return rp == 64; }
 // Blocks of each large-rank streaming kernel that are resident on the
 // device at once (compute units x blocks per compute unit).  Grids are
 // sized in whole multiples of these: blocks of a pass do equal work, so a
-// grid of 1.33 rounds takes as long as 2.
+// grid of 1.33 rounds takes as long as 2.  They are those of the 16-byte tile
+// forms on a fused step; the 4-byte forms, whose blocks have the same LDS
+// tiles, and the compress-only ones are planned with the same counts.
 struct Slots {
   int64_t p = 1024, q = 1024, m = 1024;   // left product, right product, reconstruction
 };

@@ -205,10 +205,10 @@ def test_tiny_shapes(shape, rank):
 def test_unaligned_leading_dimension():
     w = Workload(92, "ldpad", ((130, 75),), "f32", 8, 2, 2, "gauss", std=1.0)
     res, _, _ = run_workload(w, 2, ld_pad=1)
-    assert_parity(res, "f32", "ld = n + 1 (scalar path)")
+    assert_parity(res, "f32", "ld = n + 1 (rows at element alignment)")
     wb = WORKLOADS[2].scaled([(130, 75)], rank=8)
     res, _, _ = run_workload(wb, 2, ld_pad=3)
-    assert_parity(res, "bf16", "bf16 ld = n + 3 (scalar path)")
+    assert_parity(res, "bf16", "bf16 ld = n + 3 (rows at element alignment)")
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -216,7 +216,7 @@ def test_unaligned_leading_dimension():
 @pytest.mark.parametrize("rank", [32, 64, 128])
 def test_large_rank_padded_rows(rank, ld_pad, dtype):
     """Rows of pitch n + 1 (a multiple of 4: 16-byte accesses, with a ragged
-    last piece of 3 columns) and n + 2 (element accesses) at padded ranks
+    last piece of 3 columns) and n + 2 (rows at element alignment) at padded ranks
     32-128, where the reconstruction stores straight from the MFMA layout
     (rank 32, 128, bf16) or through an LDS tile by rows (fp32 rank 64).  The
     padding columns of err and M_hat must never be written."""

@@ -586,20 +586,13 @@ occ_status_t run_batch(const Batch& b, void* ws, uint32_t* flags, bool finish, b
 
 namespace {
 
-// Stand-alone decompression: M_hat = P Q^T from the caller's factors, up to
-// rank 16 with the reconstruction kernel of the fused step (SRC 1), above it
-// with a kernel of its own that runs the same products (k_dec).
+constexpr int64_t kDecRows = (int64_t)1 << 30;   // rows of one decompression launch, at most
+
+// The launch for checked arguments and at most kDecRows rows.
 template <bool OUTBF>
-occ_status_t decompress_impl(const float* P, const float* Q, int64_t m, int64_t n, int rank,
+occ_status_t decompress_part(const float* P, const float* Q, int64_t m, int64_t n, int rank,
                              bool split, void* M_hat, int64_t ldh, hipStream_t s) {
-  OCC_TRY(check_shape(m, n, ldh));
-  if (rank < 1 || rank > OCC_MAX_RANK || rank > m || rank > n) return OCC_E_RANK;
-  if (!P || !Q || !M_hat) return OCC_E_NULL;
   const size_t es = OUTBF ? 2 : 4;
-  if (!aligned(P, 4) || !aligned(Q, 4) || !aligned(M_hat, es)) return OCC_E_ALIGN;
-  std::vector<Span> spans = {span2d(P, m, rank, rank, 4, false), span2d(Q, n, rank, rank, 4, false),
-                             span2d(M_hat, m, n, ldh, es, true)};
-  if (overlaps(spans)) return OCC_E_ALIAS;
   const int rp = padded_rank(rank);
   const Tiling t = make_tiling(m, n, rp);
   Desc d{};
@@ -653,6 +646,31 @@ occ_status_t decompress_impl(const float* P, const float* Q, int64_t m, int64_t 
     });
   });
   return st;
+}
+
+// Stand-alone decompression: M_hat = P Q^T from the caller's factors, up to
+// rank 16 with the reconstruction kernel of the fused step (SRC 1), above it
+// with a kernel of its own that runs the same products (k_dec).
+template <bool OUTBF>
+occ_status_t decompress_impl(const float* P, const float* Q, int64_t m, int64_t n, int rank,
+                             bool split, void* M_hat, int64_t ldh, hipStream_t s) {
+  OCC_TRY(check_shape(m, n, ldh));
+  if (rank < 1 || rank > OCC_MAX_RANK || rank > m || rank > n) return OCC_E_RANK;
+  if (!P || !Q || !M_hat) return OCC_E_NULL;
+  const size_t es = OUTBF ? 2 : 4;
+  if (!aligned(P, 4) || !aligned(Q, 4) || !aligned(M_hat, es)) return OCC_E_ALIGN;
+  std::vector<Span> spans = {span2d(P, m, rank, rank, 4, false), span2d(Q, n, rank, rank, 4, false),
+                             span2d(M_hat, m, n, ldh, es, true)};
+  if (overlaps(spans)) return OCC_E_ALIAS;
+  // The kernels form rows one tile or block past the last one as int, so a
+  // matrix of close to 2^31 rows goes in parts (its rows are independent).
+  if (m > kDecRows) {
+    for (int64_t r0 = 0; r0 < m; r0 += kDecRows)
+      OCC_TRY(decompress_part<OUTBF>(P + r0 * rank, Q, std::min(kDecRows, m - r0), n, rank, split,
+                                     (char*)M_hat + r0 * ldh * (int64_t)es, ldh, s));
+    return OCC_OK;
+  }
+  return decompress_part<OUTBF>(P, Q, m, n, rank, split, M_hat, ldh, s);
 }
 
 }  // namespace

@@ -56,19 +56,29 @@ struct DCShape {
 // Factor rows are read in float4s of consecutive ranks straight from the
 // caller's array.  Unless r is the padded rank, the last ones of a row run on
 // into the next rows, so the values from rank r on are dropped when used.  At
-// the end of the array (INSIDE false) a float4 that would leave it is taken
-// from the last four elements and shifted.  A bounds test at every float4 made
-// each load wait for the one before, and so did reading those rows element by
-// element, which every small output waited for: 512 x 512 rank 108, fp32
-// products 13.0 -> 9.9 us, split products 10.1 -> 6.9 us.
-template <bool INSIDE>
-__device__ __forceinline__ f4v dc_load4(const float* base, int64_t at, int64_t size) {
+// the end of the array (INSIDE false; `last` its last element) a float4 may not
+// leave it.  A bounds test at every float4 made each load wait for the one
+// before, and so did reading those rows element by element behind tests, which
+// every small output waited for.  In 64-column blocks (small outputs) such a
+// float4 is taken from the last four elements and shifted: 512 x 512 rank 108,
+// fp32 products 13.0 -> 9.9 us, split products 10.1 -> 6.9 us.  In 128-column
+// blocks its elements are loaded one by one without tests, the last one in the
+// place of those past it: the shifts' registers there cost every tile (8192 x
+// 4096 rank 64, fp32 products 47.4 against 46.9 us, rank 128 82.6 against 79.1).
+template <bool INSIDE, int COLS>
+__device__ __forceinline__ f4v dc_load4(const float* row, int k, const float* last) {
+  const float* const p = row + k;
   if constexpr (INSIDE) {
-    return *(const f4u_t*)(base + at);
+    return *(const f4u_t*)p;
+  } else if constexpr (COLS == DC_COLS) {
+    f4v v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = *(p + e < last ? p + e : last);
+    return v;
   } else {
-    const int64_t last = size - 4;     // (a factor above rank 16 holds hundreds of elements)
-    f4v v = *(const f4u_t*)(base + min(at, last));
-    const int sh = (int)min(max(at - last, (int64_t)0), (int64_t)4);
+    const float* const q = last - 3;   // (a factor above rank 16 holds hundreds of elements)
+    f4v v = *(const f4u_t*)(p < q ? p : q);
+    const int sh = p < q ? 0 : (int)min(p - q, (int64_t)4);
     v = sh & 1 ? f4v{v[1], v[2], v[3], 0.f} : v;
     v = sh & 2 ? f4v{v[2], v[3], 0.f, 0.f} : v;
     return sh & 4 ? f4v{0.f, 0.f, 0.f, 0.f} : v;
@@ -106,29 +116,27 @@ __global__ __launch_bounds__(dc_waves(RP, COLS) * kWave, RP >= 128 ? 2 : 3) void
   __shared__ __attribute__((aligned(16))) uint8_t smem[S::BYTES];
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 31, g = lane >> 5;
-  // m and n may be close to 2^31: rows past a block's or the matrix's last one
-  // are formed unsigned, and columns are compared by what is left of the row
-  const int col_tiles = (int)(((uint32_t)d.n + COLS - 1) / COLS);
+  const int col_tiles = (d.n + COLS - 1) / COLS;
   const int ct = (int)blockIdx.x % col_tiles, rb = (int)blockIdx.x / col_tiles;
   const int c0 = ct * COLS;
-  const uint32_t r_lo = (uint32_t)(rb * d.mr), r_hi = min((uint32_t)d.m, r_lo + (uint32_t)d.mr);
+  const int r_lo = rb * d.mr, r_hi = min(d.m, r_lo + d.mr);
 
   // P rows of one tile as loaded, whole rows side by side: float4 x of a lane
   // is float4 64 x + lane of the tile.
   f4v raw[NF];
-  auto p_load_as = [&](auto in, uint32_t row0) __attribute__((always_inline)) {
+  auto p_load_as = [&](auto in, int row0) __attribute__((always_inline)) {
 #pragma unroll
     for (int x = 0; x < NF; ++x) {
-      const int f = 64 * x + lane;
-      const uint32_t row = min(row0 + f / (RP / 4), (uint32_t)d.m - 1);
-      raw[x] = dc_load4<decltype(in)::value>(d.P, (int64_t)row * d.r + 4 * (f % (RP / 4)), (int64_t)d.m * d.r);
+      const int f = 64 * x + lane, row = min(row0 + f / (RP / 4), d.m - 1);
+      raw[x] = dc_load4<decltype(in)::value, COLS>(d.P + (int64_t)row * d.r, 4 * (f % (RP / 4)),
+                                                   d.P + (int64_t)d.m * d.r - 1);
     }
   };
-  auto p_load = [&](uint32_t row0) __attribute__((always_inline)) {
-    if (dc_inside((int64_t)row0 + 31, d.m, d.r, RP)) p_load_as(std::true_type{}, row0);
+  auto p_load = [&](int row0) __attribute__((always_inline)) {
+    if (dc_inside(row0 + 31, d.m, d.r, RP)) p_load_as(std::true_type{}, row0);
     else p_load_as(std::false_type{}, row0);
   };
-  uint32_t row0 = r_lo + 32 * wave;
+  int row0 = r_lo + 32 * wave;
   if (row0 < r_hi) p_load(row0);
 
   // Q columns c0 .. c0 + 127 into LDS (zero past n and r).  SPLIT: bf16 hi and
@@ -145,10 +153,11 @@ __global__ __launch_bounds__(dc_waves(RP, COLS) * kWave, RP >= 128 ? 2 : 3) void
 #pragma unroll
       for (int x = 0; x < QL; ++x) {
         const int f = threadIdx.x + NTH * x, c = f / (RP / 4), k = 4 * (f % (RP / 4));
-        q4[x] = dc_load4<decltype(in)::value>(d.Q, (int64_t)min(c0 + c, d.n - 1) * d.r + k, (int64_t)d.n * d.r);
+        q4[x] = dc_load4<decltype(in)::value, COLS>(d.Q + (int64_t)min(c0 + c, d.n - 1) * d.r, k,
+                                                    d.Q + (int64_t)d.n * d.r - 1);
       }
     };
-    if (dc_inside((int64_t)c0 + COLS - 1, d.n, d.r, RP)) q_load(std::true_type{});
+    if (dc_inside(c0 + COLS - 1, d.n, d.r, RP)) q_load(std::true_type{});
     else q_load(std::false_type{});
 #pragma unroll
     for (int x = 0; x < QL; ++x) {
@@ -311,7 +320,7 @@ __global__ __launch_bounds__(dc_waves(RP, COLS) * kWave, RP >= 128 ? 2 : 3) void
         if (row0 + 32 * NW < r_hi) p_operands();
         if (row0 + 64 * NW < r_hi) p_load(row0 + 64 * NW);
       }
-      if (row0 + 32 <= r_hi && d.n - c0 >= COLS) {
+      if (row0 + 32 <= r_hi && c0 + COLS <= d.n) {
         // the common tile, without tests
 #pragma unroll
         for (int x = 0; x < NX; ++x)
@@ -319,9 +328,9 @@ __global__ __launch_bounds__(dc_waves(RP, COLS) * kWave, RP >= 128 ? 2 : 3) void
       } else {
 #pragma unroll
         for (int x = 0; x < NX; ++x) {
-          const uint32_t row = row0 + RPI * x + rl;
+          const int row = row0 + RPI * x + rl;
           const int64_t off = (int64_t)row * d.ldh + col;
-          if (row < r_hi && d.n - col >= W) {
+          if (row < r_hi && col + W <= d.n) {
             dc_store16<OUTBF, NT>(d, off, ov[x]);
           } else if (row < r_hi) {
             const uint32_t w[4] = {ov[x].x, ov[x].y, ov[x].z, ov[x].w};

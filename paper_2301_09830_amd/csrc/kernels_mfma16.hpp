@@ -756,12 +756,10 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
   constexpr int NTILE = F_MHCOLS / 16;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int li = lane & 15, g = lane >> 4;
-  // m and n may be close to 2^31, so tests ask what is left of the block's
-  // rows and of the row instead of forming the row or column to come
-  const int col_tiles = (int)(((uint32_t)d.n + F_MHCOLS - 1) / F_MHCOLS);
+  const int col_tiles = (d.n + F_MHCOLS - 1) / F_MHCOLS;
   const int ct = b % col_tiles, rb = b / col_tiles;
   const int c0 = ct * F_MHCOLS;
-  const int r_lo = rb * d.mr, r_hi = d.mr < d.m - r_lo ? r_lo + d.mr : d.m;
+  const int r_lo = rb * d.mr, r_hi = min(d.m, r_lo + d.mr);
   const float* qs = (SRC == 0) ? d.qpad : d.Q;
   const float* ps = (SRC == 0) ? d.phat : d.P;
 
@@ -774,16 +772,15 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
   }
   const int cl = 4 * (lane % MX_LPR), rl = lane / MX_LPR;
   const int col = c0 + cl;
-  const bool vec_col = d.n - col >= 4;
+  const bool vec_col = col + 4 <= d.n;
   float* tile = sm.t[wave];
   // Without A to read, a group's P rows are its only loads: they come one
   // group ahead, so that the products and stores of the current group cover
   // their latency (with the 16-byte bf16 stores below, 8192 x 4096 rank 16
   // bf16 out: 31 -> 17.5 us).
   float pn[S];
-  int r0 = r_lo + 16 * wave;
-  if (!WRITE_ERR) factor_load<RP, SRC>(ps, d.r, r0 + li, r_hi - r0 > li, S * g, pn);
-  for (int left = r_hi - r0; left > 0; left -= F_MHGROUP, r0 = (int)((uint32_t)r0 + F_MHGROUP)) {
+  if (!WRITE_ERR) factor_load<RP, SRC>(ps, d.r, r_lo + 16 * wave + li, r_lo + 16 * wave + li < r_hi, S * g, pn);
+  for (int r0 = r_lo + 16 * wave; r0 < r_hi; r0 += F_MHGROUP) {
     AChunk<DT> x[MX_NCH];
     if (WRITE_ERR) {
 #pragma unroll
@@ -800,7 +797,8 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
     } else {
 #pragma unroll
       for (int s = 0; s < S; ++s) pb[s] = pn[s];
-      factor_load<RP, SRC>(ps, d.r, (int)((uint32_t)rowb + F_MHGROUP), left - li > F_MHGROUP, S * g, pn);
+      const int rown = rowb + F_MHGROUP;
+      factor_load<RP, SRC>(ps, d.r, rown, rown < r_hi, S * g, pn);
     }
 #pragma unroll
     for (int t = 0; t < NTILE; ++t) {
@@ -825,7 +823,7 @@ __device__ __forceinline__ void mh16_body(const Desc& d, int b, MXSmem& sm) {
         uint16_t* o = (uint16_t*)d.Mhat + (int64_t)row * d.ldh + colb;
         const uint32_t w[4] = {bf16_pack2(a.x, a.y), bf16_pack2(a.z, a.w), bf16_pack2(c.x, c.y),
                                bf16_pack2(c.z, c.w)};
-        if (d.n - colb >= 8) {
+        if (colb + 8 <= d.n) {
           typedef uint32_t nu4 __attribute__((ext_vector_type(4)));
           if (NT) __builtin_nontemporal_store(nu4{w[0], w[1], w[2], w[3]}, (nu4*)o);
           else *(u4h_t*)o = u4h_t{w[0], w[1], w[2], w[3]};

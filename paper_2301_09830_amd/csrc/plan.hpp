@@ -198,15 +198,16 @@ inline Tiling make_tiling(int64_t m, int64_t n, int rp, double share = 1.0,
     // block forming T run in one round
     const int64_t col_tiles = cdiv(n, F_QCOLS);
     // splits of about 64 rows (m / 64 of them, rounded up), of 128 where that
-    // still leaves 32 of them, and of 32 while the whole grid stays within 64
-    // blocks: a block's sums over its waves and its partial cost as much as
+    // still leaves 32 of them, and of 32 at padded rank 4 (whose partials are the
+    // smallest) while the whole grid stays within 64 blocks: a block's sums over its waves and its partial cost as much as
     // several K-steps, and every split is read again by the finishing kernel
     // (4096 x 1024 bf16 rank 8: 63 splits 32.4 us a step, 32 splits 31.2 us;
     // 1024 x 1024 fp32 rank 4: 32 splits 24.3, 16 splits 23.8, 8 splits 25.2;
-    // 256 x 256 rank 4, two rounds: 4 splits 25.8, 8 splits 25.0; 256 x 4096
-    // rank 8 compress, 32 column tiles: 4 splits 30.5, 8 splits 31.6)
+    // 256 x 256, two rounds, rank 4: 4 splits 25.8, 8 splits 25.0, rank 8 28.7 and
+    // 28.6; 256 x 4096 rank 8 compress, 32 column tiles: 4 splits 30.5, 8 splits
+    // 31.6; 2642 x 64 rank 13, two rounds: 32 splits 42.1, 64 splits 44.1)
     const int64_t by_rows = std::min(cdiv(m, 64), std::max<int64_t>(32, cdiv(m, 128)));
-    const int64_t few = std::min(64 / col_tiles, cdiv(m, 32));
+    const int64_t few = rp == 4 ? std::min<int64_t>(16, std::min(64 / col_tiles, cdiv(m, 32))) : 0;
     const int64_t sq = clamp64((F_QBLOCKS - 1) / col_tiles, 1, std::max(by_rows, few));
     t.q_rows = (int)round_up(cdiv(m, sq), 4);
     t.sq = (int)cdiv(m, t.q_rows);

@@ -1,7 +1,8 @@
 """Row splits of the rank <= 16 right product, from the plan compiled with the
-host compiler: a small grid keeps splits of 32 rows (few long ones make the
-whole call wait), a grid of many column tiles does not get more splits for it,
-and the blocks of one matrix never exceed one round.
+host compiler: at padded rank 4 a small grid keeps splits of 32 rows (few long
+ones make the whole call wait), a grid of many column tiles or a higher rank
+does not get more splits for it, and the blocks of one matrix never exceed one
+round.
 """
 
 import os
@@ -37,7 +38,8 @@ def test_splits_of_small_and_wide_grids(tmp_path):
     seen = {}
     for line in subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout.split("\n")[:-1]:
         rp, m, n, sq, q_rows = map(int, line.split())
-        seen[m, n] = sq
+        seen[rp, m, n] = sq
         assert sq * q_rows >= m and -(-n // 128) * sq <= 511
-    assert seen[128, 128] == 4 and seen[256, 256] == 8 and seen[512, 512] == 16
-    assert seen[256, 4096] == 4 and seen[1024, 1024] == 16 and seen[4096, 1024] == 32
+    for rp, few in ((4, (4, 8, 16)), (8, (2, 4, 8)), (16, (2, 4, 8))):
+        assert (seen[rp, 128, 128], seen[rp, 256, 256], seen[rp, 512, 512]) == few
+        assert seen[rp, 256, 4096] == 4 and seen[rp, 1024, 1024] == 16 and seen[rp, 4096, 1024] == 32

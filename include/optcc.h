@@ -31,8 +31,9 @@
  *   the array (never past the last row's last element), and what they read
  *   there is not used; occ_step_rows reads the listed rows only.  err is read
  *   inside its rows only.
- * - Any alignment is accepted; 16-byte aligned bases with ld a multiple of 4
- *   select the vectorised load path.
+ * - Any alignment is accepted, with vector accesses at any; rows that start on
+ *   16 bytes (outputs: on 64 bytes, ld a multiple of 16) and hold a multiple of
+ *   32 columns select the fastest forms.
  * - Argument errors are detected on the host before anything is enqueued and
  *   are returned as occ_status_t; nothing aborts.  A failed kernel launch
  *   returns OCC_E_HIP.

@@ -2,11 +2,11 @@
 block more columns than it sums at once: P_hat, Q, M_hat and err against
 float64, at the error that sums of that length have.
 
-The bound is the random-walk error of fp32 sums: k products summed in sequence
-are off by about sqrt(k / 3) eps / 2 of their root mean square each; with at
-most 256 columns a sum, 16 partial sums of it and the same again for the right
-product, M_hat stays below 6e-7 on noise (measured 4.0e-7 to 4.5e-7 in sums of
-256 columns; in one sum over a block's columns, 4.4e-7 to 8.0e-7).
+An fp32 sum of k products in sequence is off by about sqrt(k) eps of its terms,
+so a sum of twice the columns adds up to 40 % to the left product's part of the
+error.  The bounds are 10 % above the errors measured with sums of the columns
+of the splits before they were merged (3.8e-7, 6.0e-7, 5.4e-7, 4.2e-7, 5.6e-7);
+in one sum over a block's columns the first two were 4.4e-7 and 8.0e-7.
 """
 
 import pytest
@@ -16,9 +16,10 @@ from gpu_util import torch_mod
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("shape,rank", [((5003, 2047), 48), ((3722, 8120), 41), ((3467, 4736), 32),
-                                        ((5003, 2047), 128), ((3467, 4736), 100)])
-def test_error_of_merged_splits(shape, rank):
+@pytest.mark.parametrize("shape,rank,bound", [((5003, 2047), 48, 4.2e-7), ((3722, 8120), 41, 6.6e-7),
+                                              ((3467, 4736), 32, 5.9e-7), ((5003, 2047), 128, 4.6e-7),
+                                              ((3467, 4736), 100, 6.2e-7)])
+def test_error_of_merged_splits(shape, rank, bound):
     from paper_2301_09830_amd import optcc
     torch = torch_mod()
     m, n = shape
@@ -33,7 +34,7 @@ def test_error_of_merged_splits(shape, rank):
     ref = p @ (A.T @ p).T
     rel = ((Mh.double() - ref).norm() / ref.norm()).item()
     print(f"[sums] {m}x{n} r{rank}: M_hat {rel:.3e}", flush=True)
-    assert rel <= 6e-7
+    assert rel <= bound
     # the compress-only call runs the same sums
     Mc = 1e-3 * torch.randn((m, n), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
     ec = 0.5 * Mc.flip(0)
